@@ -9,7 +9,7 @@
 // replayed.
 #include <type_traits>
 
-#include "tile.hpp"
+#include "real.hpp"
 
 namespace tanq {
 
@@ -154,9 +154,8 @@ __global__ __launch_bounds__(NT, (BatchMinBlocks<T, K>::value)) void batch_apply
   static_assert(sizeof(ApplyGeom) % 4 == 0, "geometry copied as dwords");
 
   __shared__ u32x4 lds[IO::SLOTS];
-  // FP32 k = 3: the out-of-place result buffer (FP64 k = 3 stays in place: its operand slices
-  // leave no registers for the second path)
-  constexpr bool kOop = K == 3 && std::is_same_v<T, float>;
+  // k = 3: the out-of-place result buffer
+  constexpr bool kOop = K == 3;
   __shared__ u32x4 lds2[kOop ? IO::SLOTS : 1];
   __shared__ ApplyGeom sg;
 
@@ -183,7 +182,7 @@ __global__ __launch_bounds__(NT, (BatchMinBlocks<T, K>::value)) void batch_apply
     const BatchChunk ch = chunks[c];
     if (ch.item != cur) {
       lds_barrier();  // the previous item's geometry is no longer read
-      const uint32_t* src = reinterpret_cast<const uint32_t*>(&items[ch.item].g);
+      const uint32_t* src = reinterpret_cast<const uint32_t*>(&items[ch.item].geom.g);
       uint32_t* dst = reinterpret_cast<uint32_t*>(&sg);
       for (int i = tid; i < (int)(sizeof(ApplyGeom) / 4); i += NT) dst[i] = src[i];
       lds_barrier();
@@ -214,37 +213,143 @@ __global__ __launch_bounds__(NT, (BatchMinBlocks<T, K>::value)) void batch_apply
   }
 }
 
-// Shapes: 16 KiB tiles for k = 2 (2^10 FP64 / 2^11 FP32 elements) and for FP32 k = 3 (2^11
-// elements, 256 threads: measured 4% more circuits/s on the serving stream than 2^12 / 512);
-// FP64 k = 3 uses 2^11 elements and 512 threads, which keeps it free of register spills.
-template <typename T, int K>
+// FP64 states are kept in real form (real.hpp): half the bytes of vec(rho) and one real product per
+// superoperator in place of the complex form's three or four.  Bound by the state traffic at 11
+// and 12 qubits, by launches below.  Bursts of 40 requests, complex form -> real form: 4-12 qubits
+// at width 3 147 -> 66.7 ms, 4-11 qubits at width 2 95 -> 49 ms.  FP32 keeps vec(rho), although the
+// real form serves it 1.9 times faster (82 -> 43 ms) with a fifth of the error: its results are
+// defined by their rounding in single precision, which would change in the seventh digit.
+// The tiles [t0, t1) of one item, in place: the next tile is prefetched into registers while the
+// current one is multiplied in one of two LDS buffers.  A wave multiplies its own groups in place,
+// so a tile takes two barriers: one between the multiplication and the store phase (which also
+// fills the other buffer with the next tile), one after it.
+template <bool FULL, typename T, typename IO, typename Op>
+__device__ inline void batch_real_tiles(T* __restrict__ rho, const IO& io, const Op& op, const BatchRuns& runs,
+                                   u32x4 (&lds)[2][IO::SLOTS], uint32_t t0, uint32_t t1, int tid) {
+  uint32_t cur = (uint32_t)runs.base(t0);
+  u32x4 buf[IO::ITERS];
+#pragma unroll
+  for (int it = 0; it < IO::ITERS; ++it)
+    if (io.template has<FULL>(it, tid)) buf[it] = *global_ptr(reinterpret_cast<const u32x4*>(rho + (cur + io.off[it])));
+#pragma unroll
+  for (int it = 0; it < IO::ITERS; ++it)
+    if (io.template has<FULL>(it, tid)) lds[0][io.lslot[it]] = buf[it];
+  lds_barrier();
+  int b = 0;
+  for (uint32_t t = t0;;) {
+    const bool more = t + 1 < t1;
+    uint32_t nbase = 0;
+    if (more) {
+      nbase = (uint32_t)runs.base(t + 1);
+#pragma unroll
+      for (int it = 0; it < IO::ITERS; ++it)
+        if (io.template has<FULL>(it, tid))
+          buf[it] = *global_ptr(reinterpret_cast<const u32x4*>(rho + (nbase + io.off[it])));
+    }
+    op.template compute<FULL>(reinterpret_cast<T*>(lds[b]));
+    lds_barrier();  // results complete
+#pragma unroll
+    for (int it = 0; it < IO::ITERS; ++it)
+      if (io.template has<FULL>(it, tid)) *global_ptr(reinterpret_cast<u32x4*>(rho + (cur + io.off[it]))) = lds[b][io.lslot[it]];
+    if (more) {
+#pragma unroll
+      for (int it = 0; it < IO::ITERS; ++it)
+        if (io.template has<FULL>(it, tid)) lds[b ^ 1][io.lslot[it]] = buf[it];
+    }
+    lds_barrier();  // this buffer is read out, the other one filled (or both free for the next chunk)
+    if (!more) break;
+    ++t;
+    b ^= 1;
+    cur = nbase;
+  }
+}
+
+template <typename T, int K, int VMAX, int NT>
+__global__ __launch_bounds__(NT, 2) void batch_real_kernel(const BatchItem* __restrict__ items,
+                                                         const BatchChunk* __restrict__ chunks,
+                                                         uint32_t* __restrict__ count) {
+  using IO = RealIo<T, VMAX, NT>;
+  using Op = OpReal<T, K, VMAX, NT>;
+  static_assert(sizeof(RealGeom) % 4 == 0, "geometry copied as dwords");
+
+  __shared__ u32x4 lds[2][IO::SLOTS];
+  __shared__ RealGeom sg;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t nch = count[0];
+  __shared__ uint32_t s_next;
+
+  uint32_t cur = 0xffffffffu;
+  bool full = false;
+  IO io;
+  Op op;
+  BatchRuns runs;
+  T* rho = nullptr;
+  for (;;) {
+    // dynamic assignment: each workgroup claims the next chunk (count[1], zeroed by the copy of
+    // the work list that precedes every launch), so the launch ends when its last chunks do
+    if (tid == 0) s_next = atomicAdd(&count[1], 1u);
+    lds_barrier();
+    const uint32_t c = s_next;
+    lds_barrier();
+    if (c >= nch) break;
+    const BatchChunk ch = chunks[c];
+    if (ch.item != cur) {
+      lds_barrier();  // the previous item's geometry is no longer read
+      const uint32_t* src = reinterpret_cast<const uint32_t*>(&items[ch.item].geom.rg);
+      uint32_t* dst = reinterpret_cast<uint32_t*>(&sg);
+      for (int i = tid; i < (int)(sizeof(RealGeom) / 4); i += NT) dst[i] = src[i];
+      lds_barrier();
+      rho = reinterpret_cast<T*>(items[ch.item].rho);
+      const T* frag = reinterpret_cast<const T*>(items[ch.item].frag);
+      io.init(sg, tid);
+      op.load(frag, lane);
+      op.prepare(sg, lane, wave);
+      runs.load(sg);
+      full = __builtin_amdgcn_readfirstlane(sg.V) == VMAX;
+      cur = ch.item;
+    }
+    if (ch.tile_begin >= ch.tile_end) continue;
+    if (full)
+      batch_real_tiles<true, T>(rho, io, op, runs, lds, ch.tile_begin, ch.tile_end, tid);
+    else
+      batch_real_tiles<false, T>(rho, io, op, runs, lds, ch.tile_begin, ch.tile_end, tid);
+  }
+}
+
+// Shapes.  FP32: 16 KiB tiles (2^11 elements; k = 3: measured 4% more circuits/s on the serving
+// stream than 2^12 / 512).  FP64 (real form): 2^12 elements (32 KiB), which give each of four waves
+// one 16-group column block at k = 3 and four at k = 2.
+template <typename T>
 struct BatchShape;
 template <>
-struct BatchShape<double, 2> { static constexpr int V = 10, NT = 256; };
+struct BatchShape<double> { static constexpr int V = 12, NT = 256; };
 template <>
-struct BatchShape<float, 2> { static constexpr int V = 11, NT = 256; };
-template <>
-struct BatchShape<double, 3> { static constexpr int V = 11, NT = 512; };
-template <>
-struct BatchShape<float, 3> { static constexpr int V = 11, NT = 256; };
+struct BatchShape<float> { static constexpr int V = 11, NT = 256; };
 
-int batch_tile_bits(int k, tanq_prec p) {
-  if (k == 2) return p == TANQ_F64 ? BatchShape<double, 2>::V : BatchShape<float, 2>::V;
-  return p == TANQ_F64 ? BatchShape<double, 3>::V : BatchShape<float, 3>::V;
+template <typename T, int K>
+static constexpr auto batch_kernel() {
+  if constexpr (sizeof(T) == 8)
+    return batch_real_kernel<T, K, BatchShape<T>::V, BatchShape<T>::NT>;
+  else
+    return batch_apply_kernel<T, K, BatchShape<T>::V, BatchShape<T>::NT>;
 }
+
+int batch_tile_bits(tanq_prec p) { return p == TANQ_F64 ? BatchShape<double>::V : BatchShape<float>::V; }
 
 // Persistent grid of the batched kernel: as many workgroups as fit on the device at once.
 template <typename T, int K>
 static unsigned batch_grid_typed() {
-  constexpr int NT = BatchShape<T, K>::NT;
+  constexpr int NT = BatchShape<T>::NT;
   static thread_local int cap_dev = -1;
   static thread_local unsigned cap = 0;
   int dev = 0;
   TANQ_HIP(hipGetDevice(&dev));
   if (cap_dev != dev) {
     int per_cu = 0;
-    TANQ_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &per_cu, batch_apply_kernel<T, K, BatchShape<T, K>::V, NT>, NT, 0));
+    TANQ_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel<T, K>(), NT, 0));
     cap = (unsigned)(device_cu_count() * (per_cu < 1 ? 1 : per_cu));
     cap_dev = dev;
   }
@@ -260,9 +365,8 @@ int batch_grid(int k, tanq_prec p) {
 template <typename T, int K>
 static void launch_batch_typed(const BatchItem* items, const BatchChunk* chunks, uint32_t* count,
                                hipStream_t s) {
-  constexpr int V = BatchShape<T, K>::V, NT = BatchShape<T, K>::NT;
-  hipLaunchKernelGGL((batch_apply_kernel<T, K, V, NT>), dim3(batch_grid_typed<T, K>()), dim3(NT), 0, s, items,
-                     chunks, count);
+  auto kern = batch_kernel<T, K>();
+  hipLaunchKernelGGL(kern, dim3(batch_grid_typed<T, K>()), dim3(BatchShape<T>::NT), 0, s, items, chunks, count);
   TANQ_HIP(hipGetLastError());
 }
 

@@ -103,12 +103,34 @@ struct FuseBlockDev {
   int64_t pack_off;   // offset (elements of the packed precision) of the packed operand
 };
 
+// One superoperator apply on a state in real form (real.hpp): tiles as in ApplyGeom, with real
+// elements.  Local index bits are the target bits in ascending tile position.
+constexpr int kRealSwzPairs = 6;
+struct RealGeom {
+  uint32_t ntiles;                // 2^(2n - V)
+  uint32_t free_mask;             // tile bits that index groups inside the tile
+  int32_t V;                      // tile bits
+  int32_t G;                      // groups per tile = 2^(V - 2k)
+  int32_t nruns;                  // runs of fixed bits
+  uint8_t vpos[16];               // tile bit -> global bit (ascending)
+  uint8_t tpos[8];                // local index bit -> tile bit (ascending)
+  uint8_t xsrc[8];                // LDS swizzle: tile bit xsrc[p] is XORed into bit xdst[p],
+  uint8_t xdst[8];                // p < kRealSwzPairs (unused pairs: source bit 31)
+  uint8_t run_src[8];             // first tile-id bit of run r
+  uint8_t run_len[8];             // length of run r
+  uint8_t run_dst[8];             // first global bit of run r
+};
+
 // Serving: one batched launch applies one superoperator to each of many states.  Items and
 // chunks live in device memory; a chunk is a range of tiles of one item.
+union BatchGeom {
+  ApplyGeom g;   // FP32: vec(rho)
+  RealGeom rg;   // FP64: real form
+};
 struct BatchItem {
   uint64_t rho;   // device address of the state
   uint64_t frag;  // device address of the packed operand
-  ApplyGeom g;
+  BatchGeom geom;
 };
 
 struct BatchChunk {
@@ -128,6 +150,8 @@ constexpr int packed_elems(int k) { return k == 1 ? 32 : (k == 2 ? 32 * 32 : 4 *
 // ------------------------------------------------------------------------------------
 
 ApplyGeom make_apply_geom(int n, int k, const int* qubits, int vbits, tanq_prec p);
+// Geometry of one k-qubit superoperator (qubits ascending) on a state in real form.
+RealGeom make_real_geom(int n, int k, const int* qubits, int vbits, tanq_prec p);
 
 // Apply-kernel variants per (k, precision), k in {2, 3}: count, shape, process-wide choice.
 int variant_count(int k, tanq_prec p);
@@ -193,6 +217,21 @@ void launch_pack(const FuseBlockDev* blocks, int nblocks, const double* raw, voi
 // Pack a single FP64 superoperator (device) of width k.
 void launch_pack_one(int k, const double* raw, void* packed, tanq_prec p, hipStream_t s);
 
+// Real form (real.hip).  Superoperators of every operation as real 4^j x 4^j matrices (offset sop_off,
+// in doubles), their composition per block in circuit order, packed as the real apply kernels'
+// operands; FP64, rounded once.  Every block has k qubits (2 or 3).
+void launch_build_real(const FuseOpDev* ops, int nops, const double* kraus, double* sops, hipStream_t s);
+void launch_compose_real(const FuseBlockDev* blocks, int nblocks, int k, const FuseOpDev* ops, const double* sops,
+                         void* packed, tanq_prec p, hipStream_t s);
+// w = the real form of |0..0><0..0|
+void launch_real_init(void* w, int n, tanq_prec p, hipStream_t s);
+// Outputs of a state in real form, n <= kRealOutMaxN: out[0] = the trace, then the 2^n probabilities
+// divided by it if want_probs, then (Re, Im) of count Pauli expectations (masks: x, z, #Y mod 4 per
+// string, as launch_pauli).  masks and out are device-accessible (pinned host memory).
+constexpr int kRealOutMaxN = 14;
+void launch_real_outputs(const void* w, int n, tanq_prec p, int want_probs, int count, const uint64_t* masks,
+                         double* out, hipStream_t s);
+
 // Reductions (FP64).  partials: device scratch of at least reduce_partials() doubles.
 int reduce_partials();
 void launch_diag(const void* rho, int n, tanq_prec p, double* probs_dev, double* partials,
@@ -218,9 +257,9 @@ void launch_compare(const void* a, tanq_prec pa, const void* b, tanq_prec pb, ui
 
 int device_cu_count();
 
-// Tile bits of the batched kernel for width k (2 or 3) and precision p (geometry of the items
-// must be built with this value).
-int batch_tile_bits(int k, tanq_prec p);
+// Tile bits of the batched kernel of precision p (geometry of the items must be built with this
+// value).
+int batch_tile_bits(tanq_prec p);
 // Workgroups of the batched kernel's persistent grid on the current device.
 int batch_grid(int k, tanq_prec p);
 // Apply the items of `*count` chunks (count lives in device memory so the launch can be

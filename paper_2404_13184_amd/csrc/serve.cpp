@@ -5,7 +5,8 @@
 // scheduler thread owns one HIP stream.  Each iteration it
 //   1. admits waiting requests (FIFO) while their footprint fits: fuses the circuit on the GPU
 //      (superoperators, FP64 composition, packing, all blocks widened to the server's width)
-//      and initialises rho = |0..0><0..0|;
+//      and initialises rho = |0..0><0..0|.  A state starts Hermitian and only Kraus sets act on
+//      it, so in FP64 it lives in real form (real.hpp), and so do its operands;
 //   2. builds the work of S steps: in step s every active request contributes its next fused
 //      superoperator as one batch item, split into chunks of tiles;
 //   3. launches the S batched kernels (captured once in a hipGraph per work buffer and
@@ -102,7 +103,7 @@ struct ServeRequest {
   size_t res_off = 0, res_size = 0;
   size_t rho_off = 0;
   std::vector<size_t> pack_off;  // per fused block (absolute arena offsets)
-  std::vector<ApplyGeom> geom;   // per fused block
+  std::vector<BatchGeom> geom;   // per fused block
   size_t cursor = 0;
   bool finishing = false;  // its reductions are queued; leaves the resident set
   tanq_status drop = TANQ_OK;  // TANQ_E_CANCELED / TANQ_E_TIMEOUT: stop and free it, no outputs
@@ -288,13 +289,24 @@ void tanq_server_s::admit_one(ServeRequest* r) {
   hipEvent_t ev = get_event();
   TANQ_HIP(hipEventRecord(ev, adm_stream));
   staged.push_back({ev, stage_off, stage_size});
-  run_fuse_kernels(L, (const FuseOpDev*)tmp, (const FuseBlockDev*)(tmp + ops_b), (const double*)(tmp + ops_b + blk_b),
-                   (double*)(tmp + ops_b + blk_b + kr_b), (double*)(tmp + ops_b + blk_b + kr_b + sop_b),
-                   arena_base + keep_off + rho_b, p, adm_stream);
+  const FuseOpDev* d_ops = (const FuseOpDev*)tmp;
+  const FuseBlockDev* d_blk = (const FuseBlockDev*)(tmp + ops_b);
+  const double* d_kraus = (const double*)(tmp + ops_b + blk_b);
+  double* d_sops = (double*)(tmp + ops_b + blk_b + kr_b);
+  if (p == TANQ_F64) {
+    launch_build_real(d_ops, (int)L.ops.size(), d_kraus, d_sops, adm_stream);
+    launch_compose_real(d_blk, (int)L.blocks.size(), w, d_ops, d_sops, arena_base + keep_off + rho_b, p, adm_stream);
+  } else {
+    run_fuse_kernels(L, d_ops, d_blk, d_kraus, d_sops, (double*)(tmp + ops_b + blk_b + kr_b + sop_b),
+                     arena_base + keep_off + rho_b, p, adm_stream);
+  }
   // every later user of this region is ordered after the fusion kernels: other admissions run
   // on the same stream, and only admissions allocate from the arena
   arena.release(tmp_off, tmp_size);
-  launch_init_zero(arena_base + r->rho_off, r->n, p, adm_stream);
+  if (p == TANQ_F64)
+    launch_real_init(arena_base + r->rho_off, r->n, p, adm_stream);
+  else
+    launch_init_zero(arena_base + r->rho_off, r->n, p, adm_stream);
   // the batched launches (on the other stream) take the request only once this has completed,
   // checked on the host, so they never wait on the admission stream
   r->ready_ev = get_event();
@@ -303,10 +315,13 @@ void tanq_server_s::admit_one(ServeRequest* r) {
 
   r->pack_off.resize(L.host.size());
   r->geom.resize(L.host.size());
-  const int vb = batch_tile_bits(w, p);
+  const int vb = batch_tile_bits(p);
   for (size_t i = 0; i < L.host.size(); ++i) {
     r->pack_off[i] = keep_off + rho_b + L.host[i].pack_off;
-    r->geom[i] = make_apply_geom(r->n, w, L.host[i].qubits, vb, p);
+    if (p == TANQ_F64)
+      r->geom[i].rg = make_real_geom(r->n, w, L.host[i].qubits, vb, p);
+    else
+      r->geom[i].g = make_apply_geom(r->n, w, L.host[i].qubits, vb, p);
   }
   r->cursor = 0;
   r->t_admit = now();
@@ -383,7 +398,7 @@ void tanq_server_s::run_iteration() {
       BatchItem& it = items[ni];
       it.rho = (uint64_t)(uintptr_t)(arena_base + r->rho_off);
       it.frag = (uint64_t)(uintptr_t)(arena_base + r->pack_off[r->cursor]);
-      it.g = r->geom[r->cursor];
+      it.geom = r->geom[r->cursor];
       ++ni;
       r->cursor += 1;
       if (r->cursor == r->geom.size()) {
@@ -400,7 +415,7 @@ void tanq_server_s::run_iteration() {
     uint64_t remaining = 0;
     for (uint32_t i = 0; i < ni; ++i) {
       order[i] = i;
-      ntiles[i] = items[i].g.ntiles;
+      ntiles[i] = cfg.prec == TANQ_F64 ? items[i].geom.rg.ntiles : items[i].geom.g.ntiles;
       remaining += ntiles[i];
     }
     std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return ntiles[a] > ntiles[b]; });
@@ -459,6 +474,13 @@ void tanq_server_s::run_iteration() {
       }
       unsigned char* rho = arena_base + r->rho_off;
       double* hres = (double*)(pinned_base + r->res_off);
+      if (p == TANQ_F64) {  // one kernel, straight into the pinned result region
+        const size_t np = r->paulis.size(), nprob = r->want_probs ? (size_t)1 << r->n : 0;
+        uint64_t* masks = (uint64_t*)(hres + 1 + nprob + 2 * np);
+        if (np) std::memcpy(masks, r->paulis.data(), 3 * np * sizeof(uint64_t));
+        launch_real_outputs(rho, r->n, p, r->want_probs, (int)np, masks, hres, stream);
+        continue;
+      }
       launch_diag(rho, r->n, p, probs_dev, partials, result_dev, 1, stream);
       TANQ_HIP(hipMemcpyAsync(hres, result_dev, sizeof(double), hipMemcpyDeviceToHost, stream));
       if (r->want_probs)
@@ -583,7 +605,8 @@ void tanq_server_s::loop() {
       bool deferred = false;  // a request went back to the queue for lack of memory
       for (ServeRequest* r : to_admit) {
         size_t roff = 0;
-        r->res_size = (1 + (r->want_probs ? ((size_t)1 << r->n) : 0) + 2 * r->paulis.size()) * sizeof(double);
+        // trace, probabilities, (Re, Im) per string, and (FP64) the strings' masks for the kernel
+        r->res_size = (1 + (r->want_probs ? ((size_t)1 << r->n) : 0) + 5 * r->paulis.size()) * sizeof(double);
         bool ok = pinned.alloc(r->res_size, &roff);
         r->res_off = roff;
         try {
