@@ -267,7 +267,14 @@ tanq_status tanq_autotune_dense(tanq_dm d, int reps, double* ms_per_apply);
  * 128-byte lines of vec(rho), with at most 4 (FP64) or 6 (FP32) superoperators.  With passes
  * enabled, tanq_fuse also orders commuting blocks so that blocks sharing a pass are adjacent,
  * and widens 1-qubit blocks that join a pass to 2 qubits (the identity on the added qubit).  The limit is
- * the most superoperators per pass, 1..8 (1 = no passes; default 8), process-wide. */
+ * the most superoperators per pass, 1..8 (1 = no passes; default 8), process-wide.
+ *
+ * Long FP64 lists (11 to 16 qubits, at least 12 launches as tanq_fused_launches counts them, passes
+ * not switched off) on an exactly Hermitian rho are applied in real form: the 4^n Pauli expectations, on
+ * which every superoperator is a real matrix, formed in place before the first superoperator and
+ * turned back after the last.  The device checks rho and chooses; the call stays asynchronous and the
+ * results agree with the blocks applied one by one to rounding (exactly Hermitian).  Any other rho
+ * takes the launches that tanq_fused_launches lists. */
 tanq_status tanq_set_pass_limit(int max_superops);
 tanq_status tanq_get_pass_limit(int* max_superops);
 /* How tanq_apply_fused groups f's blocks under the current limit: *passes receives the number
@@ -277,7 +284,8 @@ tanq_status tanq_fused_passes(tanq_fused f, int* passes, int* in_passes);
 /* The launches tanq_apply_fused makes for f, in order: run_len[i] blocks (1 = a single apply,
  * >= 2 = a pass) starting where launch i - 1 ended.  *count receives the number of launches;
  * run_len may be NULL to query it (E_ARG if cap is smaller).  Applying f launch by launch with
- * tanq_apply_fused_range over these ranges gives the same launches.  Host only. */
+ * tanq_apply_fused_range over these ranges gives the same launches (a list applied in real form, see
+ * tanq_set_pass_limit, agrees with them to rounding).  Host only. */
 tanq_status tanq_fused_launches(tanq_fused f, int* run_len, int cap, int* count);
 /* Diagnostics of one pass layout (host only): m 2-qubit superoperators on n qubits, qubits =
  * m pairs; *conflict_free receives how many of the 2 m LDS access patterns (the MFMA operand

@@ -42,13 +42,14 @@ namespace tanq {
 // only drains the vector-memory counter down to the number of outstanding stores).
 template <typename T, int K, int VMAX, int NT, bool FULL>
 __global__ __launch_bounds__(NT) void apply_tiles_kernel(T* __restrict__ rho, const T* __restrict__ frag,
-                                                         const ApplyGeom g) {
+                                                         const ApplyGeom g, const uint32_t* skip) {
   using IO = TileIo<T, VMAX, NT>;
   using Op = std::conditional_t<K == 2, Op2<T, VMAX, NT>, Op3<T, VMAX, NT>>;
   using c2 = typename Mfma<T>::c2;
 
   __shared__ u32x4 lds[IO::SLOTS];
 
+  if (skip_launch(skip)) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -112,13 +113,14 @@ __global__ __launch_bounds__(NT) void apply_tiles_kernel(T* __restrict__ rho, co
 // tile's loads, are allowed to remain outstanding.
 template <typename T, int K, int VMAX, int NT>
 __global__ __launch_bounds__(NT) void apply_dma_kernel(T* __restrict__ rho, const T* __restrict__ frag,
-                                                       const ApplyGeom g) {
+                                                       const ApplyGeom g, const uint32_t* skip) {
   using IO = TileDma<T, VMAX, NT>;
   using Op = std::conditional_t<K == 2, Op2<T, VMAX, NT>, Op3<T, VMAX, NT>>;
   using c2 = typename Mfma<T>::c2;
 
   __shared__ u32x4 lds[2][IO::SLOTS];
 
+  if (skip_launch(skip)) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -175,7 +177,7 @@ __global__ __launch_bounds__(NT) void apply_dma_kernel(T* __restrict__ rho, cons
 // The direct-staging instances of the variant table, instantiated explicitly (implicit
 // instantiation through the launch table did not emit every host-side kernel handle).
 #define TANQ_DMA_INSTANCE(T, K, V, NT) \
-  template __global__ void apply_dma_kernel<T, K, V, NT>(T*, const T*, const ApplyGeom);
+  template __global__ void apply_dma_kernel<T, K, V, NT>(T*, const T*, const ApplyGeom, const uint32_t*);
 TANQ_DMA_INSTANCE(double, 2, 11, 256)
 TANQ_DMA_INSTANCE(double, 2, 12, 512)
 TANQ_DMA_INSTANCE(double, 3, 12, 512)
@@ -193,7 +195,8 @@ TANQ_DMA_INSTANCE(float, 3, 11, 256)
 
 template <typename T>
 __global__ __launch_bounds__(256) void apply_c1_kernel(T* __restrict__ rho, const double* __restrict__ S,
-                                                      const C1Geom g) {
+                                                      const C1Geom g, const uint32_t* skip) {
+  if (skip_launch(skip)) return;
   using c2 = typename Mfma<T>::c2;
   T sr[16], si[16];
 #pragma unroll
@@ -397,7 +400,7 @@ static uint64_t persistent_cap(KernelT kernel, int threads) {
 }
 
 template <typename T, int K, int VMAX, int NT, bool FULL>
-static void launch_tiles(const ApplyGeom& g, void* rho, const void* frag, hipStream_t s) {
+static void launch_tiles(const ApplyGeom& g, void* rho, const void* frag, hipStream_t s, const uint32_t* skip) {
   auto kern = apply_tiles_kernel<T, K, VMAX, NT, FULL>;
   static thread_local int cap_dev = -1;
   static thread_local uint64_t cap = 0;
@@ -408,12 +411,12 @@ static void launch_tiles(const ApplyGeom& g, void* rho, const void* frag, hipStr
     cap_dev = dev;
   }
   const uint64_t grid = g.ntiles < cap ? g.ntiles : cap;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), 0, s, (T*)rho, (const T*)frag, g);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), 0, s, (T*)rho, (const T*)frag, g, skip);
   TANQ_HIP(hipGetLastError());
 }
 
 template <typename T, int K, int VMAX, int NT>
-static void launch_dma(const ApplyGeom& g, void* rho, const void* frag, hipStream_t s) {
+static void launch_dma(const ApplyGeom& g, void* rho, const void* frag, hipStream_t s, const uint32_t* skip) {
   auto kern = apply_dma_kernel<T, K, VMAX, NT>;
   static thread_local int cap_dev = -1;
   static thread_local uint64_t cap = 0;
@@ -424,26 +427,26 @@ static void launch_dma(const ApplyGeom& g, void* rho, const void* frag, hipStrea
     cap_dev = dev;
   }
   const uint64_t grid = g.ntiles < cap ? g.ntiles : cap;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), 0, s, (T*)rho, (const T*)frag, g);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), 0, s, (T*)rho, (const T*)frag, g, skip);
   TANQ_HIP(hipGetLastError());
 }
 
 // STAGING 0: register prefetch (apply_tiles_kernel); 1: direct global-to-LDS loads into two
 // LDS buffers (apply_dma_kernel) for full tiles, the register kernel for partial ones.
 template <typename T, int K, int VMAX, int NT, int STAGING>
-static void launch_variant(void* rho, int n, const int* qubits, const void* frag, hipStream_t s) {
+static void launch_variant(void* rho, int n, const int* qubits, const void* frag, hipStream_t s, const uint32_t* skip) {
   const ApplyGeom g = make_apply_geom(n, K, qubits, VMAX, sizeof(T) == 8 ? TANQ_F64 : TANQ_F32);
   if (g.V == VMAX) {
     if constexpr (STAGING == 1)
-      launch_dma<T, K, VMAX, NT>(g, rho, frag, s);
+      launch_dma<T, K, VMAX, NT>(g, rho, frag, s, skip);
     else
-      launch_tiles<T, K, VMAX, NT, true>(g, rho, frag, s);
+      launch_tiles<T, K, VMAX, NT, true>(g, rho, frag, s, skip);
   } else {
-    launch_tiles<T, K, VMAX, NT, false>(g, rho, frag, s);
+    launch_tiles<T, K, VMAX, NT, false>(g, rho, frag, s, skip);
   }
 }
 
-typedef void (*apply_fn)(void*, int, const int*, const void*, hipStream_t);
+typedef void (*apply_fn)(void*, int, const int*, const void*, hipStream_t, const uint32_t*);
 
 struct VariantEntry {
   int k;
@@ -564,13 +567,14 @@ int variant_for(int n, int k, tanq_prec p) {
 }
 
 void launch_apply_variant(void* rho, int n, tanq_prec p, int k, int local, const int* qubits, const void* packed,
-                          hipStream_t s) {
+                          hipStream_t s, const uint32_t* skip) {
   const int gi = variant_global_index(k, p, local);
   if (gi < 0) fail(TANQ_E_ARG, "no such apply variant");
-  kVariants[gi].fn(rho, n, qubits, packed, s);
+  kVariants[gi].fn(rho, n, qubits, packed, s, skip);
 }
 
-void launch_apply(void* rho, int n, tanq_prec p, int k, const int* qubits, const void* packed, hipStream_t s) {
+void launch_apply(void* rho, int n, tanq_prec p, int k, const int* qubits, const void* packed, hipStream_t s,
+                  const uint32_t* skip) {
   if (k == 1) {
     C1Geom g{1ull << (2 * (n - 1)), qubits[0], n};
     uint64_t blocks = (g.ngroups + 255) / 256;
@@ -578,15 +582,15 @@ void launch_apply(void* rho, int n, tanq_prec p, int k, const int* qubits, const
     if (blocks > cap) blocks = cap;
     if (p == TANQ_F64)
       hipLaunchKernelGGL(apply_c1_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, s, (double*)rho,
-                         (const double*)packed, g);
+                         (const double*)packed, g, skip);
     else
       hipLaunchKernelGGL(apply_c1_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, s, (float*)rho,
-                         (const double*)packed, g);
+                         (const double*)packed, g, skip);
     TANQ_HIP(hipGetLastError());
     return;
   }
   if (k != 2 && k != 3) fail(TANQ_E_ARG, "superoperator width must be 1, 2 or 3");
-  launch_apply_variant(rho, n, p, k, variant_for(n, k, p), qubits, packed, s);
+  launch_apply_variant(rho, n, p, k, variant_for(n, k, p), qubits, packed, s, skip);
 }
 
 void launch_pack(const FuseBlockDev* blocks, int nblocks, const double* raw, void* packed, tanq_prec p,

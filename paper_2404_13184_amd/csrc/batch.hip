@@ -219,51 +219,6 @@ __global__ __launch_bounds__(NT, (BatchMinBlocks<T, K>::value)) void batch_apply
 // at width 3 147 -> 66.7 ms, 4-11 qubits at width 2 95 -> 49 ms.  FP32 keeps vec(rho), although the
 // real form serves it 1.9 times faster (82 -> 43 ms) with a fifth of the error: its results are
 // defined by their rounding in single precision, which would change in the seventh digit.
-// The tiles [t0, t1) of one item, in place: the next tile is prefetched into registers while the
-// current one is multiplied in one of two LDS buffers.  A wave multiplies its own groups in place,
-// so a tile takes two barriers: one between the multiplication and the store phase (which also
-// fills the other buffer with the next tile), one after it.
-template <bool FULL, typename T, typename IO, typename Op>
-__device__ inline void batch_real_tiles(T* __restrict__ rho, const IO& io, const Op& op, const BatchRuns& runs,
-                                   u32x4 (&lds)[2][IO::SLOTS], uint32_t t0, uint32_t t1, int tid) {
-  uint32_t cur = (uint32_t)runs.base(t0);
-  u32x4 buf[IO::ITERS];
-#pragma unroll
-  for (int it = 0; it < IO::ITERS; ++it)
-    if (io.template has<FULL>(it, tid)) buf[it] = *global_ptr(reinterpret_cast<const u32x4*>(rho + (cur + io.off[it])));
-#pragma unroll
-  for (int it = 0; it < IO::ITERS; ++it)
-    if (io.template has<FULL>(it, tid)) lds[0][io.lslot[it]] = buf[it];
-  lds_barrier();
-  int b = 0;
-  for (uint32_t t = t0;;) {
-    const bool more = t + 1 < t1;
-    uint32_t nbase = 0;
-    if (more) {
-      nbase = (uint32_t)runs.base(t + 1);
-#pragma unroll
-      for (int it = 0; it < IO::ITERS; ++it)
-        if (io.template has<FULL>(it, tid))
-          buf[it] = *global_ptr(reinterpret_cast<const u32x4*>(rho + (nbase + io.off[it])));
-    }
-    op.template compute<FULL>(reinterpret_cast<T*>(lds[b]));
-    lds_barrier();  // results complete
-#pragma unroll
-    for (int it = 0; it < IO::ITERS; ++it)
-      if (io.template has<FULL>(it, tid)) *global_ptr(reinterpret_cast<u32x4*>(rho + (cur + io.off[it]))) = lds[b][io.lslot[it]];
-    if (more) {
-#pragma unroll
-      for (int it = 0; it < IO::ITERS; ++it)
-        if (io.template has<FULL>(it, tid)) lds[b ^ 1][io.lslot[it]] = buf[it];
-    }
-    lds_barrier();  // this buffer is read out, the other one filled (or both free for the next chunk)
-    if (!more) break;
-    ++t;
-    b ^= 1;
-    cur = nbase;
-  }
-}
-
 template <typename T, int K, int VMAX, int NT>
 __global__ __launch_bounds__(NT, 2) void batch_real_kernel(const BatchItem* __restrict__ items,
                                                          const BatchChunk* __restrict__ chunks,
@@ -312,10 +267,11 @@ __global__ __launch_bounds__(NT, 2) void batch_real_kernel(const BatchItem* __re
       cur = ch.item;
     }
     if (ch.tile_begin >= ch.tile_end) continue;
+    auto base = [&](uint32_t t) { return (uint32_t)runs.base(t); };
     if (full)
-      batch_real_tiles<true, T>(rho, io, op, runs, lds, ch.tile_begin, ch.tile_end, tid);
+      real_tiles<true, T>(rho, io, op, base, lds, ch.tile_begin, ch.tile_end, tid);
     else
-      batch_real_tiles<false, T>(rho, io, op, runs, lds, ch.tile_begin, ch.tile_end, tid);
+      real_tiles<false, T>(rho, io, op, base, lds, ch.tile_begin, ch.tile_end, tid);
   }
 }
 

@@ -84,6 +84,27 @@ struct PassGeom {
   uint8_t run_dst[16];
 };
 
+// Real-form passes over one FP64 state (herm.hip).  Address bit A(b) of a state element: index bit
+// 2n - 1 (the top column bit) is address bit 0, index bit b is address bit b + 1, so the 4^n reals
+// fill the lower half of vec(rho)'s memory and the pair that differs in the top column bit shares
+// the 16 bytes of the lower element of the pair.
+constexpr int kHermMinN = 11, kHermMaxN = 16;
+constexpr int kHermMinLaunches = 12;
+constexpr int kRealPassBits = 13;  // 2^13 reals = 64 KiB
+constexpr int kRealPassMax = 8;    // superoperators whose operands fit in registers
+constexpr int kRealPassThreads = 512;
+struct RealPassGeom {
+  uint64_t ntiles;                      // 2^(2n - 13)
+  uint64_t dmask;                       // address bits outside the tile
+  uint64_t goff[12];                    // address offset of tile element S(2^(b + 1)): bit b of a slot index
+  uint32_t op_off[kRealPassMax];        // element offset of superoperator j's operand
+  uint16_t sbit[kRealPassMax][13];      // LDS byte offset of index bit b of superoperator j: b < 9 group
+                                        // bits, then its four local index bits (ascending)
+  uint8_t emb[kRealPassMax];            // 0: a 16 x 16 operand; else a one-qubit 4 x 4 operand on the local
+                                        // bits emb & 3 and (emb >> 2) & 3, the identity on the others (bit 4 set)
+  int32_t m;
+};
+
 // Fusion: a block of consecutive operations on at most k qubits.
 struct FuseOpDev {
   int32_t j;          // qubits of the operation
@@ -150,8 +171,9 @@ constexpr int packed_elems(int k) { return k == 1 ? 32 : (k == 2 ? 32 * 32 : 4 *
 // ------------------------------------------------------------------------------------
 
 ApplyGeom make_apply_geom(int n, int k, const int* qubits, int vbits, tanq_prec p);
-// Geometry of one k-qubit superoperator (qubits ascending) on a state in real form.
-RealGeom make_real_geom(int n, int k, const int* qubits, int vbits, tanq_prec p);
+// Geometry of one k-qubit superoperator on a state in real form: tbits = its 2k target bits in the
+// state's element address (any order), nb = 2n.
+RealGeom make_real_geom(int nb, int k, const int* tbits, int vbits, tanq_prec p);
 
 // Apply-kernel variants per (k, precision), k in {2, 3}: count, shape, process-wide choice.
 int variant_count(int k, tanq_prec p);
@@ -164,8 +186,9 @@ bool variant_tune(int n, int k, tanq_prec p, int index);
 int variant_tuned(int n, int k, tanq_prec p);
 int variant_for(int n, int k, tanq_prec p);
 int variant_find(int k, tanq_prec p, int tile_bits, int threads, int staging);
+// skip (may be NULL): device flag; the launch does nothing where it is set.
 void launch_apply_variant(void* rho, int n, tanq_prec p, int k, int index, const int* qubits, const void* packed,
-                          hipStream_t s);
+                          hipStream_t s, const uint32_t* skip = nullptr);
 
 // Passes (pass.hip): tile bits per precision; geometry of m superoperators (qubits: m pairs,
 // op_off: element offsets of their packed operands); launch on one state.
@@ -178,9 +201,33 @@ int pass_max(tanq_prec p);
 PassGeom make_pass_geom(int n, int m, const int* qubits, const uint32_t* op_off, tanq_prec p,
                         int* conflict_free = nullptr, int* achievable = nullptr);
 void launch_pass(void* rho, tanq_prec p, const PassGeom& g, const void* frags, hipStream_t s);
+// One launch for a pass of either form of an FP64 state: where *flag is set the real-form one (rg, rpacked;
+// NULL: nothing), else the complex one (g, frags; NULL: nothing).
+void launch_pass_either(void* rho, const PassGeom* g, const void* frags, const RealPassGeom* rg, const double* rpacked,
+                        const uint32_t* flag, hipStream_t s);
 // Process-wide limit on superoperators per pass (1 = no passes).
 int pass_limit();
 void set_pass_limit(int m);
+
+// Real-form passes over one FP64 state (herm.hip).  qubits: k[j] per superoperator, three apart.
+bool real_pass_fits(uint64_t qmask, int n);
+RealPassGeom make_real_pass_geom(int n, int m, const int* k, const int* qubits, const uint32_t* op_off);
+// Real operands of every block (k = 1: 4 x 4; k = 2, 3: fragments), local index bits in ascending
+// address order; elements per block real_pack_elems(k), offset of block b at off[b] (device table).
+constexpr int real_pack_elems(int k) { return k == 1 ? 16 : (k == 2 ? 256 : 4096); }
+struct RealPackDev {
+  int64_t raw_off;   // complex elements
+  int64_t pack_off;  // doubles
+  int32_t k;
+  uint8_t perm[8];   // local bit of the real operand -> local bit of the superoperator
+};
+void launch_pack_herm(const RealPackDev* blocks, int nblocks, const double* raw, double* packed, hipStream_t s);
+// *flag = 1 if vec(rho) is exactly Hermitian and within range, else 0
+void launch_herm_check(const void* rho, int n, uint32_t* flag, hipStream_t s);
+// vec(rho) -> real form and back in place; nothing where *flag is 0
+void launch_herm_in(void* rho, int n, const uint32_t* flag, hipStream_t s);
+void launch_herm_out(void* rho, int n, const uint32_t* flag, hipStream_t s);
+void launch_real_apply3(void* rho, int n, const int* qubits, const double* packed, const uint32_t* flag, hipStream_t s);
 
 void launch_init_zero(void* rho, int n, tanq_prec p, hipStream_t s);
 void launch_gather(const void* rho, tanq_prec p, const uint64_t* idx_dev, size_t count, void* out_dev,
@@ -203,7 +250,7 @@ void sample_run(tanq_dm d, uint64_t shots, uint64_t seed, const double* p01, con
 //   k == 1: packed = 4x4 complex FP64 (32 doubles), used for both precisions.
 //   k == 2, 3: packed = real-block fragments in precision p.
 void launch_apply(void* rho, int n, tanq_prec p, int k, const int* qubits, const void* packed,
-                  hipStream_t s);
+                  hipStream_t s, const uint32_t* skip = nullptr);
 
 // Superoperators of every operation (sum_i conj(K_i) (x) K_i), FP64.
 void launch_build_superops(const FuseOpDev* ops, int nops, const double* kraus, double* sops,

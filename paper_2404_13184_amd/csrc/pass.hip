@@ -29,7 +29,9 @@
 // superoperator ahead.  FP64 (apply_pass_kernel): eight waves that all multiply and each issue
 // their share of the loads; two waves per SIMD leave enough registers to hold the operands of
 // all (at most four) superoperators for the whole kernel.
-#include "tile.hpp"
+#include <algorithm>
+
+#include "real.hpp"
 
 namespace tanq {
 
@@ -344,26 +346,6 @@ __global__ __launch_bounds__(NT) void apply_pass_ws_kernel(T* __restrict__ rho, 
   }
 }
 
-// Direct global-to-LDS load of 16 bytes per lane into the LDS slots starting at lds_base (the
-// wave's base: lane l fills lds_base + 16 l), with the non-temporal policy.  Written as
-// assembly because the compiler cannot tell this wave's two tile buffers apart: with the
-// builtin it would wait for every such load before each LDS read of the other buffer, which
-// removes the overlap of the next tile's loads with this tile's multiplication.  The
-// instruction is the one the builtin emits: its only register operand is the address, read
-// when it issues, and it has no register outputs (the data goes to LDS), so nothing the
-// compiler allocates is written while it is in flight.  The compiler does not count it, so the
-// kernel orders it itself: no LDS access touches the destination buffer until this wave has
-// waited for its loads (vm_wait) and the workgroup has passed the barrier that publishes the
-// tile, and no load is left in flight at the end of the kernel.
-__device__ inline void pass_dma16(const void* gaddr, uint32_t lds_base) {
-  // M0 holds the LDS address; one wait state between writing M0 and the load that reads it
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gaddr), "{m0}"(lds_base) : "memory");
-}
-
-__device__ inline uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
-}
-
 // One tile of the consumer-only pass: the next tile's loads into `other`, the m superoperators
 // on `buf` with every operand in registers (ops[j]), then the store of `buf`.
 template <typename T, int VMAX, int NT, int MMAX, int ITERS, typename Ops>
@@ -407,9 +389,14 @@ __device__ inline void pass_cw_tile(T* __restrict__ rho, const Ops (&ops)[MMAX],
 // each wave waits only for its own loads of the next tile (the stores issued after them may
 // still be in flight; the memory counter drains in issue order), and the barrier that
 // publishes the next tile also frees the current buffer.
+//
+// Long lists on FP64 states queue passes of two forms, of which the device picks one (herm.hip).  A launch
+// carries a pass of each: a second launch that does nothing would cost about 4.5 us, a tenth of
+// a pass at 11 qubits.  flag NULL: the complex form.
 template <typename T, int VMAX, int NT>
 __global__ __launch_bounds__(NT) void apply_pass_kernel(T* __restrict__ rho, const T* __restrict__ frags,
-                                                        const PassGeom g) {
+                                                        const PassGeom g, const double* __restrict__ rpacked,
+                                                        const RealPassGeom rg, const uint32_t* flag) {
   constexpr int NW = NT / 64;
   constexpr int EPS = 16 / (2 * (int)sizeof(T));  // elements per 16-byte slot
   constexpr int SLOTS = (1 << VMAX) / EPS;
@@ -427,6 +414,12 @@ __global__ __launch_bounds__(NT) void apply_pass_kernel(T* __restrict__ rho, con
   __shared__ __align__(16) uint32_t stl[MMAX][20];
   __shared__ uint64_t soff[ITERS];
 
+  if (skip_launch(flag)) {
+    static_assert(sizeof(T) == 8 && NT == kRealPassThreads && SLOTS == 4096, "shapes of the real-form pass");
+    if (rg.m > 0) real_pass_tiles(reinterpret_cast<double*>(rho), rpacked, rg, ldsA, ldsB);
+    return;
+  }
+  if (g.m == 0) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -519,32 +512,49 @@ struct PassKernel<float> {
   static constexpr auto kern = apply_pass_ws_kernel<float, kPassTileBitsF32, 640, 2>;
 };
 
+// One workgroup per CU (two 64 KiB buffers), at most one per tile.
 template <typename T>
-static void launch_pass_typed(void* rho, const PassGeom& g, const void* frags, hipStream_t s) {
-  constexpr int V = PassShape<T>::V, NT = PassKernel<T>::NT;
-  if (g.V != V) fail(TANQ_E_STATE, "pass geometry built for another tile size");
-  if (g.m < 1 || g.m > PassMax<T>::M) fail(TANQ_E_STATE, "pass longer than its operand buffers");
-  auto kern = PassKernel<T>::kern;
+static unsigned pass_grid(uint64_t ntiles) {
   static thread_local int cap_dev = -1;
   static thread_local uint64_t cap = 0;
   int dev = 0;
   TANQ_HIP(hipGetDevice(&dev));
   if (cap_dev != dev) {
     int per_cu = 0;
-    TANQ_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, NT, 0));
+    TANQ_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, PassKernel<T>::kern, PassKernel<T>::NT, 0));
     cap = (uint64_t)device_cu_count() * (uint64_t)(per_cu < 1 ? 1 : per_cu);
     cap_dev = dev;
   }
-  const uint64_t grid = g.ntiles < cap ? g.ntiles : cap;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NT), 0, s, (T*)rho, (const T*)frags, g);
+  return (unsigned)(ntiles < cap ? ntiles : cap);
+}
+
+template <typename T>
+static void check_pass(const PassGeom& g) {
+  if (g.V != PassShape<T>::V) fail(TANQ_E_STATE, "pass geometry built for another tile size");
+  if (g.m < 1 || g.m > PassMax<T>::M) fail(TANQ_E_STATE, "pass longer than its operand buffers");
+}
+
+void launch_pass_either(void* rho, const PassGeom* g, const void* frags, const RealPassGeom* rg, const double* rpacked,
+                        const uint32_t* flag, hipStream_t s) {
+  using K = PassKernel<double>;
+  if (g) check_pass<double>(*g);
+  if (rg && (rg->m < 1 || rg->m > kRealPassMax)) fail(TANQ_E_STATE, "real pass length");
+  if ((!g && !rg) || (rg && !flag)) fail(TANQ_E_STATE, "pass launch without a pass or its flag");
+  const uint64_t tiles = std::max(g ? g->ntiles : 0, rg ? rg->ntiles : 0);
+  hipLaunchKernelGGL(K::kern, dim3(pass_grid<double>(tiles)), dim3(K::NT), 0, s, (double*)rho, (const double*)frags,
+                     g ? *g : PassGeom{}, rpacked, rg ? *rg : RealPassGeom{}, flag);
   TANQ_HIP(hipGetLastError());
 }
 
 void launch_pass(void* rho, tanq_prec p, const PassGeom& g, const void* frags, hipStream_t s) {
-  if (p == TANQ_F64)
-    launch_pass_typed<double>(rho, g, frags, s);
-  else
-    launch_pass_typed<float>(rho, g, frags, s);
+  if (p == TANQ_F64) {
+    launch_pass_either(rho, &g, frags, nullptr, nullptr, nullptr, s);
+    return;
+  }
+  using K = PassKernel<float>;
+  check_pass<float>(g);
+  hipLaunchKernelGGL(K::kern, dim3(pass_grid<float>(g.ntiles)), dim3(K::NT), 0, s, (float*)rho, (const float*)frags, g);
+  TANQ_HIP(hipGetLastError());
 }
 
 }  // namespace tanq

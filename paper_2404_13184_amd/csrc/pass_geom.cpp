@@ -249,5 +249,110 @@ PassGeom make_pass_geom(int n, int m, const int* qubits, const uint32_t* op_off,
   return g;
 }
 
-// Specialised-wave shape: 640 threads, 2 producer and 8 consumer waves.
+// ------------------------------------------------------------------------------------
+// real-form passes
+// ------------------------------------------------------------------------------------
+
+// address bit of index bit b (internal.hpp)
+static int real_addr_bit(int b, int n) { return b == 2 * n - 1 ? 0 : b + 1; }
+
+// Address bits a pass over these qubits holds: their row and column bits and the four lowest bits
+// (whole 128-byte lines of the state).
+static uint64_t real_pass_held(uint64_t qmask, int n) {
+  uint64_t held = 15;
+  for (int q = 0; q < n; ++q)
+    if ((qmask >> q) & 1ull) held |= (1ull << real_addr_bit(q, n)) | (1ull << real_addr_bit(q + n, n));
+  return held;
+}
+
+bool real_pass_fits(uint64_t qmask, int n) { return __builtin_popcountll(real_pass_held(qmask, n)) <= kRealPassBits; }
+
+RealPassGeom make_real_pass_geom(int n, int m, const int* k, const int* qubits, const uint32_t* op_off) {
+  if (m < 1 || m > kRealPassMax) fail(TANQ_E_STATE, "real pass length");
+  RealPassGeom g{};
+  const int nb = 2 * n, V = kRealPassBits, W = 5;
+  uint64_t qmask = 0;
+  for (int j = 0; j < m; ++j)
+    for (int t = 0; t < k[j]; ++t) qmask |= 1ull << qubits[3 * j + t];
+  // one-qubit operands need a second qubit that the pass holds
+  if (__builtin_popcountll(qmask) == 1) qmask |= (qmask & 1ull) ? 2ull : 1ull;
+  uint64_t held = real_pass_held(qmask, n);
+  if (__builtin_popcountll(held) > V) fail(TANQ_E_STATE, "real pass qubits do not fit one tile");
+  for (int b = 0; b < nb && __builtin_popcountll(held) < V; ++b) held |= 1ull << b;
+  int vpos[kRealPassBits], local_of[64], cnt = 0;
+  for (int b = 0; b < nb; ++b)
+    if ((held >> b) & 1ull) {
+      local_of[b] = cnt;
+      vpos[cnt++] = b;
+    }
+  g.m = m;
+  g.ntiles = 1ull << (nb - V);
+  g.dmask = ((1ull << nb) - 1ull) & ~held;
+
+  int tpos[kRealPassMax][4], fpos[kRealPassMax][9];
+  SwzProblem P{};
+  P.W = W;
+  P.V = V;
+  P.m = m;
+  for (int j = 0; j < m; ++j) {
+    int q0 = qubits[3 * j], q1 = k[j] == 2 ? qubits[3 * j + 1] : __builtin_ctzll(qmask & ~(1ull << q0));
+    const int bits[4] = {q0, q0 + n, q1, q1 + n};
+    uint32_t tm = 0;
+    for (int t = 0; t < 4; ++t) tm |= 1u << local_of[real_addr_bit(bits[t], n)];
+    int nt = 0, nf = 0;
+    for (int b = 0; b < V; ++b) {
+      if ((tm >> b) & 1u)
+        tpos[j][nt++] = b;
+      else
+        fpos[j][nf++] = b;
+    }
+    if (nt != 4) fail(TANQ_E_STATE, "a real pass superoperator repeats a qubit");
+    g.op_off[j] = op_off[j];
+    if (k[j] == 1) {
+      // the operand's two local bits among the four, lowest address first
+      int e[2], ne = 0;
+      for (int t = 0; t < 4; ++t)
+        if (tpos[j][t] == local_of[real_addr_bit(q0, n)] || tpos[j][t] == local_of[real_addr_bit(q0 + n, n)]) e[ne++] = t;
+      g.emb[j] = (uint8_t)(16 | e[0] | (e[1] << 2));
+    }
+    // 32 lanes of 8 bytes: 16 groups (the four lowest free bits) and the lowest target bit
+    for (int t = 0; t < 4; ++t) P.fbits[j][t] = (uint32_t)fpos[j][t];
+    P.t1[j] = P.t2[j] = 1u << tpos[j][0];
+  }
+  // swizzle columns never set bit 0 (the two elements of a 16-byte slot stay together)
+  uint8_t best[16] = {0};
+  int best_score = swz_score(P, best);
+  const int perfect = swz_bound(P);
+  uint64_t seed = 0x51EDull ^ ((uint64_t)n << 32) ^ (uint64_t)m;
+  for (int trial = 0; trial < 4000 && best_score < perfect; ++trial) {
+    uint8_t cand[16] = {0};
+    const uint64_t r = splitmix(seed);
+    for (int b = W; b < V; ++b) cand[b] = (uint8_t)((r >> (8 * (b - W))) & 30u);
+    const int sc = swz_score(P, cand);
+    if (sc > best_score) {
+      best_score = sc;
+      std::memcpy(best, cand, sizeof(best));
+    }
+  }
+  // S(e) = e ^ X(e), X from the bits above the window into the window: linear and an involution
+  auto S = [&](uint32_t e) {
+    uint32_t x = e;
+    for (int b = W; b < V; ++b)
+      if ((e >> b) & 1u) x ^= best[b];
+    return x;
+  };
+  for (int b = 0; b < 12; ++b) {
+    const uint32_t e = S(2u << b);
+    uint64_t o = 0;
+    for (int t = 0; t < V; ++t)
+      if ((e >> t) & 1u) o |= 1ull << vpos[t];
+    g.goff[b] = o;
+  }
+  for (int j = 0; j < m; ++j) {
+    for (int b = 0; b < 9; ++b) g.sbit[j][b] = (uint16_t)(8 * S(1u << fpos[j][b]));
+    for (int t = 0; t < 4; ++t) g.sbit[j][9 + t] = (uint16_t)(8 * S(1u << tpos[j][t]));
+  }
+  return g;
+}
+
 }  // namespace tanq

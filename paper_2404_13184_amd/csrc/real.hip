@@ -9,40 +9,6 @@
 
 namespace tanq {
 
-namespace {
-
-__device__ inline int ycount(uint32_t a, int k) {
-  const uint32_t m = (1u << k) - 1u;
-  return __popc(~a & (a >> k) & m);
-}
-
-// entry (a, b) of the real form of a superoperator S (4^k x 4^k complex)
-__device__ inline double real_entry(const f64x2* S, int k, uint32_t a, uint32_t b) {
-  const uint32_t m = (1u << k) - 1u;
-  const uint32_t ra = a & m, ca = a >> k, rb = b & m, cb = b >> k;
-  double sr = 0.0, si = 0.0;
-  for (uint32_t u = 0; u <= m; ++u)
-    for (uint32_t v = 0; v <= m; ++v) {
-      const f64x2 x = S[(((u ^ ra ^ ca) + (u << k)) << (2 * k)) + (v ^ rb ^ cb) + (v << k)];
-      const bool neg = (__popc(u & ca) + __popc(v & cb)) & 1;
-      sr += neg ? -x[0] : x[0];
-      si += neg ? -x[1] : x[1];
-    }
-  const int d = (ycount(a, k) - ycount(b, k)) & 3;  // Re((-i)^d (sr + i si))
-  const double v = d == 0 ? sr : (d == 1 ? si : (d == 2 ? -sr : -si));
-  return v / (double)(1u << k);
-}
-
-// fragment element e of a packed real operand: its row and column (real.hpp, OpReal)
-template <typename T>
-__device__ inline void real_frag_index(int e, int KS, int* row, int* col) {
-  const int lane = e & 63, rest = e >> 6, s = rest % KS, m = rest / KS, i = lane & 15;
-  *row = 16 * m + (Mfma<T>::kRowsStrided ? i : (i >> 2) + 4 * (i & 3));
-  *col = 4 * s + (lane >> 4);
-}
-
-}  // namespace
-
 // One workgroup per operation: S in LDS, then its real form.
 __global__ __launch_bounds__(256) void build_real_kernel(const FuseOpDev* __restrict__ ops,
                                                          const double* __restrict__ kraus, double* __restrict__ sops) {
@@ -211,14 +177,11 @@ __global__ __launch_bounds__(1024) void real_outputs_kernel(const T* __restrict_
 // host side
 // ------------------------------------------------------------------------------------
 
-RealGeom make_real_geom(int n, int k, const int* q, int vbits, tanq_prec p) {
+RealGeom make_real_geom(int nb, int k, const int* tbits, int vbits, tanq_prec p) {
   RealGeom g{};
-  const int nb = 2 * n, V = vbits < nb ? vbits : nb;
+  const int V = vbits < nb ? vbits : nb;
   uint64_t tmask = 0;
-  for (int t = 0; t < k; ++t) {
-    if (t > 0 && q[t] <= q[t - 1]) fail(TANQ_E_STATE, "real form needs a block's qubits in ascending order");
-    tmask |= (1ull << q[t]) | (1ull << (q[t] + n));
-  }
+  for (int t = 0; t < 2 * k; ++t) tmask |= 1ull << tbits[t];
   uint64_t vmask = tmask;
   for (int b = 0, need = V - 2 * k; b < nb && need > 0; ++b)
     if (!((vmask >> b) & 1ull)) {

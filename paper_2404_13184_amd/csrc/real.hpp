@@ -147,4 +147,229 @@ struct OpReal {
   }
 };
 
+// The tiles [t0, t1) of one state, in place: the next tile is prefetched into registers while the
+// current one is multiplied in one of two LDS buffers.  A wave multiplies its own groups in place,
+// so a tile takes two barriers: one between the multiplication and the store phase (which also
+// fills the other buffer with the next tile), one after it.
+template <bool FULL, typename T, typename IO, typename Op, typename Base>
+__device__ inline void real_tiles(T* __restrict__ rho, const IO& io, const Op& op, const Base& base, u32x4 (&lds)[2][IO::SLOTS], uint32_t t0, uint32_t t1, int tid) {
+  uint32_t cur = base(t0);
+  u32x4 buf[IO::ITERS];
+#pragma unroll
+  for (int it = 0; it < IO::ITERS; ++it)
+    if (io.template has<FULL>(it, tid)) buf[it] = *global_ptr(reinterpret_cast<const u32x4*>(rho + (cur + io.off[it])));
+#pragma unroll
+  for (int it = 0; it < IO::ITERS; ++it)
+    if (io.template has<FULL>(it, tid)) lds[0][io.lslot[it]] = buf[it];
+  lds_barrier();
+  int b = 0;
+  for (uint32_t t = t0;;) {
+    const bool more = t + 1 < t1;
+    uint32_t nbase = 0;
+    if (more) {
+      nbase = base(t + 1);
+#pragma unroll
+      for (int it = 0; it < IO::ITERS; ++it)
+        if (io.template has<FULL>(it, tid))
+          buf[it] = *global_ptr(reinterpret_cast<const u32x4*>(rho + (nbase + io.off[it])));
+    }
+    op.template compute<FULL>(reinterpret_cast<T*>(lds[b]));
+    lds_barrier();  // results complete
+#pragma unroll
+    for (int it = 0; it < IO::ITERS; ++it)
+      if (io.template has<FULL>(it, tid)) *global_ptr(reinterpret_cast<u32x4*>(rho + (cur + io.off[it]))) = lds[b][io.lslot[it]];
+    if (more) {
+#pragma unroll
+      for (int it = 0; it < IO::ITERS; ++it)
+        if (io.template has<FULL>(it, tid)) lds[b ^ 1][io.lslot[it]] = buf[it];
+    }
+    lds_barrier();  // this buffer is read out, the other one filled (or both free)
+    if (!more) break;
+    ++t;
+    b ^= 1;
+    cur = nbase;
+  }
+}
+
+// ------------------------------------------------------------------------------------
+// real form of a superoperator
+// ------------------------------------------------------------------------------------
+
+__device__ inline int ycount(uint32_t a, int k) {
+  const uint32_t m = (1u << k) - 1u;
+  return __popc(~a & (a >> k) & m);
+}
+
+// entry (a, b) of the real form of a superoperator S (4^k x 4^k complex)
+__device__ inline double real_entry(const f64x2* S, int k, uint32_t a, uint32_t b) {
+  const uint32_t m = (1u << k) - 1u;
+  const uint32_t ra = a & m, ca = a >> k, rb = b & m, cb = b >> k;
+  double sr = 0.0, si = 0.0;
+  for (uint32_t u = 0; u <= m; ++u)
+    for (uint32_t v = 0; v <= m; ++v) {
+      const f64x2 x = S[(((u ^ ra ^ ca) + (u << k)) << (2 * k)) + (v ^ rb ^ cb) + (v << k)];
+      const bool neg = (__popc(u & ca) + __popc(v & cb)) & 1;
+      sr += neg ? -x[0] : x[0];
+      si += neg ? -x[1] : x[1];
+    }
+  const int d = (ycount(a, k) - ycount(b, k)) & 3;  // Re((-i)^d (sr + i si))
+  const double v = d == 0 ? sr : (d == 1 ? si : (d == 2 ? -sr : -si));
+  return v / (double)(1u << k);
+}
+
+// fragment element e of a packed real operand: its row and column (real.hpp, OpReal)
+template <typename T>
+__device__ inline void real_frag_index(int e, int KS, int* row, int* col) {
+  const int lane = e & 63, rest = e >> 6, s = rest % KS, m = rest / KS, i = lane & 15;
+  *row = 16 * m + (Mfma<T>::kRowsStrided ? i : (i >> 2) + 4 * (i & 3));
+  *col = 4 * s + (lane >> 4);
+}
+
+
+// ------------------------------------------------------------------------------------
+// real-form passes (herm.hip)
+// ------------------------------------------------------------------------------------
+
+__device__ inline uint64_t pdep64(uint64_t x, uint64_t mask) {
+  uint64_t r = 0;
+  for (uint64_t m = mask; m; m &= m - 1) {
+    if (x & 1u) r |= m & (0 - m);
+    x >>= 1;
+  }
+  return r;
+}
+
+// A run of up to eight one- and two-qubit superoperators on each tile of 2^13 reals (64 KiB) while it
+// is in LDS, as apply_pass_kernel: one workgroup per CU, eight waves that all multiply and each load
+// their share of the next tile into the other buffer, a contiguous range of tiles per workgroup.  A
+// real operand is a third of a 3M operand, so every operand and offset stays in registers for twice
+// the superoperators.  Per tile 128 KiB move (6.5 us at the state's streaming rate) against 0.9 us of
+// products per superoperator, so up to about six superoperators the pass is bound by memory.
+__device__ inline void real_pass_tiles(double* __restrict__ w, const double* __restrict__ packed, const RealPassGeom& g,
+                                       u32x4* ldsA, u32x4* ldsB) {
+  constexpr int NT = kRealPassThreads, ITERS = 8, NBW = 4, MMAX = kRealPassMax;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint64_t per = (g.ntiles + gridDim.x - 1) / gridDim.x;
+  const uint64_t first = (uint64_t)blockIdx.x * per;
+  const uint64_t end = first + per < g.ntiles ? first + per : g.ntiles;
+  if (first >= end) return;  // uniform per workgroup
+
+  // slot it * 512 + tid; offsets are linear over GF(2) in the slot index
+  uint64_t off_t = 0;
+#pragma unroll
+  for (int b = 0; b < 9; ++b)
+    if ((tid >> b) & 1) off_t ^= g.goff[b];
+  auto off = [&](int it) {
+    return off_t ^ ((it & 1) ? g.goff[9] : 0) ^ ((it & 2) ? g.goff[10] : 0) ^ ((it & 4) ? g.goff[11] : 0);
+  };
+  uint64_t cur = pdep64(first, g.dmask);
+  {
+    const uint32_t ab = lds_addr(ldsA) + (uint32_t)wave * 1024u;
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) pass_dma16(w + cur + off(it), ab + (uint32_t)(it * NT * 16));
+  }
+
+  // operands and offsets of every superoperator (real.hpp: fragment and row order of OpReal)
+  double a[MMAX][4];
+  uint32_t lb[MMAX][NBW];  // LDS byte offset of this lane's group and row in each column block
+  const int kk = lane >> 4, li = lane & 15;
+#pragma unroll
+  for (int j = 0; j < MMAX; ++j) {
+    if (j < g.m) {
+      const double* P = packed + g.op_off[j];
+      const uint32_t em = g.emb[j];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        if (em == 0) {
+          a[j][s] = P[s * 64 + lane];
+        } else {
+          const int e0 = em & 3, e1 = (em >> 2) & 3, row = li, col = 4 * s + kk;
+          const int keep = 15 & ~((1 << e0) | (1 << e1));
+          const int r4 = ((row >> e0) & 1) | (((row >> e1) & 1) << 1), c4 = ((col >> e0) & 1) | (((col >> e1) & 1) << 1);
+          a[j][s] = ((row ^ col) & keep) ? 0.0 : P[r4 * 4 + c4];
+        }
+      }
+      uint32_t l = 0;
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        if ((li >> b) & 1) l ^= g.sbit[j][b];
+      if (kk & 1) l ^= g.sbit[j][9];
+      if (kk & 2) l ^= g.sbit[j][10];
+#pragma unroll
+      for (int b = 0; b < 3; ++b)
+        if ((wave >> b) & 1) l ^= g.sbit[j][4 + b];
+#pragma unroll
+      for (int i = 0; i < NBW; ++i)
+        lb[j][i] = l ^ ((i & 1) ? (uint32_t)g.sbit[j][7] : 0u) ^ ((i & 2) ? (uint32_t)g.sbit[j][8] : 0u);
+    }
+  }
+  vm_wait<0>();
+  raw_barrier();  // the first tile is in LDS
+
+  const int m = g.m;
+  auto tile_step = [&](u32x4* buf, u32x4* other, uint64_t nbase, bool more) {
+    char* L = reinterpret_cast<char*>(buf);
+    if (more) {
+      const uint32_t ob = lds_addr(other) + (uint32_t)wave * 1024u;
+#pragma unroll
+      for (int it = 0; it < ITERS; ++it) pass_dma16(w + nbase + off(it), ob + (uint32_t)(it * NT * 16));
+    }
+#pragma unroll
+    for (int j = 0; j < MMAX; ++j) {
+      if (j >= m) break;  // uniform
+      const uint32_t t1 = g.sbit[j][11], t2 = g.sbit[j][12];
+      // formed anew for every tile: hoisted out of the tile loop, the 16 addresses per superoperator
+      // would take the registers that the operands need
+      uint32_t l[NBW];
+#pragma unroll
+      for (int i = 0; i < NBW; ++i) {
+        l[i] = lb[j][i];
+        asm volatile("" : "+v"(l[i]));
+      }
+      auto at = [&](int i, int s) -> double& {
+        return *reinterpret_cast<double*>(L + (l[i] ^ ((s & 1) ? t1 : 0u) ^ ((s & 2) ? t2 : 0u)));
+      };
+      double b[NBW][4];
+#pragma unroll
+      for (int i = 0; i < NBW; ++i)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) b[i][s] = at(i, s);
+      __builtin_amdgcn_sched_barrier(0);
+      f64x4 acc[2];
+#pragma unroll
+      for (int i = 0; i < NBW; ++i) {
+        f64x4 c = {0, 0, 0, 0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s) c = Mfma<double>::mma(a[j][s], b[i][s], c);
+        acc[i & 1] = c;
+        // the results of block i - 1 are written while block i is multiplied
+        if (i > 0) {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) at(i - 1, r) = acc[(i - 1) & 1][r];
+        }
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) at(NBW - 1, r) = acc[(NBW - 1) & 1][r];
+      raw_barrier();  // the next superoperator (or the store) reads what other waves wrote
+    }
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it)
+      __builtin_nontemporal_store(buf[it * NT + tid], reinterpret_cast<u32x4*>(w + cur + off(it)));
+  };
+  for (uint64_t tile = first;; ++tile) {
+    const bool more = tile + 1 < end;
+    // the base of the next tile: an increment under the mask of the bits outside the tile
+    const uint64_t nbase = more ? ((cur | ~g.dmask) + 1ull) & g.dmask : 0;
+    if ((tile - first) & 1)
+      tile_step(ldsB, ldsA, nbase, more);
+    else
+      tile_step(ldsA, ldsB, nbase, more);
+    if (!more) break;
+    vm_wait<ITERS>();  // this wave's loads of the next tile (issued before its stores)
+    raw_barrier();     // the next tile is in LDS; this buffer is read out
+    cur = nbase;
+  }
+}
+
 }  // namespace tanq

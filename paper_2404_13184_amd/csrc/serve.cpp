@@ -318,9 +318,15 @@ void tanq_server_s::admit_one(ServeRequest* r) {
   const int vb = batch_tile_bits(p);
   for (size_t i = 0; i < L.host.size(); ++i) {
     r->pack_off[i] = keep_off + rho_b + L.host[i].pack_off;
-    if (p == TANQ_F64)
-      r->geom[i].rg = make_real_geom(r->n, w, L.host[i].qubits, vb, p);
-    else
+    if (p == TANQ_F64) {
+      // rows, then columns: ascending, as the composed operand's local index
+      int tbits[6];
+      for (int t = 0; t < w; ++t) {
+        tbits[t] = L.host[i].qubits[t];
+        tbits[w + t] = L.host[i].qubits[t] + r->n;
+      }
+      r->geom[i].rg = make_real_geom(2 * r->n, w, tbits, vb, p);
+    } else
       r->geom[i].g = make_apply_geom(r->n, w, L.host[i].qubits, vb, p);
   }
   r->cursor = 0;

@@ -75,3 +75,113 @@ def test_server_outputs_of_large_states(n):
     assert abs(res["trace"] - tr) <= 1e-12
     assert np.abs(res["probs"] - p).max() <= 1e-12
     assert np.abs(res["pauli"] - e).max() <= 1e-12
+
+
+# ---- long lists on single states (11 qubits and up, at least 12 launches) --------------------------
+
+
+def hermitian_vec(n, seed):
+    """vec of a random Hermitian matrix, exactly Hermitian in FP64 (not positive: linearity is enough)."""
+    rng = np.random.default_rng(seed)
+    a = rng.standard_normal((1 << n, 1 << n)) + 1j * rng.standard_normal((1 << n, 1 << n))
+    h = np.tril(a, -1)
+    return (h + h.conj().T + np.diag(a.diagonal().real)).T.reshape(-1) / (1 << n)
+
+
+def long_ops(n, seed):
+    """Every width, with and without the top qubit, neighbours and distant pairs, unordered."""
+    rng = np.random.default_rng(seed)
+    ops = []
+    for layer in range(6):
+        perm = [int(q) for q in rng.permutation(n)]
+        for q in perm:
+            ops.append(W.gate(W.random_unitary(rng, 2), (q,)))
+        ops.append(W.channel(W.amplitude_damping(0.1), (n - 1,)))
+        for i in range(0, n - 1, 2):
+            ops.append(W.gate(W.random_unitary(rng, 4), perm[i:i + 2]))
+            ops.append(W.channel(W.depolarizing(0.01, 2), perm[i + 1:None if i == 0 else i - 1:-1]))
+        ops.append(W.gate(W.random_unitary(rng, 8), perm[:3]))
+    return ops
+
+
+def apply_list(n, ops, mode, vec, limit, pieces=False):
+    old = T.tanq_get_pass_limit()
+    try:
+        c = T.Circuit(n, ops)
+        f = c.fuse(mode, "f64")
+        T.tanq_set_pass_limit(limit)
+        d = T.DM(n, "f64")
+        if vec is not None:
+            d.write(vec)
+        runs = f.launches()
+        if pieces:
+            pos = 0
+            for r in runs:
+                d.apply_fused(f, pos, pos + r)
+                pos += r
+        else:
+            d.apply_fused(f)
+        out = d.read()
+        d.free()
+        f.free()
+        c.free()
+        return out, len(runs)
+    finally:
+        T.tanq_set_pass_limit(old)
+
+
+# sums of at most 64 products per operation, some 100 operations and 2 n butterflies: a few 1e-14 of the
+# largest entry at worst
+LIST_TOL = 1e-12
+
+
+@pytest.mark.parametrize("mode", [T.TANQ_FUSE_NONE, T.TANQ_FUSE_PAPER, 1, 2, 3])
+@pytest.mark.parametrize("n", [11, 12, 13])
+def test_long_list_on_hermitian_state(n, mode):
+    """Real form against the blocks applied one by one (passes off, which keeps the complex form);
+    the result is exactly Hermitian.  11, 12 and 13 qubits: one, two and two uneven steps of the
+    transform beside its first."""
+    say("real-form list n=%d mode=%d" % (n, mode))
+    ops = long_ops(n, 100 * n + mode)
+    vec = hermitian_vec(n, n)
+    want, _ = apply_list(n, ops, mode, vec, 1)
+    got, launches = apply_list(n, ops, mode, vec, 8)
+    assert launches >= 12
+    assert np.abs(got - want).max() <= LIST_TOL * np.abs(want).max()
+    m = got.reshape(1 << n, 1 << n)
+    assert np.array_equal(m, m.conj().T)
+
+
+@pytest.mark.parametrize("limit", [2, 3, 8])
+def test_long_list_pass_limits(limit):
+    n = 11
+    say("real-form list limit=%d" % limit)
+    ops = W.random_u3_cx(n, 12, 5, 1e-3, 1e-2)
+    want, _ = apply_list(n, ops, 2, None, 1)
+    got, launches = apply_list(n, ops, 2, None, limit)
+    assert launches >= 12
+    assert np.abs(got - want).max() <= LIST_TOL * np.abs(want).max()
+
+
+@pytest.mark.parametrize("spoil", ["all", "one", "diagonal", "huge", "nan"])
+def test_long_list_on_other_states(spoil):
+    """A state that is not Hermitian in a single element, or out of range, is applied in the complex form:
+    bit for bit what the launches one by one give."""
+    n = 11
+    say("complex list, spoil=%s" % spoil)
+    ops = W.random_u3_cx(n, 12, 6, 1e-3, 1e-2)
+    vec = hermitian_vec(n, 3)
+    if spoil == "all":
+        vec = vec * (1 + 0.5j)
+    elif spoil == "one":
+        vec[(1 << n) * 777 + 1234] += 1e-17j * abs(vec[(1 << n) * 777 + 1234]) + 1e-18
+    elif spoil == "diagonal":
+        vec[((1 << n) + 1) * ((1 << n) - 1)] += 1e-300j
+    elif spoil == "huge":
+        vec[0] = 1e290
+    else:
+        vec[((1 << n) + 1) * 5] = np.nan
+    got, launches = apply_list(n, ops, 2, vec, 8)
+    want, _ = apply_list(n, ops, 2, vec, 8, pieces=True)
+    assert launches >= 12
+    assert np.array_equal(got.view(np.uint8), want.view(np.uint8))
