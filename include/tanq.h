@@ -269,6 +269,10 @@ tanq_status tanq_autotune_dense(tanq_dm d, int reps, double* ms_per_apply);
  * and widens 1-qubit blocks that join a pass to 2 qubits (the identity on the added qubit).  The limit is
  * the most superoperators per pass, 1..8 (1 = no passes; default 8), process-wide.
  *
+ * On states too small for passes, consecutive blocks whose qubits together number at most 5 share a
+ * launch (not with limit 1); the results are bit for bit those of the blocks one by one, and
+ * tanq_fused_launches counts them as single applies.
+ *
  * Long FP64 lists (11 to 16 qubits, at least 12 launches as tanq_fused_launches counts them, passes
  * not switched off) on an exactly Hermitian rho are applied in real form: the 4^n Pauli expectations, on
  * which every superoperator is a real matrix, formed in place before the first superoperator and

@@ -253,6 +253,28 @@ bool herm_list(int launches, int n, tanq_prec p, int lim) {
   return p == TANQ_F64 && n >= kHermMinN && n <= kHermMaxN && lim >= 2 && launches >= kHermMinLaunches;
 }
 
+// Length of the run that starts at block i (blocks before `end`) on a small state: the consecutive blocks of
+// any width whose qubits fit one tile.  1 on larger states and with passes switched off.
+template <typename BlockAt>
+int small_run(BlockAt at, int i, int end, int n, tanq_prec p, int lim) {
+  if (n > run_max_n(p) || lim < 2) return 1;
+  const int most = std::min(run_tile_bits(p), 2 * n);
+  const uint64_t low = p == TANQ_F64 ? 0 : 1;  // FP32 tiles hold index bit 0
+  uint64_t mask = 0;
+  int m = 0, m2 = 0, m3 = 0;
+  while (i + m < end && m < kRunMax) {
+    const int* q = nullptr;
+    const int k = at(i + m, &q);
+    if ((k == 2 && ++m2 > kRunMax2) || (k == 3 && ++m3 > kRunMax3)) break;
+    uint64_t nm = mask;
+    for (int t = 0; t < k; ++t) nm |= (1ull << q[t]) | (1ull << (q[t] + n));
+    if (__builtin_popcountll(nm | low) > most) break;
+    mask = nm;
+    ++m;
+  }
+  return std::max(m, 1);
+}
+
 // Length of the real-form pass that starts at block i (blocks before `end`): the longest run of
 // consecutive one- and two-qubit blocks, at most `lim`, whose qubits fit one tile; 0 for a wider block.
 template <typename BlockAt>
@@ -941,6 +963,17 @@ tanq_status tanq_apply_fused_range(tanq_dm d, tanq_fused f, int begin, int end) 
     next_real();
     for (int i = begin; i < end;) {
       const FusedBlockHost& b = f->blocks[i];
+      const int r = small_run(at, i, end, d->n, d->prec, lim);
+      if (r >= 2) {
+        RunBlock rb[kRunMax];
+        for (int t = 0; t < r; ++t) {
+          const FusedBlockHost& x = f->blocks[i + t];
+          rb[t] = {x.k, {x.qubits[0], x.qubits[1], x.qubits[2]}, x.pack_off - b.pack_off};
+        }
+        launch_run(d->ptr, d->n, d->prec, r, rb, f->packed + b.pack_off, d->stream);
+        i += r;
+        continue;
+      }
       const int m = pass_run(at, i, end, d->n, d->prec, lim);
       if (m >= 2) {
         const PassGeom* pg = pass_geom(f, i, m);

@@ -216,16 +216,10 @@ __global__ __launch_bounds__(256) void apply_c1_kernel(T* __restrict__ rho, cons
     c2 x[4];
 #pragma unroll
     for (int a = 0; a < 4; ++a) x[a] = *reinterpret_cast<const c2*>(rho + 2 * idx[a]);
+    c2 y[4];
+    c1_group<T>(sr, si, x, y);
 #pragma unroll
-    for (int a = 0; a < 4; ++a) {
-      T yr = 0, yi = 0;
-#pragma unroll
-      for (int b = 0; b < 4; ++b) {
-        yr += sr[4 * a + b] * x[b][0] - si[4 * a + b] * x[b][1];
-        yi += sr[4 * a + b] * x[b][1] + si[4 * a + b] * x[b][0];
-      }
-      *reinterpret_cast<c2*>(rho + 2 * idx[a]) = c2{yr, yi};
-    }
+    for (int a = 0; a < 4; ++a) *reinterpret_cast<c2*>(rho + 2 * idx[a]) = y[a];
   }
 }
 

@@ -105,6 +105,35 @@ struct RealPassGeom {
   int32_t m;
 };
 
+// Runs of superoperators of any width on small states, one launch per run (run.hip).
+constexpr int kRunBitsF64 = 10, kRunBitsF32 = 11;
+// blocks of a run; two-qubit blocks among them (operands in LDS), three-qubit ones
+constexpr int kRunMax = 32, kRunMax2 = 8, kRunMax3 = 8;
+inline int run_tile_bits(tanq_prec p) { return p == TANQ_F64 ? kRunBitsF64 : kRunBitsF32; }
+// states smaller than those that use passes
+inline int run_max_n(tanq_prec p) { return p == TANQ_F64 ? 9 : 10; }
+struct RunOp {
+  uint32_t off;     // packed operand, in 256 bytes
+  uint16_t k;
+  uint16_t aux;     // k = 1: blocks after this one on the same qubit (one after the other); k = 2: place of
+                    // its operand in LDS
+  uint16_t tb[6];   // LDS place (element) of each local index bit
+  uint16_t fb[10];  // and of each group index bit
+};
+struct RunGeom {
+  uint32_t dmask;                // index bits outside the tile
+  int32_t V, m, m2, m3;          // blocks; two-qubit and three-qubit ones among them
+  uint32_t goff[kRunBitsF32];    // index of each tile bit
+  uint32_t off2[kRunMax2];       // operands of the two- and three-qubit blocks, as RunOp::off
+  uint32_t off3[kRunMax3];
+  RunOp op[kRunMax];
+};
+struct RunBlock {
+  int k;
+  int qubits[3];
+  size_t pack_off;  // bytes
+};
+
 // Fusion: a block of consecutive operations on at most k qubits.
 struct FuseOpDev {
   int32_t j;          // qubits of the operation
@@ -205,6 +234,8 @@ void launch_pass(void* rho, tanq_prec p, const PassGeom& g, const void* frags, h
 // NULL: nothing), else the complex one (g, frags; NULL: nothing).
 void launch_pass_either(void* rho, const PassGeom* g, const void* frags, const RealPassGeom* rg, const double* rpacked,
                         const uint32_t* flag, hipStream_t s);
+// blocks: m consecutive blocks whose qubits fit one tile (run_tile_bits)
+void launch_run(void* rho, int n, tanq_prec p, int m, const RunBlock* blocks, const void* packed, hipStream_t s);
 // Process-wide limit on superoperators per pass (1 = no passes).
 int pass_limit();
 void set_pass_limit(int m);

@@ -222,6 +222,27 @@ __device__ inline bool skip_launch(const uint32_t* skip) {
   return skip != nullptr && __builtin_amdgcn_readfirstlane((int)*skip) != 0;
 }
 
+// k = 1: one group of four amplitudes, y = S x.  The contractions are written out, so that every kernel
+// that applies a one-qubit superoperator gives the same bits.
+template <typename T>
+__device__ inline void c1_group(const T (&sr)[16], const T (&si)[16], const typename Mfma<T>::c2 (&x)[4],
+                                typename Mfma<T>::c2 (&y)[4]) {
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    T yr = 0, yi = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      const T cr = sr[4 * a + b], ci = si[4 * a + b], xr = x[b][0], xi = x[b][1];
+      yr += __builtin_elementwise_fma(cr, xr, -(ci * xi));
+      if constexpr (sizeof(T) == 8)
+        yi += __builtin_elementwise_fma(ci, xr, cr * xi);
+      else
+        yi += __builtin_elementwise_fma(cr, xi, ci * xr);
+    }
+    y[a] = typename Mfma<T>::c2{yr, yi};
+  }
+}
+
 // ------------------------------------------------------------------------------------
 // k = 2: real-block form.  Interleaved data is a real vector of length 32 and S the 32 x 32
 // real matrix [[Sr, -Si], [Si, Sr]] (interleaved); each wave owns 16-group column blocks and
