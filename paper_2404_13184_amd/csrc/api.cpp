@@ -107,9 +107,10 @@ struct tanq_fused_s {
   double* raw = nullptr;
   unsigned char* packed = nullptr;
   // real operands for long lists on Hermitian FP64 states (herm.hip), if it is long enough for
-  // them; block b's at rpacked + rpack_off[b]
+  // them; block b's at rpacked + rpack_off[b], the defect table after the last
   double* rpacked = nullptr;
   std::vector<size_t> rpack_off;
+  double* defects = nullptr;  // inside rpacked
   // pass geometries already built, by (first block, length)
   std::mutex pass_mu;
   std::map<std::pair<int, int>, tanq::PassGeom> passes;
@@ -809,10 +810,11 @@ tanq_status tanq_fuse(tanq_circuit c, int max_width, tanq_prec p, void* hip_stre
             for (int t = 0; t < 2 * b.k; ++t) r.perm[t] = (uint8_t)t;
             std::sort(r.perm, r.perm + 2 * b.k, [&](uint8_t x, uint8_t y) { return pos[x] < pos[y]; });
           }
-          TANQ_HIP(hipMalloc((void**)&f->rpacked, elems * sizeof(double)));
+          TANQ_HIP(hipMalloc((void**)&f->rpacked, (elems + (size_t)nblk + 1) * sizeof(double)));
+          f->defects = f->rpacked + elems;
           TANQ_HIP(hipMalloc((void**)&d_rblk, rb.size() * sizeof(RealPackDev)));
           TANQ_HIP(hipMemcpyAsync(d_rblk, rb.data(), rb.size() * sizeof(RealPackDev), hipMemcpyHostToDevice, s));
-          launch_pack_herm(d_rblk, nblk, f->raw, f->rpacked, s);
+          launch_pack_herm(d_rblk, nblk, f->raw, f->rpacked, f->defects, s);
           TANQ_HIP(hipStreamSynchronize(s));  // rb is read by the copy
         }
         TANQ_HIP(hipStreamSynchronize(s));
@@ -991,7 +993,7 @@ tanq_status tanq_apply_fused_range(tanq_dm d, tanq_fused f, int begin, int end) 
       i += m;
     }
     for (; rg; next_real()) launch_pass_either(d->ptr, nullptr, nullptr, rg, rpacked, flag, d->stream);
-    if (real) launch_herm_out(d->ptr, d->n, flag, d->stream);
+    if (real) launch_herm_out(d->ptr, d->n, f->defects + begin, f->defects + end, flag, d->stream);
   });
 }
 

@@ -32,7 +32,7 @@
 #include <cstring>
 #include <type_traits>
 
-#include "tile.hpp"
+#include "compose.hpp"
 
 namespace tanq {
 
@@ -226,46 +226,6 @@ __global__ __launch_bounds__(256) void apply_c1_kernel(T* __restrict__ rho, cons
 // ------------------------------------------------------------------------------------
 // packing of FP64 superoperators into the kernels' A-operand lane layouts
 // ------------------------------------------------------------------------------------
-
-// k = 2, real block: R[m'][k'] for m' = 2a + cm, k' = 2b + ck is
-//   (cm, ck) = (0,0): Re S[a][b]   (0,1): -Im S[a][b]   (1,0): Im S[a][b]   (1,1): Re S[a][b]
-// stored as P[(mt * 8 + ks) * 64 + lane] = R[16 mt + lane % 16][4 ks + lane / 16].
-// k = 3, 3M: P[((mt * 16 + ks) * 3 + c) * 64 + lane] = C_c[16 mt + lane % 16][4 ks + lane / 16]
-//   with C_0 = Re S, C_1 = Im S, C_2 = Re S + Im S (summed in FP64, rounded once).
-// k = 1: the FP64 superoperator itself (32 doubles), for both precisions.
-template <typename T>
-__device__ void pack_block(int k, const double* __restrict__ S, unsigned char* __restrict__ out) {
-  if (k == 1) {
-    double* P = reinterpret_cast<double*>(out);
-    for (int e = threadIdx.x; e < 32; e += blockDim.x) P[e] = S[e];
-  } else if (k == 2) {
-    T* P = reinterpret_cast<T*>(out);
-    for (int e = threadIdx.x; e < 2 * 8 * 64; e += blockDim.x) {
-      const int lane = e & 63, rest = e >> 6;
-      const int ks = rest % 8, mt = rest / 8;
-      const int mrow = 16 * mt + (lane & 15), kcol = 4 * ks + (lane >> 4);
-      const int a = mrow >> 1, cm = mrow & 1, b = kcol >> 1, ck = kcol & 1;
-      const double re = S[2 * (a * 16 + b)], im = S[2 * (a * 16 + b) + 1];
-      P[e] = (T)((cm == ck) ? re : (cm == 0 ? -im : im));
-    }
-  } else {
-    T* P = reinterpret_cast<T*>(out);
-    for (int e = threadIdx.x; e < 4 * 16 * 3 * 64; e += blockDim.x) {
-      const int lane = e & 63, rest = e >> 6;
-      const int c = rest % 3, ks = (rest / 3) % 16, mt = rest / 48;
-      const int a = 16 * mt + (lane & 15), b = 4 * ks + (lane >> 4);
-      const double re = S[2 * (a * 64 + b)], im = S[2 * (a * 64 + b) + 1];
-      P[e] = (T)(c == 0 ? re : (c == 1 ? im : re + im));
-    }
-  }
-}
-
-template <typename T>
-__global__ void pack_kernel(const FuseBlockDev* __restrict__ blocks, const double* __restrict__ raw,
-                            unsigned char* __restrict__ packed) {
-  const FuseBlockDev blk = blocks[blockIdx.x];
-  pack_block<T>(blk.k, raw + 2 * blk.out_off, packed + blk.pack_off);
-}
 
 template <typename T>
 __global__ void pack_one_kernel(int k, const double* __restrict__ raw, unsigned char* __restrict__ packed) {
@@ -585,16 +545,6 @@ void launch_apply(void* rho, int n, tanq_prec p, int k, const int* qubits, const
   }
   if (k != 2 && k != 3) fail(TANQ_E_ARG, "superoperator width must be 1, 2 or 3");
   launch_apply_variant(rho, n, p, k, variant_for(n, k, p), qubits, packed, s, skip);
-}
-
-void launch_pack(const FuseBlockDev* blocks, int nblocks, const double* raw, void* packed, tanq_prec p,
-                 hipStream_t s) {
-  if (nblocks <= 0) return;
-  if (p == TANQ_F64)
-    hipLaunchKernelGGL(pack_kernel<double>, dim3(nblocks), dim3(256), 0, s, blocks, raw, (unsigned char*)packed);
-  else
-    hipLaunchKernelGGL(pack_kernel<float>, dim3(nblocks), dim3(256), 0, s, blocks, raw, (unsigned char*)packed);
-  TANQ_HIP(hipGetLastError());
 }
 
 void launch_pack_one(int k, const double* raw, void* packed, tanq_prec p, hipStream_t s) {

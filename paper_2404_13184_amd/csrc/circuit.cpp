@@ -79,8 +79,7 @@ void run_fuse_kernels(const FuseLayout& L, const FuseOpDev* d_ops, const FuseBlo
                       double* d_sops, double* d_raw, unsigned char* d_packed, tanq_prec p, hipStream_t s) {
   if (L.blocks.empty()) return;
   launch_build_superops(d_ops, (int)L.ops.size(), d_kraus, d_sops, s);
-  launch_compose(d_blk, (int)L.blocks.size(), L.max_k, d_ops, d_sops, d_raw, s);
-  launch_pack(d_blk, (int)L.blocks.size(), d_raw, d_packed, p, s);
+  launch_compose(d_blk, (int)L.blocks.size(), L.max_k, d_ops, d_sops, d_raw, d_packed, p, s);
 }
 
 }  // namespace tanq

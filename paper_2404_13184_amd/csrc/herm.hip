@@ -162,13 +162,16 @@ __global__ __launch_bounds__(kEdgeNT) void herm_in_kernel(f64x2* __restrict__ rh
 
 // The last step of the way back: a tile and its mirror image (rows and columns of the outside bits
 // exchanged) together, since rho[r][c] takes X[r][c] and X[c][r].
-__global__ __launch_bounds__(kEdgeNT) void herm_out_kernel(f64x2* __restrict__ rho, int n, const uint32_t* flag) {
+__global__ __launch_bounds__(kEdgeNT) void herm_out_kernel(f64x2* __restrict__ rho, int n,
+                                                           const double* __restrict__ from,
+                                                           const double* __restrict__ to, const uint32_t* flag) {
   __shared__ double t[2][1 << kEdgeV];
   if (!flag_set(flag)) return;
   const int tid = threadIdx.x;
   const int no = n - 6;
   const uint64_t ntiles = 1ull << (2 * no);
-  const double scale = 0.5 / (double)(1ull << n);  // the halves of n butterflies and of X +- X^T
+  // the halves of n butterflies and of X +- X^T, and the operands' common factor
+  const double scale = (1.0 + (to[0] - from[0])) * (0.5 / (double)(1ull << n));
   for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const uint32_t ro = (uint32_t)(tile & ((1u << no) - 1u)), co = (uint32_t)(tile >> no);
     if (ro > co) continue;  // done with its mirror image
@@ -316,7 +319,8 @@ __global__ __launch_bounds__(256, 2) void real_apply3_kernel(double* __restrict_
 // ------------------------------------------------------------------------------------
 
 __global__ __launch_bounds__(256) void pack_herm_kernel(const RealPackDev* __restrict__ blocks,
-                                                        const double* __restrict__ raw, double* __restrict__ packed) {
+                                                        const double* __restrict__ raw, double* __restrict__ packed,
+                                                        double* __restrict__ defects) {
   const RealPackDev b = blocks[blockIdx.x];
   const f64x2* S = reinterpret_cast<const f64x2*>(raw + 2 * b.raw_off);
   double* P = packed + b.pack_off;
@@ -326,10 +330,32 @@ __global__ __launch_bounds__(256) void pack_herm_kernel(const RealPackDev* __res
     for (int t = 0; t < 2 * b.k; ++t) r |= (uint32_t)((x >> t) & 1) << b.perm[t];
     return r;
   };
+  double hi, lo;
+  real_entry(S, b.k, 0, 0, &hi, &lo);
+  const double d = real_defect(hi);
+  if (threadIdx.x == 0) defects[blockIdx.x + 1] = d;
   for (int e = threadIdx.x; e < D * D; e += blockDim.x) {
     int row = e / D, col = e % D;
     if (b.k > 1) real_frag_index<double>(e, D / 4, &row, &col);
-    P[e] = real_entry(S, b.k, local(row), local(col));
+    real_entry(S, b.k, local(row), local(col), &hi, &lo);
+    P[e] = real_operand(hi, lo, d, row == col, row + col == 0);
+  }
+}
+
+// prefix sums of the blocks' defects, in place, by one wave
+__global__ void herm_defects_kernel(double* __restrict__ t, int n) {
+  const int lane = threadIdx.x;
+  double run = 0.0;
+  if (lane == 0) t[0] = 0.0;
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    double v = i0 + lane < n ? t[1 + i0 + lane] : 0.0;
+    for (int o = 1; o < 64; o <<= 1) {
+      const double u = __shfl_up(v, o, 64);
+      if (lane >= o) v += u;
+    }
+    v += run;
+    if (i0 + lane < n) t[1 + i0 + lane] = v;
+    run = __shfl(v, 63, 64);
   }
 }
 
@@ -337,9 +363,12 @@ __global__ __launch_bounds__(256) void pack_herm_kernel(const RealPackDev* __res
 // host side
 // ------------------------------------------------------------------------------------
 
-void launch_pack_herm(const RealPackDev* blocks, int nblocks, const double* raw, double* packed, hipStream_t s) {
+void launch_pack_herm(const RealPackDev* blocks, int nblocks, const double* raw, double* packed, double* defects,
+                      hipStream_t s) {
   if (nblocks <= 0) return;
-  hipLaunchKernelGGL(pack_herm_kernel, dim3(nblocks), dim3(256), 0, s, blocks, raw, packed);
+  hipLaunchKernelGGL(pack_herm_kernel, dim3(nblocks), dim3(256), 0, s, blocks, raw, packed, defects);
+  TANQ_HIP(hipGetLastError());
+  hipLaunchKernelGGL(herm_defects_kernel, dim3(1), dim3(64), 0, s, defects, nblocks);
   TANQ_HIP(hipGetLastError());
 }
 
@@ -395,14 +424,15 @@ void launch_herm_in(void* rho, int n, const uint32_t* flag, hipStream_t s) {
   }
 }
 
-void launch_herm_out(void* rho, int n, const uint32_t* flag, hipStream_t s) {
+void launch_herm_out(void* rho, int n, const double* from, const double* to, const uint32_t* flag, hipStream_t s) {
   const int steps = herm_steps(n), total = n - 6;
   for (int i = 0, q = 5; i < steps; ++i) {
     const int nq = total / steps + (i < total % steps ? 1 : 0);
     launch_herm_mid(rho, n, q, nq, i == 0 ? 2 : 0, flag, s);
     q += nq;
   }
-  hipLaunchKernelGGL(herm_out_kernel, dim3(herm_grid(1ull << (2 * (n - 6)), 2)), dim3(kEdgeNT), 0, s, (f64x2*)rho, n, flag);
+  hipLaunchKernelGGL(herm_out_kernel, dim3(herm_grid(1ull << (2 * (n - 6)), 2)), dim3(kEdgeNT), 0, s, (f64x2*)rho, n,
+                     from, to, flag);
   TANQ_HIP(hipGetLastError());
 }
 

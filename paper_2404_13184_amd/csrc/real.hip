@@ -4,12 +4,15 @@
 // superoperator S becomes R[a][b] = Re((-i)^(y_a - y_b) 2^-k sum_{u,v} (-1)^(u.c_a + v.c_b)
 // S[i(a,u)][i(b,v)]), i(a, u) = (u ^ r_a ^ c_a) + 2^k u, where (r, c) are a local index's row and
 // column halves and y = popcount(~r & c).  For S = sum_i conj(K_i) (x) K_i the imaginary part of
-// that expression is zero.
+// that expression is zero.  R is kept as E = R - I throughout: its first row, (1, 0, .., 0) but for
+// rounding, would otherwise lose the rounding of the Kraus sets that the complex form carries along
+// (errors of 5e-14 on repeated layers instead of 1e-15).
+#include "compose.hpp"
 #include "real.hpp"
 
 namespace tanq {
 
-// One workgroup per operation: S in LDS, then its real form.
+// One workgroup per operation: S in LDS, then E = R - I.
 __global__ __launch_bounds__(256) void build_real_kernel(const FuseOpDev* __restrict__ ops,
                                                          const double* __restrict__ kraus, double* __restrict__ sops) {
   __shared__ f64x2 S[64 * 64];
@@ -30,15 +33,18 @@ __global__ __launch_bounds__(256) void build_real_kernel(const FuseOpDev* __rest
     S[e] = f64x2{sr, si};
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < dd * dd; e += blockDim.x)
-    sops[op.sop_off + e] = real_entry(S, j, (uint32_t)(e / dd), (uint32_t)(e % dd));
+  for (int e = threadIdx.x; e < dd * dd; e += blockDim.x) {
+    double hi, lo;
+    real_entry(S, j, (uint32_t)(e / dd), (uint32_t)(e % dd), &hi, &lo);
+    sops[op.sop_off + e] = hi;
+  }
 }
 
-// One workgroup per block: M <- R_op(embedded) M in circuit order from M = I, out of place between
-// two LDS buffers (one barrier per operation), then M in the operand layout.  The chain over a
-// block's operations is serial and each step is short, so what counts is its latency: the next
-// operation's matrix is loaded into registers while the current one is applied.  Thread t works
-// on column t % D; the 256 / D threads of a column share its groups and outputs.
+// One workgroup per block: M <- (I + E_op)(embedded) M in circuit order from M = I, kept as N = M - I (N <- N +
+// E_op (I + N)), out of place between two LDS buffers (one barrier per operation), then the operand
+// (real_operand) and, after its 4^2k elements, its factor's defect d.  Thread t works on column
+// t % D; the 256 / D threads of a column share its groups and outputs.  The chain over a block's operations
+// is serial: ComposeFeed keeps it from waiting for memory.
 template <typename T, int K>
 __global__ __launch_bounds__(256) void compose_real_kernel(const FuseBlockDev* __restrict__ blocks,
                                                            const FuseOpDev* __restrict__ ops,
@@ -46,89 +52,98 @@ __global__ __launch_bounds__(256) void compose_real_kernel(const FuseBlockDev* _
                                                            unsigned char* __restrict__ packed) {
   constexpr int D = 1 << (2 * K), SLOTS = 256 / D;
   __shared__ double M[2][D * D];
-  __shared__ double Sl[2][256];
+  __shared__ typename ComposeFeed<double>::Lds fl;
   const FuseBlockDev blk = blocks[blockIdx.x];
   const int tid = threadIdx.x, c = tid % D, slot = tid / D;
-  for (int e = tid; e < D * D; e += 256) M[0][e] = (e / D) == (e % D) ? 1.0 : 0.0;
-  FuseOpDev op = ops[blk.op_begin];
-  if (blk.op_count > 0 && op.j <= 2 && tid < (1 << (4 * op.j))) Sl[0][tid] = sops[op.sop_off + tid];
-  __syncthreads();
+  for (int e = tid; e < D * D; e += 256) M[0][e] = 0.0;
+  ComposeFeed<double> feed(fl, ops + blk.op_begin, sops, blk.op_count);
+  feed.start();
   int cur = 0;
   for (int oi = 0; oi < blk.op_count; ++oi) {
-    const bool more = oi + 1 < blk.op_count;
-    const FuseOpDev nop = more ? ops[blk.op_begin + oi + 1] : op;
-    double pre = 0.0;
-    const bool fetch = more && nop.j <= 2 && tid < (1 << (4 * nop.j));
-    if (fetch) pre = sops[nop.sop_off + tid];
-
+    feed.request(oi);
+    const FuseOpDev& op = fl.tab[oi % feed.kTab];
     const double* X = M[cur];
     double* Y = M[cur ^ 1];
-    const double* S = Sl[oi & 1];
-    const int j = op.j, Dj = 1 << (2 * j);
+    const double* S = fl.ring[oi % feed.kRing];
+    const int j = __builtin_amdgcn_readfirstlane(op.j);
     // row bits (within M) of the operation's local index bits
-    uint32_t tbit[6] = {0, 0, 0, 0, 0, 0}, tmask = 0;
-    for (int t = 0; t < j; ++t) {
-      tbit[t] = 1u << op.pos[t];
-      tbit[j + t] = 1u << (K + op.pos[t]);
-      tmask |= tbit[t] | tbit[j + t];
+    uint32_t tb[6], tmask = 0;
+#pragma unroll
+    for (int t = 0; t < 6; ++t) {
+      const int q = t < j ? t : t - j;
+      tb[t] = t < 2 * j ? 1u << ((t < j ? 0 : K) + __builtin_amdgcn_readfirstlane(op.pos[q < 3 ? q : 0])) : 0u;
+      tmask |= tb[t];
     }
     auto dep = [&](int l) {
       uint32_t r = 0;
-      for (int t = 0; t < 2 * j; ++t)
-        if ((l >> t) & 1) r |= tbit[t];
+#pragma unroll
+      for (int t = 0; t < 6; ++t)
+        if ((l >> t) & 1) r |= tb[t];
       return r;
     };
-    const uint32_t freemask = (uint32_t)(D - 1) & ~tmask;
-    if (j <= 2) {
-      // work items of a column: (group, run of outputs); as many runs per group as the threads of a
-      // column need to have one each
-      const int groups = D / Dj;
-      const int split = groups < SLOTS ? SLOTS / groups : 1;
-      const int outs = Dj / split;  // at least 1: SLOTS <= D
-      for (int it = slot; it < groups * split; it += SLOTS) {
-        const uint32_t base = pdep32((uint32_t)(it / split), freemask);
-        const int a0 = (it % split) * outs;
-        if (j == 1) {
+    const uint32_t fm = (uint32_t)(D - 1) & ~tmask;
+    auto full = [&](uint32_t row) { return X[row * D + c] + ((int)row == c ? 1.0 : 0.0); };  // (I + N)[row][c]
+    if (j == 1) {
+      if constexpr (K == 2) {  // one output each: group slot / 4, output slot % 4
+        const uint32_t base = pdep32((uint32_t)(slot >> 2), fm);
+        const int a = slot & 3;
+        double y = 0.0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) y += S[a * 4 + b] * full(base | dep(b));
+        Y[(base | dep(a)) * D + c] = X[(base | dep(a)) * D + c] + y;
+      } else {
+        for (int g = slot; g < D / 4; g += SLOTS) {
+          const uint32_t base = pdep32((uint32_t)g, fm);
           double x[4];
 #pragma unroll
-          for (int b = 0; b < 4; ++b) x[b] = X[(base | dep(b)) * D + c];
-          for (int a = a0; a < a0 + outs; ++a) {
+          for (int b = 0; b < 4; ++b) x[b] = full(base | dep(b));
+#pragma unroll
+          for (int a = 0; a < 4; ++a) {
             double y = 0.0;
 #pragma unroll
             for (int b = 0; b < 4; ++b) y += S[a * 4 + b] * x[b];
-            Y[(base | dep(a)) * D + c] = y;
+            Y[(base | dep(a)) * D + c] = X[(base | dep(a)) * D + c] + y;
           }
-        } else {
-          double x[16];
+        }
+      }
+    } else if (j == 2) {
+      if constexpr (K == 2) {  // one group; one output each
+        double y = 0.0;
 #pragma unroll
-          for (int b = 0; b < 16; ++b) x[b] = X[(base | dep(b)) * D + c];
-          for (int a = a0; a < a0 + outs; ++a) {
-            double y = 0.0;
+        for (int b = 0; b < 16; ++b) y += S[slot * 16 + b] * full(dep(b));
+        Y[dep(slot) * D + c] = X[dep(slot) * D + c] + y;
+      } else {  // one group each, all its outputs
+        const uint32_t base = pdep32((uint32_t)slot, fm);
+        double x[16];
 #pragma unroll
-            for (int b = 0; b < 16; ++b) y += S[a * 16 + b] * x[b];
-            Y[(base | dep(a)) * D + c] = y;
-          }
+        for (int b = 0; b < 16; ++b) x[b] = full(base | dep(b));
+#pragma unroll 4
+        for (int a = 0; a < 16; ++a) {
+          double y = 0.0;
+#pragma unroll
+          for (int b = 0; b < 16; ++b) y += S[a * 16 + b] * x[b];
+          Y[(base | dep(a)) * D + c] = X[(base | dep(a)) * D + c] + y;
         }
       }
     } else if constexpr (K == 3) {
       const double* Sg = sops + op.sop_off;
       for (int a = slot; a < D; a += SLOTS) {
         double y = 0.0;
-        for (int b = 0; b < D; ++b) y += Sg[a * D + b] * X[dep(b) * D + c];
-        Y[dep(a) * D + c] = y;
+        for (int b = 0; b < D; ++b) y += Sg[a * D + b] * full(dep(b));
+        Y[dep(a) * D + c] = X[dep(a) * D + c] + y;
       }
     }
-    if (fetch) Sl[(oi + 1) & 1][tid] = pre;
-    __syncthreads();
+    feed.next(oi);
     cur ^= 1;
-    op = nop;
   }
   T* P = reinterpret_cast<T*>(packed + blk.pack_off);
+  const double d = real_defect(M[cur][0]);
   for (int e = tid; e < D * D; e += 256) {
     int row, col;
     real_frag_index<T>(e, D / 4, &row, &col);
-    P[e] = (T)M[cur][row * D + col];
+    P[e] = (T)real_operand(M[cur][row * D + col], 0.0, d, row == col, row + col == 0);
   }
+  if (tid == 0) P[D * D] = (T)d;
 }
 
 // |0..0><0..0| has expectation 1 for every string of I and Z (r' = c') and 0 for the others.
@@ -143,11 +158,20 @@ __global__ void real_init_kernel(T* __restrict__ w, int n) {
 // LDS, FP64); every other output is one element of w.
 template <typename T, int NMAX>
 __global__ __launch_bounds__(1024) void real_outputs_kernel(const T* __restrict__ w, int n, int want_probs, int count,
-                                                            const uint64_t* __restrict__ masks,
-                                                            double* __restrict__ out) {
+                                                            const uint64_t* __restrict__ masks, const T* __restrict__ defects,
+                                                            int stride, int nblocks, double* __restrict__ out) {
   __shared__ double p[1 << NMAX];
+  __shared__ double part[16];
   const uint32_t dim = 1u << n;
-  const double tr = (double)w[0];
+  // the common factor of the applied operands: the product of 1 + d, d below 1e-9
+  double f = 0.0;
+  for (int i = threadIdx.x; i < nblocks; i += 1024) f += (double)defects[(size_t)i * stride];
+  for (int o = 32; o > 0; o >>= 1) f += __shfl_down(f, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = f;
+  __syncthreads();
+  f = 1.0;
+  for (int i = 0; i < 16; ++i) f += part[i];
+  const double tr = (double)w[0] * f;
   if (threadIdx.x == 0) out[0] = tr;
   double* res = out + 1;
   if (want_probs) {
@@ -162,13 +186,13 @@ __global__ __launch_bounds__(1024) void real_outputs_kernel(const T* __restrict_
       }
       __syncthreads();
     }
-    const double inv = 1.0 / tr, scale = 1.0 / (double)dim;
+    const double inv = 1.0 / tr, scale = f / (double)dim;
     for (uint32_t x = threadIdx.x; x < dim; x += 1024) res[x] = (p[x] * scale) * inv;
     res += dim;
   }
   for (int i = threadIdx.x; i < count; i += 1024) {
     const uint64_t xm = masks[3 * i], zm = masks[3 * i + 1];
-    res[2 * i] = (double)w[(xm ^ zm) + (zm << n)];
+    res[2 * i] = (double)w[(xm ^ zm) + (zm << n)] * f;
     res[2 * i + 1] = 0.0;  // rho is Hermitian
   }
 }
@@ -285,25 +309,28 @@ void launch_real_init(void* w, int n, tanq_prec p, hipStream_t s) {
 }
 
 template <typename T>
-static void real_outputs_typed(const void* w, int n, int want_probs, int count, const uint64_t* masks, double* out,
-                               hipStream_t s) {
+static void real_outputs_typed(const void* w, int n, int want_probs, int count, const uint64_t* masks,
+                               const T* defects, int stride, int nblocks, double* out, hipStream_t s) {
   // two LDS sizes: up to 12 qubits (32 KiB) and up to 14 (128 KiB)
   if (n <= 12)
     hipLaunchKernelGGL((real_outputs_kernel<T, 12>), dim3(1), dim3(1024), 0, s, (const T*)w, n, want_probs, count,
-                       masks, out);
+                       masks, defects, stride, nblocks, out);
   else
     hipLaunchKernelGGL((real_outputs_kernel<T, kRealOutMaxN>), dim3(1), dim3(1024), 0, s, (const T*)w, n, want_probs,
-                       count, masks, out);
+                       count, masks, defects, stride, nblocks, out);
   TANQ_HIP(hipGetLastError());
 }
 
 void launch_real_outputs(const void* w, int n, tanq_prec p, int want_probs, int count, const uint64_t* masks,
-                         double* out, hipStream_t s) {
+                         const void* packed, int k, size_t stride_bytes, int nblocks, double* out, hipStream_t s) {
   if (n > kRealOutMaxN) fail(TANQ_E_ARG, "outputs of a real-form state: too many qubits");
+  const int d = 1 << (4 * k);  // a block's defect follows its operand
   if (p == TANQ_F64)
-    real_outputs_typed<double>(w, n, want_probs, count, masks, out, s);
+    real_outputs_typed<double>(w, n, want_probs, count, masks, (const double*)packed + d,
+                               (int)(stride_bytes / sizeof(double)), nblocks, out, s);
   else
-    real_outputs_typed<float>(w, n, want_probs, count, masks, out, s);
+    real_outputs_typed<float>(w, n, want_probs, count, masks, (const float*)packed + d,
+                              (int)(stride_bytes / sizeof(float)), nblocks, out, s);
 }
 
 }  // namespace tanq

@@ -58,10 +58,12 @@ struct RealIo {
   __device__ inline bool has(int it, int tid) const { return FULL || it * NT + tid < slots; }
 };
 
-// One superoperator in real form on the tile in LDS, in place.  R fragment (m, s) of lane l is
-// R[row(m, l % 16)][4 s + l / 16]; accumulator value r of lane l holds row 16 m + l / 16 + 4 r in both
-// precisions (the FP32 packing permutes the rows within an m-tile), so the elements a lane writes
-// are the ones it read and one set of addresses serves both.
+// One superoperator in real form on the tile in LDS, in place: y = x + P x, P = R - I up to a common
+// factor (real_operand).  The accumulators start from x, so the identity part is exact and what P rounds is
+// small where R is near the identity.  P fragment (m, s) of lane l is P[row(m, l % 16)][4 s + l / 16];
+// accumulator value r of lane l holds row 16 m + l / 16 + 4 r in both precisions (the FP32 packing permutes
+// the rows within an m-tile), so the elements a lane writes are the ones it read: one set of addresses
+// serves both, and the accumulators' start is in registers.
 template <typename T, int K, int VMAX, int NT>
 struct OpReal {
   using M = Mfma<T>;
@@ -120,29 +122,37 @@ struct OpReal {
     for (int i0 = 0; i0 < NBW; i0 += STEP) {
       if (!FULL && wave + i0 * NW >= nblk) break;  // uniform per wave
       T b[STEP][KS];
-      acc_t acc[STEP][MT];
 #pragma unroll
       for (int u = 0; u < STEP; ++u)
 #pragma unroll
         for (int s = 0; s < KS; ++s) b[u][s] = lds[ts(s) ^ lb[i0 + u]];
+      // m-tiles two at a time: every element is in registers by then, and four accumulators would spill
+      constexpr int MP = MT < 2 ? MT : 2;
 #pragma unroll
-      for (int u = 0; u < STEP; ++u)
-#pragma unroll
-        for (int m = 0; m < MT; ++m) acc[u][m] = acc_t{0, 0, 0, 0};
-#pragma unroll
-      for (int s = 0; s < KS; ++s)
+      for (int m0 = 0; m0 < MT; m0 += MP) {
+        acc_t acc[STEP][MP];
 #pragma unroll
         for (int u = 0; u < STEP; ++u)
 #pragma unroll
-          for (int m = 0; m < MT; ++m) acc[u][m] = M::mma(a[m][s], b[u][s], acc[u][m]);
+          for (int m = 0; m < MP; ++m) {
+            const int r0 = 4 * (m0 + m);
+            acc[u][m] = acc_t{b[u][r0], b[u][r0 + 1], b[u][r0 + 2], b[u][r0 + 3]};
+          }
 #pragma unroll
-      for (int u = 0; u < STEP; ++u)
-        if (FULL || act[i0 + u]) {
+        for (int s = 0; s < KS; ++s)
 #pragma unroll
-          for (int m = 0; m < MT; ++m)
+          for (int u = 0; u < STEP; ++u)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) lds[ts(4 * m + r) ^ lb[i0 + u]] = acc[u][m][r];
-        }
+            for (int m = 0; m < MP; ++m) acc[u][m] = M::mma(a[m0 + m][s], b[u][s], acc[u][m]);
+#pragma unroll
+        for (int u = 0; u < STEP; ++u)
+          if (FULL || act[i0 + u]) {
+#pragma unroll
+            for (int m = 0; m < MP; ++m)
+#pragma unroll
+              for (int r = 0; r < 4; ++r) lds[ts(4 * (m0 + m) + r) ^ lb[i0 + u]] = acc[u][m][r];
+          }
+      }
     }
   }
 };
@@ -200,21 +210,36 @@ __device__ inline int ycount(uint32_t a, int k) {
   return __popc(~a & (a >> k) & m);
 }
 
-// entry (a, b) of the real form of a superoperator S (4^k x 4^k complex)
-__device__ inline double real_entry(const f64x2* S, int k, uint32_t a, uint32_t b) {
+// E[a][b] = R[a][b] - (a == b) of the real form R of a superoperator S (4^k x 4^k complex), as hi + lo: summed
+// without rounding loss, because R's first row is (1, 0, .., 0) but for the rounding of S, and that defect,
+// far below one unit in the last place of 1, acts on the trace once per superoperator.
+__device__ inline void real_entry(const f64x2* S, int k, uint32_t a, uint32_t b, double* hi, double* lo) {
   const uint32_t m = (1u << k) - 1u;
   const uint32_t ra = a & m, ca = a >> k, rb = b & m, cb = b >> k;
-  double sr = 0.0, si = 0.0;
+  const int d = (ycount(a, k) - ycount(b, k)) & 3;  // Re((-i)^d (x + i y)) = x, y, -x, -y
+  const double scale = 1.0 / (double)(1u << k);
+  double h = a == b ? -1.0 : 0.0, l = 0.0;
   for (uint32_t u = 0; u <= m; ++u)
     for (uint32_t v = 0; v <= m; ++v) {
       const f64x2 x = S[(((u ^ ra ^ ca) + (u << k)) << (2 * k)) + (v ^ rb ^ cb) + (v << k)];
-      const bool neg = (__popc(u & ca) + __popc(v & cb)) & 1;
-      sr += neg ? -x[0] : x[0];
-      si += neg ? -x[1] : x[1];
+      const bool neg = ((__popc(u & ca) + __popc(v & cb)) & 1) != (d >> 1);
+      double t = ((d & 1) ? x[1] : x[0]) * scale;
+      t = neg ? -t : t;
+      const double s = h + t, bb = s - h;  // s + the error term is the exact sum
+      l += (h - (s - bb)) + (t - bb);
+      h = s;
     }
-  const int d = (ycount(a, k) - ycount(b, k)) & 3;  // Re((-i)^d (sr + i si))
-  const double v = d == 0 ? sr : (d == 1 ? si : (d == 2 ? -sr : -si));
-  return v / (double)(1u << k);
+  *hi = h + l;
+  *lo = l - (*hi - h);
+}
+
+// A superoperator that keeps the trace up to rounding (|E[0][0]| below this) is applied as (1 + d) (I + P) with
+// d = E[0][0] and P = (E - d (I + E)) / (1 + d), so P[0][0] = 0: the factors are products of 1 + d over the
+// list, far more exact than a first row rounded to doubles, and are applied to the result once.
+constexpr double kRealDefect = 0x1p-30;
+__device__ inline double real_defect(double e00) { return fabs(e00) < kRealDefect ? e00 : 0.0; }
+__device__ inline double real_operand(double hi, double lo, double d, bool diag, bool first) {
+  return first && d != 0.0 ? 0.0 : hi + (lo - d * (hi + (diag ? 1.0 : 0.0)));
 }
 
 // fragment element e of a packed real operand: its row and column (real.hpp, OpReal)
@@ -339,7 +364,7 @@ __device__ inline void real_pass_tiles(double* __restrict__ w, const double* __r
       f64x4 acc[2];
 #pragma unroll
       for (int i = 0; i < NBW; ++i) {
-        f64x4 c = {0, 0, 0, 0};
+        f64x4 c = {b[i][0], b[i][1], b[i][2], b[i][3]};  // y = x + P x (OpReal)
 #pragma unroll
         for (int s = 0; s < 4; ++s) c = Mfma<double>::mma(a[j][s], b[i][s], c);
         acc[i & 1] = c;

@@ -484,7 +484,11 @@ void tanq_server_s::run_iteration() {
         const size_t np = r->paulis.size(), nprob = r->want_probs ? (size_t)1 << r->n : 0;
         uint64_t* masks = (uint64_t*)(hres + 1 + nprob + 2 * np);
         if (np) std::memcpy(masks, r->paulis.data(), 3 * np * sizeof(uint64_t));
-        launch_real_outputs(rho, r->n, p, r->want_probs, (int)np, masks, hres, stream);
+        // every block has the server's width, so the operands lie at equal distances
+        const int nblk = (int)r->pack_off.size();
+        const size_t stride = align256(packed_bytes(cfg.width, p));
+        launch_real_outputs(rho, r->n, p, r->want_probs, (int)np, masks, nblk ? arena_base + r->pack_off[0] : nullptr,
+                            cfg.width, stride, nblk, hres, stream);
         continue;
       }
       launch_diag(rho, r->n, p, probs_dev, partials, result_dev, 1, stream);

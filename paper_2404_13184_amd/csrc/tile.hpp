@@ -234,10 +234,7 @@ __device__ inline void c1_group(const T (&sr)[16], const T (&si)[16], const type
     for (int b = 0; b < 4; ++b) {
       const T cr = sr[4 * a + b], ci = si[4 * a + b], xr = x[b][0], xi = x[b][1];
       yr += __builtin_elementwise_fma(cr, xr, -(ci * xi));
-      if constexpr (sizeof(T) == 8)
-        yi += __builtin_elementwise_fma(ci, xr, cr * xi);
-      else
-        yi += __builtin_elementwise_fma(cr, xi, ci * xr);
+      yi += __builtin_elementwise_fma(ci, xr, cr * xi);
     }
     y[a] = typename Mfma<T>::c2{yr, yi};
   }
