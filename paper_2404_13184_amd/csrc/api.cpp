@@ -39,6 +39,8 @@ constexpr int RING = 8;
 constexpr int RESULT_DOUBLES = 4096;            // result scratch of a handle
 constexpr int HERM_FLAG_AT = RESULT_DOUBLES - 1;  // its last word: the Hermitian flag of a list
 constexpr size_t SLOT_DOUBLES = 2 * 64 * 64;  // one 3-qubit superoperator, complex128
+constexpr int PAULI_CHUNK = 1024;             // strings per launch
+constexpr size_t RES_BYTES = (size_t)1 << 20; // 2^17 probabilities or outcomes
 
 void check_prec(tanq_prec p) {
   if (p != TANQ_F64 && p != TANQ_F32) fail(TANQ_E_ARG, "precision must be TANQ_F64 or TANQ_F32");
@@ -82,14 +84,18 @@ struct tanq_dm_s {
   bool owned = false;
   hipStream_t stream = nullptr;
   int device = 0;
-  double* probs_dev = nullptr;
+  // device scratch, one allocation
+  unsigned char* scratch = nullptr;
+  double* probs_dev = nullptr;            // 2^n
   double* partials = nullptr;
   double* result_dev = nullptr;
-  uint64_t* masks_dev = nullptr;
-  double* s_raw_dev = nullptr;      // RING slots of a FP64 superoperator
   unsigned char* s_packed_dev = nullptr;  // RING slots of a packed operand
-  double* pinned = nullptr;         // RING slots, host
-  hipEvent_t ev[RING] = {};
+  // pinned host memory, one allocation, which kernels read and write directly
+  unsigned char* host = nullptr;
+  double* pinned = nullptr;               // RING slots of a FP64 superoperator
+  uint64_t* host_masks = nullptr;         // of one chunk of Pauli strings
+  double* host_res = nullptr;             // RES_BYTES: results of a synchronising call
+  hipEvent_t ev[2] = {};                  // the last use of each half of the slots
   int ring = 0;
 
   uint64_t elements() const { return 1ull << (2 * n); }
@@ -120,30 +126,30 @@ struct tanq_fused_s {
 namespace {
 
 void dm_alloc_scratch(tanq_dm_s* d) {
-  const uint64_t dim = 1ull << d->n;
-  TANQ_HIP(hipMalloc((void**)&d->probs_dev, dim * sizeof(double)));
-  TANQ_HIP(hipMalloc((void**)&d->partials, (size_t)reduce_partials() * sizeof(double)));
-  TANQ_HIP(hipMalloc((void**)&d->result_dev, RESULT_DOUBLES * sizeof(double)));
-  TANQ_HIP(hipMalloc((void**)&d->masks_dev, 3 * 2048 * sizeof(uint64_t)));
-  TANQ_HIP(hipMalloc((void**)&d->s_raw_dev, RING * SLOT_DOUBLES * sizeof(double)));
-  TANQ_HIP(hipMalloc((void**)&d->s_packed_dev, RING * packed_bytes(3, TANQ_F64)));
-  TANQ_HIP(hipHostMalloc((void**)&d->pinned, RING * SLOT_DOUBLES * sizeof(double), hipHostMallocDefault));
-  for (int i = 0; i < RING; ++i) TANQ_HIP(hipEventCreateWithFlags(&d->ev[i], hipEventDisableTiming));
+  const size_t probs_b = align256(((size_t)1 << d->n) * sizeof(double));
+  const size_t part_b = align256((size_t)reduce_partials() * sizeof(double));
+  const size_t res_b = align256(RESULT_DOUBLES * sizeof(double));
+  TANQ_HIP(hipMalloc((void**)&d->scratch, probs_b + part_b + res_b + RING * packed_bytes(3, TANQ_F64)));
+  d->probs_dev = reinterpret_cast<double*>(d->scratch);
+  d->partials = reinterpret_cast<double*>(d->scratch + probs_b);
+  d->result_dev = reinterpret_cast<double*>(d->scratch + probs_b + part_b);
+  d->s_packed_dev = d->scratch + probs_b + part_b + res_b;
+  const size_t ring_b = RING * SLOT_DOUBLES * sizeof(double), mask_b = 3 * PAULI_CHUNK * sizeof(uint64_t);
+  TANQ_HIP(hipHostMalloc((void**)&d->host, ring_b + mask_b + RES_BYTES, hipHostMallocDefault));
+  d->pinned = reinterpret_cast<double*>(d->host);
+  d->host_masks = reinterpret_cast<uint64_t*>(d->host + ring_b);
+  d->host_res = reinterpret_cast<double*>(d->host + ring_b + mask_b);
+  for (hipEvent_t& e : d->ev) TANQ_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
 }
 
 void dm_release(tanq_dm_s* d) {
   if (!d) return;
   (void)hipSetDevice(d->device);
   (void)hipStreamSynchronize(d->stream);
-  for (int i = 0; i < RING; ++i)
-    if (d->ev[i]) (void)hipEventDestroy(d->ev[i]);
-  if (d->pinned) (void)hipHostFree(d->pinned);
-  dfree(d->probs_dev);
-  dfree(d->partials);
-  dfree(d->result_dev);
-  dfree(d->masks_dev);
-  dfree(d->s_raw_dev);
-  dfree(d->s_packed_dev);
+  for (hipEvent_t e : d->ev)
+    if (e) (void)hipEventDestroy(e);
+  if (d->host) (void)hipHostFree(d->host);
+  dfree(d->scratch);
   if (d->owned && d->ptr) (void)hipFree(d->ptr);
   delete d;
 }
@@ -908,17 +914,19 @@ tanq_status tanq_apply_superop(tanq_dm d, int k, const int* qubits, const double
     check_qubits(d->n, k, qubits, 3);
     if (!S) fail(TANQ_E_ARG, "superoperator pointer is NULL");
     DeviceGuard g(d->device);
-    const int slot = d->ring;
+    if (k == 1) {  // small enough to travel with the launch
+      launch_apply_one_qubit(d->ptr, d->n, d->prec, qubits[0], S, d->stream);
+      return;
+    }
+    // A slot is read by its pack kernel; the event after the last slot of each half orders the half's reuse.
+    const int slot = d->ring, half = slot / (RING / 2);
     d->ring = (d->ring + 1) % RING;
-    TANQ_HIP(hipEventSynchronize(d->ev[slot]));  // previous upload from this slot is done
-    const size_t cnt = ((size_t)1 << (4 * k)) * 2;
+    if (slot % (RING / 2) == 0) TANQ_HIP(hipEventSynchronize(d->ev[half]));
     double* host = d->pinned + slot * SLOT_DOUBLES;
-    std::memcpy(host, S, cnt * sizeof(double));
-    double* raw = d->s_raw_dev + slot * SLOT_DOUBLES;
+    std::memcpy(host, S, ((size_t)1 << (4 * k)) * 2 * sizeof(double));
     unsigned char* packed = d->s_packed_dev + slot * packed_bytes(3, TANQ_F64);
-    TANQ_HIP(hipMemcpyAsync(raw, host, cnt * sizeof(double), hipMemcpyHostToDevice, d->stream));
-    TANQ_HIP(hipEventRecord(d->ev[slot], d->stream));
-    launch_pack_one(k, raw, packed, d->prec, d->stream);
+    launch_pack_one(k, host, packed, d->prec, d->stream);
+    if (slot % (RING / 2) == RING / 2 - 1) TANQ_HIP(hipEventRecord(d->ev[half], d->stream));
     launch_apply(d->ptr, d->n, d->prec, k, qubits, packed, d->stream);
   });
 }
@@ -1218,11 +1226,10 @@ static void autotune_impl(tanq_dm d, int reps, bool dense, double* ms_per_apply)
           S = dense_unitary_superop(k);
         else
           for (int a = 0; a < D; ++a) S[2 * ((size_t)a * D + a)] = 1.0;
-        double* raw = d->s_raw_dev;
         unsigned char* packed = d->s_packed_dev;
-        TANQ_HIP(hipStreamSynchronize(d->stream));
-        TANQ_HIP(hipMemcpy(raw, S.data(), S.size() * sizeof(double), hipMemcpyHostToDevice));
-        launch_pack_one(k, raw, packed, p, d->stream);
+        TANQ_HIP(hipStreamSynchronize(d->stream));  // slot 0 is free
+        std::memcpy(d->pinned, S.data(), S.size() * sizeof(double));
+        launch_pack_one(k, d->pinned, packed, p, d->stream);
         int lo[3], hi[3];
         for (int t = 0; t < k; ++t) {
           lo[t] = t;
@@ -1268,8 +1275,8 @@ static void autotune_impl(tanq_dm d, int reps, bool dense, double* ms_per_apply)
         else
           for (int a = 0; a < D; ++a) S[2 * ((size_t)a * D + a)] = 1.0;
         TANQ_HIP(hipStreamSynchronize(d->stream));
-        TANQ_HIP(hipMemcpy(d->s_raw_dev, S.data(), S.size() * sizeof(double), hipMemcpyHostToDevice));
-        launch_pack_one(2, d->s_raw_dev, d->s_packed_dev, p, d->stream);
+        std::memcpy(d->pinned, S.data(), S.size() * sizeof(double));
+        launch_pack_one(2, d->pinned, d->s_packed_dev, p, d->stream);
         const int a = n - 4, b = n - 3, c = n - 2, e = n - 1;
         const int cyc[6][2] = {{a, b}, {c, e}, {a, c}, {b, e}, {a, e}, {b, c}};
         const int mmax = std::min(pass_limit(), pass_max(p));
@@ -1390,13 +1397,14 @@ tanq_status tanq_probs(tanq_dm d, double* host_out, int renormalize, double* tra
     check_dm(d);
     if (!host_out) fail(TANQ_E_ARG, "output buffer is NULL");
     DeviceGuard g(d->device);
-    launch_diag(d->ptr, d->n, d->prec, d->probs_dev, d->partials, d->result_dev, renormalize, d->stream);
-    TANQ_HIP(hipMemcpyAsync(host_out, d->probs_dev, (1ull << d->n) * sizeof(double), hipMemcpyDeviceToHost,
-                            d->stream));
-    double tr = 0.0;
-    TANQ_HIP(hipMemcpyAsync(&tr, d->result_dev, sizeof(double), hipMemcpyDeviceToHost, d->stream));
+    const size_t dim = (size_t)1 << d->n;
+    // the results pass through the pinned buffer; the trace through the first word of the masks'
+    double* tr = reinterpret_cast<double*>(d->host_masks);
+    launch_probs(d->ptr, d->n, d->prec, renormalize, nullptr, nullptr, d->probs_dev, d->partials, d->host_res, tr,
+                 d->stream);
     TANQ_HIP(hipStreamSynchronize(d->stream));
-    if (trace_out) *trace_out = tr;
+    std::memcpy(host_out, d->host_res, dim * sizeof(double));
+    if (trace_out) *trace_out = *tr;
   });
 }
 
@@ -1414,11 +1422,9 @@ tanq_status tanq_probs_readout(tanq_dm d, const double* p01, const double* p10, 
     if (!host_out || !p01 || !p10) fail(TANQ_E_ARG, "NULL argument");
     check_readout(d->n, p01, p10);
     DeviceGuard g(d->device);
-    launch_diag(d->ptr, d->n, d->prec, d->probs_dev, d->partials, d->result_dev, 1, d->stream);
-    launch_readout(d->probs_dev, d->n, p01, p10, d->stream);
-    TANQ_HIP(hipMemcpyAsync(host_out, d->probs_dev, (1ull << d->n) * sizeof(double), hipMemcpyDeviceToHost,
-                            d->stream));
+    launch_probs(d->ptr, d->n, d->prec, 1, p01, p10, d->probs_dev, d->partials, d->host_res, nullptr, d->stream);
     TANQ_HIP(hipStreamSynchronize(d->stream));
+    std::memcpy(host_out, d->host_res, ((size_t)1 << d->n) * sizeof(double));
   });
 }
 
@@ -1427,7 +1433,7 @@ tanq_status tanq_probs_readout(tanq_dm d, const double* p01, const double* p10, 
 namespace tanq {
 
 void sample_check(tanq_dm d, uint64_t shots, uint64_t seed, const double* p01, const double* p10, uint64_t* host_out,
-                  int* n, int* device) {
+                  int* n, int* device, bool* own) {
   check_dm(d);
   if (shots > 0 && !host_out) fail(TANQ_E_ARG, "NULL argument");
   if (seed >= (1ull << 23)) fail(TANQ_E_ARG, "seed must be below 2^23");
@@ -1435,16 +1441,18 @@ void sample_check(tanq_dm d, uint64_t shots, uint64_t seed, const double* p01, c
   check_readout(d->n, p01, p10);
   *n = d->n;
   *device = d->device;
+  *own = shots * sizeof(uint64_t) <= RES_BYTES;
 }
 
-void sample_run(tanq_dm d, uint64_t shots, uint64_t seed, const double* p01, const double* p10, double* cdf_dev,
-                uint64_t* out_dev, uint64_t* host_out) {
+void sample_run(tanq_dm d, uint64_t shots, uint64_t seed, const double* p01, const double* p10, uint64_t* out_dev,
+                uint64_t* host_out) {
   DeviceGuard g(d->device);
-  launch_diag(d->ptr, d->n, d->prec, d->probs_dev, d->partials, d->result_dev, 1, d->stream);
-  if (p01) launch_readout(d->probs_dev, d->n, p01, p10, d->stream);
-  launch_sample(d->probs_dev, d->n, cdf_dev, shots, seed, out_dev, d->stream);
-  TANQ_HIP(hipMemcpyAsync(host_out, out_dev, shots * sizeof(uint64_t), hipMemcpyDeviceToHost, d->stream));
+  const bool own = shots * sizeof(uint64_t) <= RES_BYTES;
+  uint64_t* out = own ? reinterpret_cast<uint64_t*>(d->host_res) : out_dev;
+  launch_sample(d->ptr, d->n, d->prec, p01, p10, d->probs_dev, d->partials, shots, seed, out, d->stream);
+  if (!own) TANQ_HIP(hipMemcpyAsync(host_out, out, shots * sizeof(uint64_t), hipMemcpyDeviceToHost, d->stream));
   TANQ_HIP(hipStreamSynchronize(d->stream));
+  if (own) std::memcpy(host_out, out, shots * sizeof(uint64_t));
 }
 
 }  // namespace tanq
@@ -1455,22 +1463,19 @@ tanq_status tanq_sample(tanq_dm d, uint64_t shots, uint64_t seed, const double* 
                         uint64_t* host_out) {
   return guarded([&] {
     int n = 0, device = 0;
-    sample_check(d, shots, seed, p01, p10, host_out, &n, &device);
+    bool own = false;
+    sample_check(d, shots, seed, p01, p10, host_out, &n, &device, &own);
     if (shots == 0) return;
     DeviceGuard g(device);
-    double* cdf = nullptr;
     uint64_t* out = nullptr;
     try {
-      TANQ_HIP(hipMalloc((void**)&cdf, (1ull << n) * sizeof(double)));
-      TANQ_HIP(hipMalloc((void**)&out, shots * sizeof(uint64_t)));
-      sample_run(d, shots, seed, p01, p10, cdf, out, host_out);
+      if (!own) TANQ_HIP(hipMalloc((void**)&out, shots * sizeof(uint64_t)));
+      sample_run(d, shots, seed, p01, p10, out, host_out);
     } catch (...) {
       (void)hipStreamSynchronize(d->stream);
-      dfree(cdf);
       dfree(out);
       throw;
     }
-    dfree(cdf);
     dfree(out);
   });
 }
@@ -1491,12 +1496,9 @@ tanq_status tanq_reduced_dm(tanq_dm d, int k, const int* keep, double* host_out)
     if (!host_out) fail(TANQ_E_ARG, "output is NULL");
     check_qubits(d->n, k, keep, 4);
     DeviceGuard g(d->device);
-    int* kd = reinterpret_cast<int*>(d->masks_dev);  // small device scratch of the handle
-    TANQ_HIP(hipMemcpyAsync(kd, keep, k * sizeof(int), hipMemcpyHostToDevice, d->stream));
-    launch_reduced(d->ptr, d->n, d->prec, k, kd, d->result_dev, d->stream);
-    TANQ_HIP(hipMemcpyAsync(host_out, d->result_dev, 2 * ((size_t)1 << (2 * k)) * sizeof(double),
-                            hipMemcpyDeviceToHost, d->stream));
+    launch_reduced(d->ptr, d->n, d->prec, k, keep, d->partials, d->host_res, d->stream);
     TANQ_HIP(hipStreamSynchronize(d->stream));
+    std::memcpy(host_out, d->host_res, 2 * ((size_t)1 << (2 * k)) * sizeof(double));
   });
 }
 
@@ -1581,21 +1583,14 @@ tanq_status tanq_expect_pauli_batch(tanq_dm d, int count, const char* const* pau
     check_dm(d);
     if (count < 0 || (count > 0 && (!paulis || !out_re))) fail(TANQ_E_ARG, "NULL argument");
     DeviceGuard g(d->device);
-    constexpr int CHUNK = 1024;
-    std::vector<uint64_t> masks(3 * CHUNK);
-    std::vector<double> res(2 * CHUNK);
-    for (int base = 0; base < count; base += CHUNK) {
-      const int cnt = std::min(CHUNK, count - base);
-      for (int i = 0; i < cnt; ++i) parse_pauli(d->n, paulis[base + i], &masks[3 * i]);
-      TANQ_HIP(hipMemcpyAsync(d->masks_dev, masks.data(), 3 * cnt * sizeof(uint64_t), hipMemcpyHostToDevice,
-                              d->stream));
-      launch_pauli(d->ptr, d->n, d->prec, cnt, d->masks_dev, d->partials, d->result_dev, d->stream);
-      TANQ_HIP(hipMemcpyAsync(res.data(), d->result_dev, 2 * cnt * sizeof(double), hipMemcpyDeviceToHost,
-                              d->stream));
+    for (int base = 0; base < count; base += PAULI_CHUNK) {
+      const int cnt = std::min(PAULI_CHUNK, count - base);
+      for (int i = 0; i < cnt; ++i) parse_pauli(d->n, paulis[base + i], &d->host_masks[3 * i]);
+      launch_pauli(d->ptr, d->n, d->prec, cnt, d->host_masks, d->partials, d->host_res, d->stream);
       TANQ_HIP(hipStreamSynchronize(d->stream));
       for (int i = 0; i < cnt; ++i) {
-        out_re[base + i] = res[2 * i];
-        if (out_im) out_im[base + i] = res[2 * i + 1];
+        out_re[base + i] = d->host_res[2 * i];
+        if (out_im) out_im[base + i] = d->host_res[2 * i + 1];
       }
     }
   });

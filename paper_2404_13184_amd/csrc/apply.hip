@@ -193,10 +193,12 @@ TANQ_DMA_INSTANCE(float, 3, 11, 256)
 // C1 apply (k = 1): VALU, one group of four amplitudes per thread
 // ------------------------------------------------------------------------------------
 
+struct C1Op {
+  double s[32];
+};
+
 template <typename T>
-__global__ __launch_bounds__(256) void apply_c1_kernel(T* __restrict__ rho, const double* __restrict__ S,
-                                                      const C1Geom g, const uint32_t* skip) {
-  if (skip_launch(skip)) return;
+__device__ inline void c1_apply(T* __restrict__ rho, const double* S, const C1Geom& g) {
   using c2 = typename Mfma<T>::c2;
   T sr[16], si[16];
 #pragma unroll
@@ -223,13 +225,46 @@ __global__ __launch_bounds__(256) void apply_c1_kernel(T* __restrict__ rho, cons
   }
 }
 
+template <typename T>
+__global__ __launch_bounds__(256) void apply_c1_kernel(T* __restrict__ rho, const double* __restrict__ S,
+                                                      const C1Geom g, const uint32_t* skip) {
+  if (skip_launch(skip)) return;
+  c1_apply<T>(rho, S, g);
+}
+
+// the superoperator in the kernel's arguments: a caller's own channel is one launch, with no copy and no packing
+// (14.8 -> 5.7 us a call at 5 qubits)
+template <typename T>
+__global__ __launch_bounds__(256) void apply_c1_arg_kernel(T* __restrict__ rho, const C1Op S, const C1Geom g) {
+  c1_apply<T>(rho, S.s, g);
+}
+
 // ------------------------------------------------------------------------------------
 // packing of FP64 superoperators into the kernels' A-operand lane layouts
 // ------------------------------------------------------------------------------------
 
-template <typename T>
-__global__ void pack_one_kernel(int k, const double* __restrict__ raw, unsigned char* __restrict__ packed) {
-  pack_block<T>(k, raw, packed);
+// One superoperator, in pinned host memory or on the device.  Each workgroup first brings its 256 entries into
+// LDS with one load per thread (one round trip to the host): a two-qubit superoperator is one workgroup,
+// a three-qubit one sixteen (m-tile x four k-steps).
+template <typename T, int K>
+__global__ __launch_bounds__(256) void pack_one_kernel(const double* __restrict__ raw, T* __restrict__ P) {
+  __shared__ f64x2 l[256];
+  const f64x2* S = reinterpret_cast<const f64x2*>(raw);
+  const int tid = threadIdx.x;
+  if constexpr (K == 2) {
+    l[tid] = S[tid];
+    __syncthreads();
+    pack_block<T>(2, reinterpret_cast<const double*>(l), reinterpret_cast<unsigned char*>(P));
+  } else {
+    const int mt = blockIdx.x >> 2, k0 = (blockIdx.x & 3) * 4;  // rows 16 mt.., columns 4 k0..
+    l[tid] = S[(16 * mt + (tid >> 4)) * 64 + 4 * k0 + (tid & 15)];
+    __syncthreads();
+    for (int e = tid; e < 4 * 3 * 64; e += 256) {
+      const int lane = e & 63, c = (e >> 6) % 3, ks = (e >> 6) / 3;
+      const f64x2 v = l[(lane & 15) * 16 + 4 * ks + (lane >> 4)];
+      P[((mt * 16 + k0 + ks) * 3 + c) * 64 + lane] = (T)(c == 0 ? v[0] : (c == 1 ? v[1] : v[0] + v[1]));
+    }
+  }
 }
 
 // ------------------------------------------------------------------------------------
@@ -527,18 +562,32 @@ void launch_apply_variant(void* rho, int n, tanq_prec p, int k, int local, const
   kVariants[gi].fn(rho, n, qubits, packed, s, skip);
 }
 
+static unsigned c1_blocks(const C1Geom& g) {
+  const uint64_t blocks = (g.ngroups + 255) / 256, cap = (uint64_t)cu_count() * 32;
+  return (unsigned)(blocks < cap ? blocks : cap);
+}
+
+void launch_apply_one_qubit(void* rho, int n, tanq_prec p, int qubit, const double* S, hipStream_t s) {
+  const C1Geom g{1ull << (2 * (n - 1)), qubit, n};
+  C1Op op;
+  std::memcpy(op.s, S, sizeof(op.s));
+  if (p == TANQ_F64)
+    hipLaunchKernelGGL(apply_c1_arg_kernel<double>, dim3(c1_blocks(g)), dim3(256), 0, s, (double*)rho, op, g);
+  else
+    hipLaunchKernelGGL(apply_c1_arg_kernel<float>, dim3(c1_blocks(g)), dim3(256), 0, s, (float*)rho, op, g);
+  TANQ_HIP(hipGetLastError());
+}
+
 void launch_apply(void* rho, int n, tanq_prec p, int k, const int* qubits, const void* packed, hipStream_t s,
                   const uint32_t* skip) {
   if (k == 1) {
     C1Geom g{1ull << (2 * (n - 1)), qubits[0], n};
-    uint64_t blocks = (g.ngroups + 255) / 256;
-    const uint64_t cap = (uint64_t)cu_count() * 32;
-    if (blocks > cap) blocks = cap;
+    const unsigned blocks = c1_blocks(g);
     if (p == TANQ_F64)
-      hipLaunchKernelGGL(apply_c1_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, s, (double*)rho,
+      hipLaunchKernelGGL(apply_c1_kernel<double>, dim3(blocks), dim3(256), 0, s, (double*)rho,
                          (const double*)packed, g, skip);
     else
-      hipLaunchKernelGGL(apply_c1_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, s, (float*)rho,
+      hipLaunchKernelGGL(apply_c1_kernel<float>, dim3(blocks), dim3(256), 0, s, (float*)rho,
                          (const double*)packed, g, skip);
     TANQ_HIP(hipGetLastError());
     return;
@@ -547,12 +596,22 @@ void launch_apply(void* rho, int n, tanq_prec p, int k, const int* qubits, const
   launch_apply_variant(rho, n, p, k, variant_for(n, k, p), qubits, packed, s, skip);
 }
 
+template <typename T>
+static void pack_one_typed(int k, const double* raw, void* packed, hipStream_t s) {
+  if (k == 1)  // the superoperator itself, for both precisions
+    TANQ_HIP(hipMemcpyAsync(packed, raw, 32 * sizeof(double), hipMemcpyDefault, s));
+  else if (k == 2)
+    hipLaunchKernelGGL((pack_one_kernel<T, 2>), dim3(1), dim3(256), 0, s, raw, (T*)packed);
+  else
+    hipLaunchKernelGGL((pack_one_kernel<T, 3>), dim3(16), dim3(256), 0, s, raw, (T*)packed);
+  TANQ_HIP(hipGetLastError());
+}
+
 void launch_pack_one(int k, const double* raw, void* packed, tanq_prec p, hipStream_t s) {
   if (p == TANQ_F64)
-    hipLaunchKernelGGL(pack_one_kernel<double>, dim3(1), dim3(256), 0, s, k, raw, (unsigned char*)packed);
+    pack_one_typed<double>(k, raw, packed, s);
   else
-    hipLaunchKernelGGL(pack_one_kernel<float>, dim3(1), dim3(256), 0, s, k, raw, (unsigned char*)packed);
-  TANQ_HIP(hipGetLastError());
+    pack_one_typed<float>(k, raw, packed, s);
 }
 
 }  // namespace tanq

@@ -272,13 +272,13 @@ void launch_scale(void* rho, int n, tanq_prec p, double f, hipStream_t s);
 // current device; synchronous.
 double mfma_rate_tflops(tanq_prec p);
 
-// All-qubit sampling (tanq_sample and its variant without allocations): argument checks (also
-// returning the handle's qubit count and device), and the work itself on the caller's device
-// buffers for the CDF (2^n doubles) and the outcomes (shots words); synchronises.
+// All-qubit sampling (tanq_sample and its variant without allocations): argument checks (also returning the
+// handle's device and whether its own result buffer holds the outcomes), and the work itself; out_dev:
+// device buffer for the outcomes, unused if the handle's holds them.  Synchronises.
 void sample_check(tanq_dm d, uint64_t shots, uint64_t seed, const double* p01, const double* p10, uint64_t* host_out,
-                  int* n, int* device);
-void sample_run(tanq_dm d, uint64_t shots, uint64_t seed, const double* p01, const double* p10, double* cdf_dev,
-                uint64_t* out_dev, uint64_t* host_out);
+                  int* n, int* device, bool* own);
+void sample_run(tanq_dm d, uint64_t shots, uint64_t seed, const double* p01, const double* p10, uint64_t* out_dev,
+                uint64_t* host_out);
 
 // Apply one superoperator whose packed operand is at `packed` (device).
 //   k == 1: packed = 4x4 complex FP64 (32 doubles), used for both precisions.
@@ -293,8 +293,10 @@ void launch_build_superops(const FuseOpDev* ops, int nops, const double* kraus, 
 // kernels' operand layout of precision p.
 void launch_compose(const FuseBlockDev* blocks, int nblocks, int max_k, const FuseOpDev* ops, const double* sops,
                     double* out, void* packed, tanq_prec p, hipStream_t s);
-// Pack a single FP64 superoperator (device) of width k.
+// Pack a single FP64 superoperator of width k (device or pinned host memory).
 void launch_pack_one(int k, const double* raw, void* packed, tanq_prec p, hipStream_t s);
+// A one-qubit superoperator (host, 4 x 4 complex) that travels with the launch.
+void launch_apply_one_qubit(void* rho, int n, tanq_prec p, int qubit, const double* S, hipStream_t s);
 
 // Real form (real.hip).  Superoperators of every operation as real 4^j x 4^j matrices minus the identity (offset
 // sop_off, in doubles), their composition per block in circuit order, packed as the real apply kernels'
@@ -312,25 +314,26 @@ constexpr int kRealOutMaxN = 14;
 void launch_real_outputs(const void* w, int n, tanq_prec p, int want_probs, int count, const uint64_t* masks,
                          const void* packed, int k, size_t stride_bytes, int nblocks, double* out, hipStream_t s);
 
-// Reductions (FP64).  partials: device scratch of at least reduce_partials() doubles.
+// Measurement statistics (measure.hip; FP64).  partials: device scratch of at least reduce_partials() doubles;
+// probs_dev: of 2^n doubles.  Outputs (out, trace, masks) are device-accessible: device memory or
+// pinned host memory.
 int reduce_partials();
-void launch_diag(const void* rho, int n, tanq_prec p, double* probs_dev, double* partials,
-                 double* result_dev, int renormalize, hipStream_t s);
-void launch_pauli(const void* rho, int n, tanq_prec p, int count, const uint64_t* masks_dev,
-                  double* partials, double* result_dev, hipStream_t s);
+// out[x] = Re rho[x][x], divided by the trace if renormalize, through the readout error if p01 (host arrays of
+// n values); out and trace may be NULL
+void launch_probs(const void* rho, int n, tanq_prec p, int renormalize, const double* p01, const double* p10,
+                  double* probs_dev, double* partials, double* out, double* trace, hipStream_t s);
+// shots outcomes of the renormalised probabilities, through the readout error if p01
+void launch_sample(const void* rho, int n, tanq_prec p, const double* p01, const double* p10, double* probs_dev,
+                   double* partials, uint64_t shots, uint64_t seed, uint64_t* out, hipStream_t s);
+// out: (Re, Im) of count strings (at most 1024); masks: x, z, number of Y mod 4 per string
+void launch_pauli(const void* rho, int n, tanq_prec p, int count, const uint64_t* masks, double* partials, double* out,
+                  hipStream_t s);
+// reduced density matrix on the k <= 4 qubits keep (host), 2 * 4^k doubles
+void launch_reduced(const void* rho, int n, tanq_prec p, int k, const int* keep, double* partials, double* out,
+                    hipStream_t s);
 
 // vec(rho) = e_idx (rho = |r><c| for idx = r + c 2^n)
 void launch_init_basis(void* rho, int n, tanq_prec p, uint64_t idx, hipStream_t s);
-// Reduced density matrix on k <= 4 kept qubits (device list keep_dev); out_dev: 2 * 4^k doubles
-void launch_reduced(const void* rho, int n, tanq_prec p, int k, const int* keep_dev, double* out_dev, hipStream_t s);
-
-// Classical readout error on the probability vector, one qubit at a time (host arrays p01,
-// p10 of n values), in place.
-void launch_readout(double* probs_dev, int n, const double* p01, const double* p10, hipStream_t s);
-// Inverse-CDF sampling of `shots` outcomes with SplitMix64 draws; cdf_dev: 2^n doubles.
-void launch_sample(const double* probs_dev, int n, double* cdf_dev, uint64_t shots, uint64_t seed, uint64_t* out_dev,
-                   hipStream_t s);
-
 // out3 = (||a-b||_F, max|a-b|, ||a||_F); partials: reduce_partials() doubles.
 void launch_compare(const void* a, tanq_prec pa, const void* b, tanq_prec pb, uint64_t nel, double* partials,
                     double* result_dev, hipStream_t s);

@@ -1,5 +1,5 @@
 // Auxiliary HIP kernels of libtanq (gfx950): state initialisation and sampling, superoperator
-// construction and FP64 composition for fusion, and FP64 reductions.  The apply kernels (the
+// construction and FP64 composition for fusion, and the comparison of two states.  The apply kernels (the
 // hot path) and the packing of superoperators into their operand layouts are in apply.hip.
 #include <cstring>
 
@@ -261,70 +261,6 @@ __device__ inline double block_sum(double v, double* sh) {
   return t;
 }
 
-// p[x] = Re rho[x][x] = Re vec[x (2^n + 1)]; partial trace per workgroup
-template <typename T>
-__global__ __launch_bounds__(RED_THREADS) void diag_kernel(const T* __restrict__ rho, int n, double* __restrict__ p,
-                                                          double* __restrict__ partials) {
-  __shared__ double sh[RED_THREADS / 64];
-  const uint64_t dim = 1ull << n;
-  double acc = 0.0;
-  for (uint64_t x = (uint64_t)blockIdx.x * RED_THREADS + threadIdx.x; x < dim; x += (uint64_t)gridDim.x * RED_THREADS) {
-    const double v = (double)rho[2 * (x * (dim + 1))];
-    p[x] = v;
-    acc += v;
-  }
-  const double t = block_sum(acc, sh);
-  if (threadIdx.x == 0) partials[blockIdx.x] = t;
-}
-
-__global__ void sum_partials_kernel(const double* __restrict__ partials, int count, int nstr, double* __restrict__ out) {
-  // one thread per output value; fixed summation order
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < nstr) {
-    double t = 0.0;
-    for (int b = 0; b < count; ++b) t += partials[(size_t)i * count + b];
-    out[i] = t;
-  }
-}
-
-__global__ void renormalize_kernel(double* __restrict__ p, uint64_t dim, const double* __restrict__ tr) {
-  const double inv = 1.0 / tr[0];
-  for (uint64_t x = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; x < dim; x += (uint64_t)gridDim.x * blockDim.x)
-    p[x] *= inv;
-}
-
-// Tr(P rho) = sum_s phase(s) rho[s][s ^ xmask],  phase(s) = i^{#Y} (-1)^{popcount(s & zmask)}
-// masks[3 i + 0] = xmask (X or Y), masks[3 i + 1] = zmask (Z or Y), masks[3 i + 2] = #Y mod 4
-template <typename T>
-__global__ __launch_bounds__(RED_THREADS) void pauli_kernel(const T* __restrict__ rho, int n,
-                                                           const uint64_t* __restrict__ masks,
-                                                           double* __restrict__ partials) {
-  __shared__ double sh[RED_THREADS / 64];
-  const int si = blockIdx.y;
-  const uint64_t xm = masks[3 * si], zm = masks[3 * si + 1];
-  const int ny = (int)masks[3 * si + 2];
-  const uint64_t dim = 1ull << n;
-  double ar = 0.0, ai = 0.0;
-  for (uint64_t s = (uint64_t)blockIdx.x * RED_THREADS + threadIdx.x; s < dim; s += (uint64_t)gridDim.x * RED_THREADS) {
-    const uint64_t e = s + ((s ^ xm) << n);
-    const double vr = (double)rho[2 * e], vi = (double)rho[2 * e + 1];
-    const double sg = (__popcll(s & zm) & 1) ? -1.0 : 1.0;
-    ar += sg * vr;
-    ai += sg * vi;
-  }
-  // multiply by i^{#Y}
-  double pr = ar, pi = ai;
-  if (ny == 1) { pr = -ai; pi = ar; }
-  else if (ny == 2) { pr = -ar; pi = -ai; }
-  else if (ny == 3) { pr = ai; pi = -ar; }
-  const double tr = block_sum(pr, sh);
-  const double ti = block_sum(pi, sh);
-  if (threadIdx.x == 0) {
-    partials[((size_t)si * 2 + 0) * gridDim.x + blockIdx.x] = tr;
-    partials[((size_t)si * 2 + 1) * gridDim.x + blockIdx.x] = ti;
-  }
-}
-
 template <typename TA, typename TB>
 __global__ __launch_bounds__(RED_THREADS) void compare_kernel(const TA* __restrict__ a, const TB* __restrict__ b,
                                                              uint64_t nel, double* __restrict__ partials) {
@@ -366,104 +302,6 @@ __global__ void compare_finish_kernel(const double* __restrict__ partials, int n
     out[0] = sqrt(s0);
     out[1] = sqrt(m);
     out[2] = sqrt(s2);
-  }
-}
-
-// Reduced density matrix on the kept qubits: out[a][b] = sum over the other qubits' values f
-// of rho[dep(a) | f][dep(b) | f].  One workgroup per output element (a, b); FP64.
-template <typename T>
-__global__ __launch_bounds__(RED_THREADS) void reduced_kernel(const T* __restrict__ rho, int n, int k,
-                                                             const int* __restrict__ keep,
-                                                             double* __restrict__ out) {
-  __shared__ double sh[RED_THREADS / 64];
-  __shared__ int kq[8];
-  if (threadIdx.x < (unsigned)k) kq[threadIdx.x] = keep[threadIdx.x];
-  __syncthreads();
-  const int D = 1 << k;
-  const int a = blockIdx.x % D, b = blockIdx.x / D;
-  uint64_t ra = 0, rb = 0, kmask = 0;
-  for (int t = 0; t < k; ++t) {
-    kmask |= 1ull << kq[t];
-    if ((a >> t) & 1) ra |= 1ull << kq[t];
-    if ((b >> t) & 1) rb |= 1ull << kq[t];
-  }
-  const uint64_t nf = 1ull << (n - k);
-  double sr = 0.0, si = 0.0;
-  for (uint64_t f = threadIdx.x; f < nf; f += RED_THREADS) {
-    // deposit f into the bits outside kmask
-    uint64_t x = 0, ff = f;
-    for (int bit = 0; bit < n; ++bit)
-      if (!((kmask >> bit) & 1ull)) {
-        x |= (ff & 1ull) << bit;
-        ff >>= 1;
-      }
-    const uint64_t e = (ra | x) + ((rb | x) << n);
-    sr += (double)rho[2 * e];
-    si += (double)rho[2 * e + 1];
-  }
-  const double tr = block_sum(sr, sh);
-  const double ti = block_sum(si, sh);
-  if (threadIdx.x == 0) {
-    out[2 * (a * D + b)] = tr;
-    out[2 * (a * D + b) + 1] = ti;
-  }
-}
-
-// ------------------------------------------------------------------------------------
-// readout error and sampling (FP64, on the probability vector)
-// ------------------------------------------------------------------------------------
-
-// Qubit t is read as 1 when it is 0 with probability p10 and as 0 when it is 1 with p01:
-// q[x with bit t = 0] = (1 - p10) p[.0.] + p01 p[.1.],  q[.1.] = p10 p[.0.] + (1 - p01) p[.1.]
-__global__ void readout_kernel(double* __restrict__ p, uint64_t dim, int t, double p01, double p10) {
-  const uint64_t half = dim >> 1, bit = 1ull << t, low = bit - 1ull;
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < half; i += (uint64_t)gridDim.x * blockDim.x) {
-    const uint64_t x0 = ((i & ~low) << 1) | (i & low), x1 = x0 | bit;
-    const double a = p[x0], b = p[x1];
-    p[x0] = (1.0 - p10) * a + p01 * b;
-    p[x1] = p10 * a + (1.0 - p01) * b;
-  }
-}
-
-// Inclusive prefix sums of p[0..dim) by one workgroup of 1024 threads (fixed order).
-__global__ __launch_bounds__(1024) void cdf_kernel(const double* __restrict__ p, uint64_t dim, double* __restrict__ cdf) {
-  __shared__ double part[1024];
-  const uint64_t per = (dim + 1023) / 1024;
-  const uint64_t b = threadIdx.x * per, e = (b + per < dim) ? b + per : dim;
-  double s = 0.0;
-  for (uint64_t x = b; x < e; ++x) s += p[x];
-  part[threadIdx.x] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double run = 0.0;
-    for (int i = 0; i < 1024; ++i) {
-      const double v = part[i];
-      part[i] = run;
-      run += v;
-    }
-  }
-  __syncthreads();
-  double run = part[threadIdx.x];
-  for (uint64_t x = b; x < e; ++x) {
-    run += p[x];
-    cdf[x] = run;
-  }
-}
-
-// Shot i draws u = top 53 bits of SplitMix64((seed << 40) + i) in [0, 1) and returns the
-// smallest x with cdf[x] > u * cdf[dim - 1].
-__global__ void sample_kernel(const double* __restrict__ cdf, uint64_t dim, uint64_t shots, uint64_t seed,
-                              uint64_t* __restrict__ out) {
-  const double total = cdf[dim - 1];
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < shots; i += (uint64_t)gridDim.x * blockDim.x) {
-    const double u = (double)(splitmix64((seed << 40) + i) >> 11) * 0x1.0p-53 * total;
-    uint64_t lo = 0, hi = dim - 1;
-    while (lo < hi) {
-      const uint64_t mid = (lo + hi) >> 1;
-      if (cdf[mid] > u) hi = mid;
-      else lo = mid + 1;
-    }
-    out[i] = lo;
   }
 }
 
@@ -651,64 +489,9 @@ void launch_init_basis(void* rho, int n, tanq_prec p, uint64_t idx, hipStream_t 
   TANQ_HIP(hipGetLastError());
 }
 
-void launch_reduced(const void* rho, int n, tanq_prec p, int k, const int* keep_dev, double* out_dev, hipStream_t s) {
-  const unsigned nb = 1u << (2 * k);
-  if (p == TANQ_F64)
-    hipLaunchKernelGGL(reduced_kernel<double>, dim3(nb), dim3(RED_THREADS), 0, s, (const double*)rho, n, k, keep_dev,
-                       out_dev);
-  else
-    hipLaunchKernelGGL(reduced_kernel<float>, dim3(nb), dim3(RED_THREADS), 0, s, (const float*)rho, n, k, keep_dev,
-                       out_dev);
-  TANQ_HIP(hipGetLastError());
-}
-
-void launch_readout(double* probs_dev, int n, const double* p01, const double* p10, hipStream_t s) {
-  const uint64_t dim = 1ull << n;
-  uint64_t blocks = (dim / 2 + 255) / 256;
-  if (blocks > 1024) blocks = 1024;
-  if (blocks < 1) blocks = 1;
-  for (int t = 0; t < n; ++t) {
-    hipLaunchKernelGGL(readout_kernel, dim3((unsigned)blocks), dim3(256), 0, s, probs_dev, dim, t, p01[t], p10[t]);
-    TANQ_HIP(hipGetLastError());
-  }
-}
-
-void launch_sample(const double* probs_dev, int n, double* cdf_dev, uint64_t shots, uint64_t seed, uint64_t* out_dev,
-                   hipStream_t s) {
-  const uint64_t dim = 1ull << n;
-  hipLaunchKernelGGL(cdf_kernel, dim3(1), dim3(1024), 0, s, probs_dev, dim, cdf_dev);
-  TANQ_HIP(hipGetLastError());
-  uint64_t blocks = (shots + 255) / 256;
-  if (blocks > 4096) blocks = 4096;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(sample_kernel, dim3((unsigned)blocks), dim3(256), 0, s, cdf_dev, dim, shots, seed, out_dev);
-  TANQ_HIP(hipGetLastError());
-}
-
-int reduce_partials() { return RED_BLOCKS * 2 * 64; }
-
 static int red_blocks(uint64_t dim) {
   uint64_t b = (dim + RED_THREADS - 1) / RED_THREADS;
   return (int)(b < (uint64_t)RED_BLOCKS ? b : (uint64_t)RED_BLOCKS);
-}
-
-void launch_diag(const void* rho, int n, tanq_prec p, double* probs_dev, double* partials, double* result_dev,
-                 int renormalize, hipStream_t s) {
-  const uint64_t dim = 1ull << n;
-  const int nb = red_blocks(dim);
-  if (p == TANQ_F64)
-    hipLaunchKernelGGL(diag_kernel<double>, dim3(nb), dim3(RED_THREADS), 0, s, (const double*)rho, n, probs_dev,
-                       partials);
-  else
-    hipLaunchKernelGGL(diag_kernel<float>, dim3(nb), dim3(RED_THREADS), 0, s, (const float*)rho, n, probs_dev,
-                       partials);
-  TANQ_HIP(hipGetLastError());
-  hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(64), 0, s, partials, nb, 1, result_dev);
-  TANQ_HIP(hipGetLastError());
-  if (renormalize) {
-    hipLaunchKernelGGL(renormalize_kernel, dim3(nb), dim3(RED_THREADS), 0, s, probs_dev, dim, result_dev);
-    TANQ_HIP(hipGetLastError());
-  }
 }
 
 template <typename TA, typename TB>
@@ -726,25 +509,6 @@ void launch_compare(const void* a, tanq_prec pa, const void* b, tanq_prec pb, ui
   else compare_typed<float, float>(a, b, nel, nb, partials, s);
   TANQ_HIP(hipGetLastError());
   hipLaunchKernelGGL(compare_finish_kernel, dim3(1), dim3(64), 0, s, partials, nb, result_dev);
-  TANQ_HIP(hipGetLastError());
-}
-
-void launch_pauli(const void* rho, int n, tanq_prec p, int count, const uint64_t* masks_dev, double* partials,
-                  double* result_dev, hipStream_t s) {
-  const uint64_t dim = 1ull << n;
-  int nb = red_blocks(dim);
-  // partials holds 2 * count * nb doubles
-  const int maxnb = reduce_partials() / (2 * count);
-  if (nb > maxnb) nb = maxnb < 1 ? 1 : maxnb;
-  if (p == TANQ_F64)
-    hipLaunchKernelGGL(pauli_kernel<double>, dim3(nb, count), dim3(RED_THREADS), 0, s, (const double*)rho, n,
-                       masks_dev, partials);
-  else
-    hipLaunchKernelGGL(pauli_kernel<float>, dim3(nb, count), dim3(RED_THREADS), 0, s, (const float*)rho, n,
-                       masks_dev, partials);
-  TANQ_HIP(hipGetLastError());
-  hipLaunchKernelGGL(sum_partials_kernel, dim3((2 * count + 63) / 64), dim3(64), 0, s, partials, nb, 2 * count,
-                     result_dev);
   TANQ_HIP(hipGetLastError());
 }
 

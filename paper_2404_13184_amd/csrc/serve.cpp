@@ -158,8 +158,6 @@ struct tanq_server_s {
   // shared reduction scratch (stream-ordered)
   double* probs_dev = nullptr;
   double* partials = nullptr;
-  double* result_dev = nullptr;
-  uint64_t* masks_dev = nullptr;
 
   // step work buffers (double-buffered), pinned and device, with one graph each
   size_t items_per_step = 0, chunks_per_step = 0, work_bytes = 0;
@@ -480,29 +478,20 @@ void tanq_server_s::run_iteration() {
       }
       unsigned char* rho = arena_base + r->rho_off;
       double* hres = (double*)(pinned_base + r->res_off);
-      if (p == TANQ_F64) {  // one kernel, straight into the pinned result region
-        const size_t np = r->paulis.size(), nprob = r->want_probs ? (size_t)1 << r->n : 0;
-        uint64_t* masks = (uint64_t*)(hres + 1 + nprob + 2 * np);
-        if (np) std::memcpy(masks, r->paulis.data(), 3 * np * sizeof(uint64_t));
+      // the kernels write into the pinned result region and read the strings' masks from it
+      const size_t np = r->paulis.size(), nprob = r->want_probs ? (size_t)1 << r->n : 0;
+      uint64_t* masks = (uint64_t*)(hres + 1 + nprob + 2 * np);
+      if (np) std::memcpy(masks, r->paulis.data(), 3 * np * sizeof(uint64_t));
+      if (p == TANQ_F64) {
         // every block has the server's width, so the operands lie at equal distances
         const int nblk = (int)r->pack_off.size();
         const size_t stride = align256(packed_bytes(cfg.width, p));
         launch_real_outputs(rho, r->n, p, r->want_probs, (int)np, masks, nblk ? arena_base + r->pack_off[0] : nullptr,
                             cfg.width, stride, nblk, hres, stream);
-        continue;
-      }
-      launch_diag(rho, r->n, p, probs_dev, partials, result_dev, 1, stream);
-      TANQ_HIP(hipMemcpyAsync(hres, result_dev, sizeof(double), hipMemcpyDeviceToHost, stream));
-      if (r->want_probs)
-        TANQ_HIP(hipMemcpyAsync(hres + 1, probs_dev, ((size_t)1 << r->n) * sizeof(double), hipMemcpyDeviceToHost,
-                                stream));
-      if (!r->paulis.empty()) {
-        const int cnt = (int)r->paulis.size();
-        TANQ_HIP(hipMemcpyAsync(masks_dev, r->paulis.data(), 3 * cnt * sizeof(uint64_t), hipMemcpyHostToDevice,
-                                stream));
-        launch_pauli(rho, r->n, p, cnt, masks_dev, partials, result_dev, stream);
-        const size_t off = 1 + (r->want_probs ? ((size_t)1 << r->n) : 0);
-        TANQ_HIP(hipMemcpyAsync(hres + off, result_dev, 2 * cnt * sizeof(double), hipMemcpyDeviceToHost, stream));
+      } else {
+        launch_probs(rho, r->n, p, 1, nullptr, nullptr, probs_dev, partials, r->want_probs ? hres + 1 : nullptr, hres,
+                     stream);
+        if (np) launch_pauli(rho, r->n, p, (int)np, masks, partials, hres + 1 + nprob, stream);
       }
     }
     hipEvent_t ev = get_event();
@@ -615,7 +604,7 @@ void tanq_server_s::loop() {
       bool deferred = false;  // a request went back to the queue for lack of memory
       for (ServeRequest* r : to_admit) {
         size_t roff = 0;
-        // trace, probabilities, (Re, Im) per string, and (FP64) the strings' masks for the kernel
+        // trace, probabilities, (Re, Im) per string, and the strings' masks for the kernel
         r->res_size = (1 + (r->want_probs ? ((size_t)1 << r->n) : 0) + 5 * r->paulis.size()) * sizeof(double);
         bool ok = pinned.alloc(r->res_size, &roff);
         r->res_off = roff;
@@ -725,8 +714,6 @@ void destroy_server(tanq_server_s* s) {
   if (s->pinned_base) (void)hipHostFree(s->pinned_base);
   if (s->probs_dev) (void)hipFree(s->probs_dev);
   if (s->partials) (void)hipFree(s->partials);
-  if (s->result_dev) (void)hipFree(s->result_dev);
-  if (s->masks_dev) (void)hipFree(s->masks_dev);
   if (s->stream) (void)hipStreamDestroy(s->stream);
   if (s->adm_stream) (void)hipStreamDestroy(s->adm_stream);
   delete s;
@@ -766,8 +753,6 @@ tanq_status tanq_server_create(const tanq_server_config* cfg, tanq_server* out) 
       s->pinned.init(pinned_size);
       TANQ_HIP(hipMalloc((void**)&s->probs_dev, ((size_t)1 << kServeMaxN) * sizeof(double)));
       TANQ_HIP(hipMalloc((void**)&s->partials, (size_t)reduce_partials() * sizeof(double)));
-      TANQ_HIP(hipMalloc((void**)&s->result_dev, 4096 * sizeof(double)));
-      TANQ_HIP(hipMalloc((void**)&s->masks_dev, 3 * 1024 * sizeof(uint64_t)));
       // chunk capacity: every slot at most kChunksPerItem chunks
       s->items_per_step = (size_t)c.max_slots;
       s->chunks_per_step = (size_t)c.max_slots * kChunksPerItem;
