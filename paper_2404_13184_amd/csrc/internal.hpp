@@ -75,10 +75,9 @@ struct PassGeom {
   int32_t m;                     // superoperators in the pass
   int32_t pad;
   uint32_t op_off[kPassMax];     // element offset of superoperator j's packed operand
-  uint32_t free_mask[kPassMax];  // tile bits that index superoperator j's groups
   uint32_t stj[kPassMax][16];    // S(tile-local index of local index l) of superoperator j
-  uint8_t xcol[16];              // swizzle column of each tile bit (0 inside the window)
-  uint8_t vpos[16];              // tile bit b -> global bit vpos[b] (ascending)
+  uint64_t goff[13];             // global offset of tile element S(2^b)
+  uint16_t fb[kPassMax][10];     // S(tile bit) of superoperator j's group index bits
   uint8_t run_src[16];           // runs of fixed bits (up to 13 around 12 target bits)
   uint8_t run_len[16];
   uint8_t run_dst[16];

@@ -29,6 +29,13 @@
 // superoperator ahead.  FP64 (apply_pass_kernel): eight waves that all multiply and each issue
 // their share of the loads; two waves per SIMD leave enough registers to hold the operands of
 // all (at most four) superoperators for the whole kernel.
+//
+// Start-up.  A workgroup has only two tiles at 11 qubits in FP32, so what comes before the first product counts.
+// Swizzle and bit deposit are linear over GF(2), so every offset is formed from the images of single bits
+// (scalar registers) rather than by walking bit tables per element, the operand loads are all
+// issued before the first is waited for, and in FP32 the consumers fill the tables while the
+// producers' loads of the first tile are under way: 38.9 -> 34.1 us a pass (mostly four to six
+// superoperators, 22 us of matrix work).
 #include <algorithm>
 
 #include "real.hpp"
@@ -36,22 +43,6 @@
 namespace tanq {
 
 namespace {
-
-template <typename T>
-struct PassWin;
-template <>
-struct PassWin<double> { static constexpr int W = 4; };
-template <>
-struct PassWin<float> { static constexpr int W = 5; };
-
-template <typename T>
-__device__ inline uint32_t pass_swz(uint32_t e, const PassGeom& g) {
-  uint32_t x = e;
-#pragma unroll
-  for (int b = PassWin<T>::W; b < 16; ++b)
-    if ((e >> b) & 1u) x ^= g.xcol[b];
-  return x;
-}
 
 __device__ inline uint64_t pass_tile_base(const PassGeom& g, uint64_t tile) {
   uint64_t b = 0;
@@ -84,14 +75,15 @@ struct PassMax<double> { static constexpr int M = kPassMaxF64; };
 template <>
 struct PassMax<float> { static constexpr int M = kPassMaxF32; };
 
-// Global offset of tile element e0 = S(first element of LDS slot p); the slot's EPS elements are
-// consecutive in the tile and in vec(rho) (tile bit 0 is global bit 0, and this swizzle never
-// flips bit 0 for FP32, so a slot's pair keeps its order).
-template <typename T, int VMAX>
-__device__ inline uint64_t pass_slot_off(uint32_t first, const PassGeom& g) {
-  const uint32_t e = pass_swz<T>(first, g);
+// Global offset of tile element S(e), e the first element of an LDS slot (the slot's elements are consecutive in
+// the tile and in vec(rho): tile bit 0 is global bit 0, and the FP32 swizzle never flips bit 0), over the
+// slot index bits [LO, HI), which x holds.
+template <typename T, int LO, int HI>
+__device__ inline uint64_t pass_slot_off(uint32_t x, const PassGeom& g) {
+  constexpr int EB = sizeof(T) == 8 ? 0 : 1;  // element bits inside a slot
   uint64_t o = 0;
-  for (int b = 0; b < VMAX; ++b) o |= (uint64_t)((e >> b) & 1u) << g.vpos[b];
+#pragma unroll
+  for (int b = LO; b < HI; ++b) o ^= ((x >> b) & 1u) ? g.goff[b + EB] : 0ull;
   return o;
 }
 
@@ -109,6 +101,38 @@ __device__ inline T pass_op3m(const T* __restrict__ rb, int r) {
   auto at = [&](int R, int C) { return rb[((R / 16) * 8 + C / 4) * 64 + (C % 4) * 16 + R % 16]; };
   const T sr = at(2 * a, 2 * b), si = at(2 * a + 1, 2 * b);
   return t == 0 ? sr : (t == 1 ? si : sr + si);
+}
+
+// The operands, row offsets and group offsets of a pass in LDS, by NT threads; every load is issued before the
+// first is waited for.
+template <typename T, int VMAX, int NT, int MMAX>
+__device__ inline void pass_setup(const T* __restrict__ frags, const PassGeom& g, T (*opl)[kOp3M], uint32_t (*stl)[20],
+                                  uint16_t (*gxt)[1 << (VMAX - 4)], int tid) {
+  constexpr int G = 1 << (VMAX - 4), N = (MMAX * kOp3M + NT - 1) / NT;
+  static_assert(G <= NT && MMAX * 20 <= NT, "one element per thread");
+  T v[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int idx = i * NT + tid, j = idx / kOp3M;
+    v[i] = j < g.m ? pass_op3m<T>(frags + g.op_off[j < kPassMax ? j : 0], idx % kOp3M) : T(0);
+  }
+  const int sj = tid / 20, sl = tid % 20;
+  const uint32_t st = sj < g.m ? g.stj[sj][sl < 16 ? sl : 4 * (sl - 16)] : 0u;
+  if (tid < G) {
+#pragma unroll
+    for (int j = 0; j < MMAX; ++j) {
+      uint32_t x = 0;
+#pragma unroll
+      for (int b = 0; b < VMAX - 4; ++b) x ^= ((tid >> b) & 1) ? (uint32_t)g.fb[j][b] : 0u;
+      gxt[j][tid] = (uint16_t)x;
+    }
+  }
+  if (sj < g.m) stl[sj][sl] = st;
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int idx = i * NT + tid;
+    if (idx < g.m * kOp3M) opl[idx / kOp3M][idx % kOp3M] = v[i];
+  }
 }
 
 // One superoperator of a pass on the tile in ldsC, by consumer wave cw of NCW, in 3M form:
@@ -245,29 +269,21 @@ __global__ __launch_bounds__(NT) void apply_pass_ws_kernel(T* __restrict__ rho, 
   const PassTiles range = pass_tiles(g.ntiles);
   uint64_t tile = range.first;
   if (tile >= range.end) return;  // uniform per workgroup
-  for (int idx = tid; idx < g.m * kOp3M; idx += NT)
-    opl[idx / kOp3M][idx % kOp3M] = pass_op3m<T>(frags + g.op_off[idx / kOp3M], idx % kOp3M);
-  if (tid < CITERS) soff[tid] = pass_slot_off<T, VMAX>((uint32_t)(tid * CT * EPS), g);
-  for (int idx = tid; idx < g.m * 20; idx += NT) {
-    const int j = idx / 20, l = idx % 20;
-    stl[j][l] = g.stj[j][l < 16 ? l : 4 * (l - 16)];
-  }
-  for (int idx = tid; idx < g.m * G; idx += NT) {
-    const int j = idx / G, gi = idx % G;
-    gxt[j][gi] = (uint16_t)pass_swz<T>(pdep32((uint32_t)gi, g.free_mask[j]), g);
-  }
-  lds_barrier();  // operands and table in place before the roles split
+  constexpr int SB = VMAX - (EPS == 2 ? 1 : 0);                  // slot index bits
+  constexpr int PB = __builtin_ctz(PT), CB = __builtin_ctz(CT);  // of a producer's and a consumer's thread part
 
   if (wave < NPW) {
     // ---------------- producer ----------------
     uint64_t off[PITERS];
+    const uint64_t off_t = pass_slot_off<T, 0, PB>((uint32_t)tid, g);
 #pragma unroll
-    for (int it = 0; it < PITERS; ++it) off[it] = pass_slot_off<T, VMAX>((uint32_t)((it * PT + tid) * EPS), g);
+    for (int it = 0; it < PITERS; ++it) off[it] = off_t ^ pass_slot_off<T, PB, SB>((uint32_t)it << PB, g);
     {
       const uint64_t base = pass_tile_base(g, tile);
       if (tid == 0) tbase[0] = base;
       pass_dma_tile<T, PITERS, PT>(rho, base, off, ldsA, wave);
     }
+    raw_barrier();  // the consumers' tables, which they write while the first tile is on its way
     vm_wait<0>();
     raw_barrier();  // B0: first tile ready
     for (int t = 0;; ++t) {
@@ -294,7 +310,10 @@ __global__ __launch_bounds__(NT) void apply_pass_ws_kernel(T* __restrict__ rho, 
     // global offset of the slots this thread stores: the slot index it * CT + ct splits into
     // disjoint bit fields and the offset is linear in them over GF(2) (swizzle and bit deposit
     // are), so offset = offset(ct part) ^ offset(it part), the latter the same for every thread
-    const uint64_t off_ct = pass_slot_off<T, VMAX>((uint32_t)(ct * EPS), g);
+    const uint64_t off_ct = pass_slot_off<T, 0, CB>((uint32_t)ct, g);
+    pass_setup<T, VMAX, CT, MMAX>(frags, g, opl, stl, gxt, ct);
+    if (ct < CITERS) soff[ct] = pass_slot_off<T, CB, SB>((uint32_t)ct << CB, g);
+    lds_barrier();  // operands and tables in place
     // two operand sets: superoperator j multiplies with ops[j & 1] while ops[(j + 1) & 1] is
     // filled for j + 1 (for superoperator 0 of the next tile after the last one)
     Ops ops[2];
@@ -412,7 +431,6 @@ __global__ __launch_bounds__(NT) void apply_pass_kernel(T* __restrict__ rho, con
   __shared__ T opl[MMAX][kOp3M];
   __shared__ uint16_t gxt[MMAX][G];
   __shared__ __align__(16) uint32_t stl[MMAX][20];
-  __shared__ uint64_t soff[ITERS];
 
   if (skip_launch(flag)) {
     static_assert(sizeof(T) == 8 && NT == kRealPassThreads && SLOTS == 4096, "shapes of the real-form pass");
@@ -427,17 +445,7 @@ __global__ __launch_bounds__(NT) void apply_pass_kernel(T* __restrict__ rho, con
   const PassTiles range = pass_tiles(g.ntiles);
   uint64_t tile = range.first;
   if (tile >= range.end) return;  // uniform per workgroup
-  for (int idx = tid; idx < g.m * kOp3M; idx += NT)
-    opl[idx / kOp3M][idx % kOp3M] = pass_op3m<T>(frags + g.op_off[idx / kOp3M], idx % kOp3M);
-  if (tid < ITERS) soff[tid] = pass_slot_off<T, VMAX>((uint32_t)(tid * NT * EPS), g);
-  for (int idx = tid; idx < g.m * 20; idx += NT) {
-    const int j = idx / 20, l = idx % 20;
-    stl[j][l] = g.stj[j][l < 16 ? l : 4 * (l - 16)];
-  }
-  for (int idx = tid; idx < g.m * G; idx += NT) {
-    const int j = idx / G, gi = idx % G;
-    gxt[j][gi] = (uint16_t)pass_swz<T>(pdep32((uint32_t)gi, g.free_mask[j]), g);
-  }
+  pass_setup<T, VMAX, NT, MMAX>(frags, g, opl, stl, gxt, tid);
   lds_barrier();
 
   static_assert(MMAX <= 4, "every superoperator's operands fit in registers");
@@ -448,9 +456,10 @@ __global__ __launch_bounds__(NT) void apply_pass_kernel(T* __restrict__ rho, con
   // global offset of slot it * NT + tid (linear over GF(2) in the slot index)
   uint64_t off[ITERS];
   {
-    const uint64_t off_t = pass_slot_off<T, VMAX>((uint32_t)(tid * EPS), g);
+    constexpr int SB = VMAX - (EPS == 2 ? 1 : 0), TB = __builtin_ctz(NT);
+    const uint64_t off_t = pass_slot_off<T, 0, TB>((uint32_t)tid, g);
 #pragma unroll
-    for (int it = 0; it < ITERS; ++it) off[it] = off_t ^ soff[it];
+    for (int it = 0; it < ITERS; ++it) off[it] = off_t ^ pass_slot_off<T, TB, SB>((uint32_t)it << TB, g);
   }
   // The run table deposits the tile index into the global bits outside the tile, lowest first,
   // so the base of the next tile follows from the current one by an increment under that mask

@@ -143,20 +143,21 @@ PassGeom make_pass_geom(int n, int m, const int* qubits, const uint32_t* op_off,
     }
   int cnt = 0;
   int local_of[64];
+  int vpos[16];  // tile bit -> global bit (ascending)
   for (int b = 0; b < nb; ++b) {
     local_of[b] = -1;
     if ((vmask >> b) & 1ull) {
       local_of[b] = cnt;
-      g.vpos[cnt++] = (uint8_t)b;
+      vpos[cnt++] = b;
     }
   }
   if (cnt != V) fail(TANQ_E_STATE, "pass tile bit count");
   // FP32 moves two elements per 16-byte slot: global bit 0 must be tile bit 0
-  if (p != TANQ_F64 && g.vpos[0] != 0) fail(TANQ_E_STATE, "pass tile without global bit 0");
+  if (p != TANQ_F64 && vpos[0] != 0) fail(TANQ_E_STATE, "pass tile without global bit 0");
   g.V = V;
   g.m = m;
 
-  uint32_t tj[kPassMax][16];
+  uint32_t tj[kPassMax][16], free_mask[kPassMax];
   SwzProblem P{};
   P.W = (p == TANQ_F64) ? 4 : 5;
   P.V = V;
@@ -176,11 +177,11 @@ PassGeom make_pass_geom(int n, int m, const int* qubits, const uint32_t* op_off,
         if ((l >> t) & 1) r |= 1u << tpos[t];
       tj[j][l] = r;
     }
-    g.free_mask[j] = ((1u << V) - 1u) & ~tmask;
+    free_mask[j] = ((1u << V) - 1u) & ~tmask;
     g.op_off[j] = op_off[j];
     int q = 0;
     for (int b = 0; b < V && q < 4; ++b)
-      if ((g.free_mask[j] >> b) & 1u) P.fbits[j][q++] = (uint32_t)b;
+      if ((free_mask[j] >> b) & 1u) P.fbits[j][q++] = (uint32_t)b;
     P.t1[j] = tj[j][1];  // FP32 operand reads: lanes 0-31 cover rows 0 and 1
     P.t2[j] = tj[j][4];  // FP32 result writes: lanes 0-31 cover rows 0-3 and 4-7
   }
@@ -207,22 +208,32 @@ PassGeom make_pass_geom(int n, int m, const int* qubits, const uint32_t* op_off,
       std::memcpy(best, cand, sizeof(best));
     }
   }
-  std::memcpy(g.xcol, best, sizeof(best));
   if (conflict_free) *conflict_free = best_score;
   if (achievable) *achievable = perfect;
   auto S = [&](uint32_t e) {
     uint32_t x = e;
     for (int b = P.W; b < 16; ++b)
-      if ((e >> b) & 1u) x ^= g.xcol[b];
+      if ((e >> b) & 1u) x ^= best[b];
     return x;
   };
-  for (int j = 0; j < m; ++j)
+  // S and the deposit of a tile element into the state's index bits are linear over GF(2): the kernels form
+  // any offset from the images of single bits
+  for (int b = 0; b < V; ++b) {
+    const uint32_t e = S(1u << b);
+    for (int t = 0; t < V; ++t)
+      if ((e >> t) & 1u) g.goff[b] |= 1ull << vpos[t];
+  }
+  for (int j = 0; j < m; ++j) {
     for (int l = 0; l < 16; ++l) g.stj[j][l] = S(tj[j][l]);
+    int f = 0;
+    for (int b = 0; b < V; ++b)
+      if ((free_mask[j] >> b) & 1u) g.fb[j][f++] = (uint16_t)S(1u << b);
+  }
   // S(e) = e ^ X(e) with X linear in the bits above the window and valued inside it, so S is an
   // involution of [0, 2^V) exactly when every column lies inside the window (and, in FP32, never
   // flips bit 0, which keeps slot pairs whole and in order); columns of bits >= V are unused
   for (int b = 0; b < 16; ++b)
-    if ((b < P.W && g.xcol[b]) || (g.xcol[b] >> P.W) || (b >= V && g.xcol[b]) || (p != TANQ_F64 && (g.xcol[b] & 1u)))
+    if ((b < P.W && best[b]) || (best[b] >> P.W) || (b >= V && best[b]) || (p != TANQ_F64 && (best[b] & 1u)))
       fail(TANQ_E_STATE, "pass swizzle column outside the bank window");
 
   // runs of fixed bits: the maximal runs of global bits outside the tile, lowest first, each
