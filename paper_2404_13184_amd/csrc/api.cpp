@@ -7,7 +7,6 @@
 #include <mutex>
 #include <algorithm>
 #include <cstring>
-#include <deque>
 #include <map>
 #include <memory>
 #include <string>
@@ -110,13 +109,14 @@ struct tanq_fused_s {
   int source_ops = 0;
   int count_k[4] = {0, 0, 0, 0};
   std::vector<FusedBlockHost> blocks;
+  unsigned char* mem = nullptr;  // the one device allocation; what follows points into it
   double* raw = nullptr;
   unsigned char* packed = nullptr;
   // real operands for long lists on Hermitian FP64 states (herm.hip), if it is long enough for
   // them; block b's at rpacked + rpack_off[b], the defect table after the last
   double* rpacked = nullptr;
   std::vector<size_t> rpack_off;
-  double* defects = nullptr;  // inside rpacked
+  double* defects = nullptr;
   // pass geometries already built, by (first block, length)
   std::mutex pass_mu;
   std::map<std::pair<int, int>, tanq::PassGeom> passes;
@@ -201,14 +201,10 @@ inline int pass_low_run(uint64_t qmask, int n, int V) {
   uint64_t held = qmask | (qmask << n);
   int fill = V - __builtin_popcountll(held);
   if (fill < 0) return -1;
-  for (int b = 0; b < 2 * n && fill > 0; ++b)
-    if (!((held >> b) & 1ull)) {
-      held |= 1ull << b;
-      --fill;
-    }
-  int c = 0;
-  while (c < 2 * n && ((held >> c) & 1ull)) ++c;
-  return c;
+  // the first bit that is neither held nor one of the `fill` lowest others
+  uint64_t others = ~held;
+  for (; fill > 0; --fill) others &= others - 1;
+  return std::min(__builtin_ctzll(others), 2 * n);
 }
 
 // Length of the pass that starts at block i (blocks before `end`): the longest run of
@@ -312,78 +308,89 @@ int real_run(BlockAt at, int i, int end, int n, int lim) {
 // qubits (the identity on a qubit the pass already holds), since a pass applies 2-qubit
 // superoperators.  Reordering commuting superoperators leaves the product unchanged.  Returns
 // the list unchanged where passes do not apply.
-std::vector<PlanBlock> pass_order(const std::vector<PlanBlock>& pl, int n, tanq_prec p, int lim) {
+std::vector<PlanBlock> pass_order(std::vector<PlanBlock> pl, int n, tanq_prec p, int lim) {
   const int V = pass_tile_bits(p);
   const int min_run = p == TANQ_F64 ? 3 : 4;
-  constexpr size_t kWindow = 16;
+  constexpr int kWindow = 16;
   lim = std::min(lim, pass_max(p));
   if (lim < 2 || 2 * n - V < kPassMinTileBits) return pl;
-  auto qmask = [&](int b) {
-    uint64_t m = 0;
-    for (int q : pl[b].qubits) m |= 1ull << q;
-    return m;
+  struct Item {
+    int block;
+    bool narrow;  // one or two qubits
+    uint64_t qubits;
   };
-  // blocks not yet placed; taken blocks lie within the window at the front, where a deque
-  // erases in constant time
-  std::deque<int> rem(pl.size());
-  for (size_t i = 0; i < rem.size(); ++i) rem[i] = (int)i;
-  auto fits = [&](int b, uint64_t U, uint64_t blocked) {
-    const uint64_t qb = qmask(b);
-    return pl[b].qubits.size() <= 2 && !(qb & blocked) && pass_low_run(U | qb, n, V) >= min_run;
-  };
-  // scan positions after `from`, starting from pass qubits U, taken positions `take` and
-  // blocked qubits; returns the taken positions (increasing) and their qubit union
-  auto scan = [&](size_t from, uint64_t U, uint64_t blocked, std::vector<size_t> take, uint64_t* Uout) {
-    const size_t end = std::min(rem.size(), kWindow);
-    for (size_t pos = from; pos < end && (int)take.size() < lim; ++pos) {
-      const int b = rem[pos];
-      if (fits(b, U, blocked)) {
-        take.push_back(pos);
-        U |= qmask(b);
-      } else {
-        blocked |= qmask(b);
-      }
+  // the first blocks not yet placed, in order; `next` is the first one not in it
+  Item win[kWindow];
+  int count = 0, next = 0;
+  auto refill = [&] {
+    for (; count < kWindow && next < (int)pl.size(); ++next, ++count) {
+      uint64_t m = 0;
+      for (int q : pl[next].qubits) m |= 1ull << q;
+      win[count] = {next, pl[next].qubits.size() <= 2, m};
     }
-    *Uout = U;
-    return take;
+  };
+  auto fits = [&](const Item& b, uint64_t U, uint64_t blocked) {
+    return b.narrow && !(b.qubits & blocked) && pass_low_run(U | b.qubits, n, V) >= min_run;
+  };
+  // positions of the window taken for a pass (increasing) and the union of their qubits
+  struct Take {
+    int m = 0;
+    uint64_t U = 0;
+    int pos[kPassMax];
+    void add(int at, uint64_t qubits) {
+      pos[m++] = at;
+      U |= qubits;
+    }
+  };
+  // adds the fitting positions after `from`
+  auto scan = [&](int from, uint64_t blocked, Take t) {
+    for (int pos = from; pos < count && t.m < lim; ++pos) {
+      if (fits(win[pos], t.U, blocked))
+        t.add(pos, win[pos].qubits);
+      else
+        blocked |= win[pos].qubits;
+    }
+    return t;
   };
   std::vector<PlanBlock> out;
   out.reserve(pl.size());
-  while (!rem.empty()) {
-    const int b0 = rem[0];
-    std::vector<size_t> take(1, 0);
-    uint64_t U = qmask(b0);
-    if (pl[b0].qubits.size() <= 2) {
-      uint64_t Ub = 0;
-      take = scan(1, U, 0, take, &Ub);
-      U = Ub;
+  for (refill(); count > 0; refill()) {
+    Take head;
+    head.add(0, win[0].qubits);
+    Take take = head;
+    if (win[0].narrow) {
+      take = scan(1, 0, head);
       // the same scan with each fitting block forced as the second member
       uint64_t blocked = 0;
-      for (size_t pos = 1; pos < std::min(rem.size(), kWindow) && lim >= 3; ++pos) {
-        const int b = rem[pos];
-        if (fits(b, qmask(b0), blocked)) {
-          uint64_t Uf = 0;
-          std::vector<size_t> t = scan(pos + 1, qmask(b0) | qmask(b), blocked, std::vector<size_t>{0, pos}, &Uf);
-          if (t.size() > take.size()) {
-            take = std::move(t);
-            U = Uf;
-          }
+      for (int pos = 1; pos < count && lim >= 3; ++pos) {
+        if (fits(win[pos], head.U, blocked)) {
+          Take t = head;
+          t.add(pos, win[pos].qubits);
+          t = scan(pos + 1, blocked, t);
+          if (t.m > take.m) take = t;
         }
-        blocked |= qmask(b);
+        blocked |= win[pos].qubits;
       }
     }
-    const bool pass = take.size() >= 2 && __builtin_popcountll(U) >= 2;
-    for (size_t t : take) {
-      PlanBlock b = pl[rem[t]];
+    const bool pass = take.m >= 2 && __builtin_popcountll(take.U) >= 2;
+    for (int t = 0; t < take.m; ++t) {
+      PlanBlock b = std::move(pl[win[take.pos[t]].block]);
       if (pass && b.qubits.size() == 1) {
         const int q = b.qubits[0];
-        const uint64_t others = U & ~(1ull << q);
+        const uint64_t others = take.U & ~(1ull << q);
         b.qubits.push_back(__builtin_ctzll(others));
         std::sort(b.qubits.begin(), b.qubits.end());
       }
       out.push_back(std::move(b));
     }
-    for (auto it = take.rbegin(); it != take.rend(); ++it) rem.erase(rem.begin() + (ptrdiff_t)*it);
+    int keep = 0;
+    for (int pos = 0, t = 0; pos < count; ++pos) {
+      if (t < take.m && take.pos[t] == pos)
+        ++t;
+      else
+        win[keep++] = win[pos];
+    }
+    count = keep;
   }
   return out;
 }
@@ -769,70 +776,80 @@ tanq_status tanq_fuse(tanq_circuit c, int max_width, tanq_prec p, void* hip_stre
     for (int k = 0; k < 4; ++k) f->count_k[k] = L.count_k[k];
 
     if (!plan.empty()) {
-      FuseOpDev* d_ops = nullptr;
-      FuseBlockDev* d_blk = nullptr;
-      RealPackDev* d_rblk = nullptr;
-      double *d_kraus = nullptr, *d_sops = nullptr;
-      auto cleanup = [&] {
-        dfree(d_ops);
-        dfree(d_blk);
-        dfree(d_rblk);
-        dfree(d_kraus);
-        dfree(d_sops);
+      auto at = [&](int j, const int** q) {
+        *q = f->blocks[j].qubits;
+        return f->blocks[j].k;
       };
-      try {
-        TANQ_HIP(hipMalloc((void**)&d_ops, L.ops.size() * sizeof(FuseOpDev)));
-        TANQ_HIP(hipMalloc((void**)&d_blk, L.blocks.size() * sizeof(FuseBlockDev)));
-        TANQ_HIP(hipMalloc((void**)&d_kraus, L.kraus.size() * sizeof(double)));
-        TANQ_HIP(hipMalloc((void**)&d_sops, L.sop_elems * 2 * sizeof(double)));
-        TANQ_HIP(hipMalloc((void**)&f->raw, L.raw_elems * 2 * sizeof(double)));
-        TANQ_HIP(hipMalloc((void**)&f->packed, L.pack_bytes));
-        TANQ_HIP(hipMemcpyAsync(d_ops, L.ops.data(), L.ops.size() * sizeof(FuseOpDev), hipMemcpyHostToDevice, s));
-        TANQ_HIP(hipMemcpyAsync(d_blk, L.blocks.data(), L.blocks.size() * sizeof(FuseBlockDev), hipMemcpyHostToDevice, s));
-        TANQ_HIP(hipMemcpyAsync(d_kraus, L.kraus.data(), L.kraus.size() * sizeof(double), hipMemcpyHostToDevice, s));
-        run_fuse_kernels(L, d_ops, d_blk, d_kraus, d_sops, f->raw, f->packed, p, s);
-        auto at = [&](int j, const int** q) {
-          *q = f->blocks[j].qubits;
-          return f->blocks[j].k;
-        };
-        const int nblk = (int)f->blocks.size();
-        if (herm_list(count_launches(at, 0, nblk, n, p, pass_limit()), n, p, pass_limit())) {
-          std::vector<RealPackDev> rb(nblk);
-          size_t elems = 0;
-          for (int i = 0; i < nblk; ++i) {
-            const FusedBlockHost& b = f->blocks[i];
-            RealPackDev& r = rb[i];
-            r.k = b.k;
-            r.raw_off = (int64_t)b.raw_off;
-            r.pack_off = (int64_t)elems;
-            f->rpack_off.push_back(elems);
-            elems += real_pack_elems(b.k);
-            // local bits by ascending address: the top column bit first, then rows and columns
-            int pos[6];
-            for (int t = 0; t < b.k; ++t) {
-              pos[t] = b.qubits[t] + 1;
-              pos[b.k + t] = b.qubits[t] == n - 1 ? 0 : b.qubits[t] + n + 1;
-            }
-            for (int t = 0; t < 2 * b.k; ++t) r.perm[t] = (uint8_t)t;
-            std::sort(r.perm, r.perm + 2 * b.k, [&](uint8_t x, uint8_t y) { return pos[x] < pos[y]; });
+      const int nblk = (int)f->blocks.size();
+      std::vector<RealPackDev> rb;
+      size_t real_elems = 0;
+      if (herm_list(count_launches(at, 0, nblk, n, p, pass_limit()), n, p, pass_limit())) {
+        rb.resize(nblk);
+        for (int i = 0; i < nblk; ++i) {
+          const FusedBlockHost& b = f->blocks[i];
+          RealPackDev& r = rb[i];
+          r.k = b.k;
+          r.raw_off = (int64_t)b.raw_off;
+          r.pack_off = (int64_t)real_elems;
+          f->rpack_off.push_back(real_elems);
+          real_elems += real_pack_elems(b.k);
+          // local bits by ascending address: the top column bit first, then rows and columns
+          int pos[6];
+          for (int t = 0; t < b.k; ++t) {
+            pos[t] = b.qubits[t] + 1;
+            pos[b.k + t] = b.qubits[t] == n - 1 ? 0 : b.qubits[t] + n + 1;
           }
-          TANQ_HIP(hipMalloc((void**)&f->rpacked, (elems + (size_t)nblk + 1) * sizeof(double)));
-          f->defects = f->rpacked + elems;
-          TANQ_HIP(hipMalloc((void**)&d_rblk, rb.size() * sizeof(RealPackDev)));
-          TANQ_HIP(hipMemcpyAsync(d_rblk, rb.data(), rb.size() * sizeof(RealPackDev), hipMemcpyHostToDevice, s));
-          launch_pack_herm(d_rblk, nblk, f->raw, f->rpacked, f->defects, s);
-          TANQ_HIP(hipStreamSynchronize(s));  // rb is read by the copy
+          for (int t = 0; t < 2 * b.k; ++t) r.perm[t] = (uint8_t)t;
+          std::sort(r.perm, r.perm + 2 * b.k, [&](uint8_t x, uint8_t y) { return pos[x] < pos[y]; });
         }
-        TANQ_HIP(hipStreamSynchronize(s));
+      }
+      // One allocation for what the handle keeps, and one upload of the tables into the memory that only the
+      // kernels below need.  That memory shares the allocation where it is small: each further
+      // hipMalloc and hipFree pair costs about 10 us, and fusing a 6-qubit circuit of 180
+      // operations took 105 us with six pairs and three uploads.
+      const size_t raw_b = align256(L.raw_elems * 2 * sizeof(double));
+      const size_t real_b = rb.empty() ? 0 : align256((real_elems + (size_t)nblk + 1) * sizeof(double));
+      const size_t keep_b = raw_b + align256(L.pack_bytes) + real_b;
+      const size_t ops_b = align256(L.ops.size() * sizeof(FuseOpDev));
+      const size_t blk_b = align256(L.blocks.size() * sizeof(FuseBlockDev));
+      const size_t rblk_b = align256(rb.size() * sizeof(RealPackDev));
+      const size_t kraus_b = align256(L.kraus.size() * sizeof(double));
+      const size_t up_b = ops_b + blk_b + rblk_b + kraus_b;
+      const size_t tmp_b = up_b + L.sop_elems * 2 * sizeof(double);
+      constexpr size_t kShareMax = (size_t)16 << 20;
+      unsigned char* tmp = nullptr;
+      unsigned char* own_tmp = nullptr;
+      try {
+        TANQ_HIP(hipMalloc((void**)&f->mem, keep_b + (tmp_b <= kShareMax ? tmp_b : 0)));
+        if (tmp_b <= kShareMax) {
+          tmp = f->mem + keep_b;
+        } else {
+          TANQ_HIP(hipMalloc((void**)&own_tmp, tmp_b));
+          tmp = own_tmp;
+        }
+        f->raw = (double*)f->mem;
+        f->packed = f->mem + raw_b;
+        std::unique_ptr<unsigned char[]> up(new unsigned char[up_b]);
+        std::memcpy(up.get(), L.ops.data(), L.ops.size() * sizeof(FuseOpDev));
+        std::memcpy(up.get() + ops_b, L.blocks.data(), L.blocks.size() * sizeof(FuseBlockDev));
+        if (!rb.empty()) std::memcpy(up.get() + ops_b + blk_b, rb.data(), rb.size() * sizeof(RealPackDev));
+        std::memcpy(up.get() + ops_b + blk_b + rblk_b, L.kraus.data(), L.kraus.size() * sizeof(double));
+        TANQ_HIP(hipMemcpyAsync(tmp, up.get(), up_b, hipMemcpyHostToDevice, s));
+        run_fuse_kernels(L, (const FuseOpDev*)tmp, (const FuseBlockDev*)(tmp + ops_b),
+                         (const double*)(tmp + ops_b + blk_b + rblk_b), (double*)(tmp + up_b), f->raw, f->packed, p, s);
+        if (!rb.empty()) {
+          f->rpacked = (double*)(f->packed + align256(L.pack_bytes));
+          f->defects = f->rpacked + real_elems;
+          launch_pack_herm((const RealPackDev*)(tmp + ops_b + blk_b), nblk, f->raw, f->rpacked, f->defects, s);
+        }
+        TANQ_HIP(hipStreamSynchronize(s));  // `up` is read by the copy
       } catch (...) {
         (void)hipStreamSynchronize(s);
-        cleanup();
-        dfree(f->raw);
-        dfree(f->packed);
-        dfree(f->rpacked);
+        dfree(own_tmp);
+        dfree(f->mem);
         throw;
       }
-      cleanup();
+      dfree(own_tmp);
     }
     *out = f.release();
   });
@@ -881,9 +898,7 @@ tanq_status tanq_fused_free(tanq_fused f) {
     (void)hipSetDevice(f->device);
     // applies of f may still be queued on any stream of the device
     (void)hipDeviceSynchronize();
-    dfree(f->raw);
-    dfree(f->packed);
-    dfree(f->rpacked);
+    dfree(f->mem);
     delete f;
   });
 }

@@ -1,7 +1,6 @@
 #include "circuit.hpp"
 
 #include <algorithm>
-#include <map>
 #include <utility>
 
 namespace tanq {
@@ -25,9 +24,15 @@ void widen_plan(std::vector<PlanBlock>& plan, int n, int w) {
 
 FuseLayout make_fuse_layout(const std::vector<HostOp>& ops, const std::vector<PlanBlock>& plan, tanq_prec p) {
   FuseLayout L;
-  // identical Kraus sets (same pool and offset, e.g. a noise channel repeated through a
-  // circuit) are uploaded once; their superoperators are still built per operation
-  std::map<std::pair<const void*, size_t>, int64_t> seen;
+  // identical Kraus sets (same pool, offset and size, e.g. a noise channel repeated through a
+  // circuit) are uploaded once; their superoperators are still built per operation.  Open addressing:
+  // entry h holds an operation with that key (its index in L.ops is seen[h]), -1 is free.
+  size_t cap = 16;
+  while (cap < 2 * ops.size()) cap *= 2;
+  std::vector<int> seen(cap, -1), source(ops.size());  // source: operation of each entry of L.ops
+  L.ops.reserve(ops.size());
+  L.blocks.reserve(plan.size());
+  L.host.reserve(plan.size());
   for (const auto& pb : plan) {
     const int k = (int)pb.qubits.size();
     if (k > 3) fail(TANQ_E_UNSUPPORTED, "a block wider than 3 qubits");
@@ -50,13 +55,20 @@ FuseLayout make_fuse_layout(const std::vector<HostOp>& ops, const std::vector<Pl
       FuseOpDev od{};
       od.j = ho.j;
       od.m = ho.m;
-      const auto key = std::make_pair((const void*)ho.pool.get(), ho.koff);
-      auto it = seen.find(key);
-      if (it == seen.end()) {
-        it = seen.emplace(key, (int64_t)(L.kraus.size() / 2)).first;
-        L.kraus.insert(L.kraus.end(), ho.K(), ho.K() + ho.kdoubles());
+      size_t h = ((uintptr_t)ho.pool.get() / 16 + ho.koff * 0x9E3779B97F4A7C15ull) >> 7 & (cap - 1);
+      while (seen[h] >= 0) {
+        const HostOp& other = ops[source[seen[h]]];
+        if (other.pool == ho.pool && other.koff == ho.koff && other.kdoubles() == ho.kdoubles()) break;
+        h = (h + 1) & (cap - 1);
       }
-      od.kraus_off = it->second;
+      if (seen[h] < 0) {
+        seen[h] = (int)L.ops.size();
+        od.kraus_off = (int64_t)(L.kraus.size() / 2);
+        L.kraus.insert(L.kraus.end(), ho.K(), ho.K() + ho.kdoubles());
+      } else {
+        od.kraus_off = L.ops[seen[h]].kraus_off;
+      }
+      source[L.ops.size()] = oi;
       od.sop_off = (int64_t)L.sop_elems;
       for (int t = 0; t < ho.j; ++t) {
         int pos = -1;

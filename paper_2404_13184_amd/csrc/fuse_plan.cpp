@@ -24,12 +24,14 @@ std::vector<PlanBlock> plan_fusion(const std::vector<PlanOp>& ops, int n, int mo
           joined = true;
         }
       } else {
-        std::vector<int> u = B.qubits;
+        int add[3], na = 0;  // qubits the block would gain
         for (int t = 0; t < op.j; ++t)
-          if (std::find(u.begin(), u.end(), op.q[t]) == u.end()) u.push_back(op.q[t]);
-        if ((int)u.size() <= mode) {
-          std::sort(u.begin(), u.end());
-          B.qubits = u;
+          if (std::find(B.qubits.begin(), B.qubits.end(), op.q[t]) == B.qubits.end()) add[na++] = op.q[t];
+        if ((int)B.qubits.size() + na <= mode) {
+          if (na) {
+            B.qubits.insert(B.qubits.end(), add, add + na);
+            std::sort(B.qubits.begin(), B.qubits.end());
+          }
           B.ops.push_back(i);
           joined = true;
         }
@@ -37,6 +39,8 @@ std::vector<PlanBlock> plan_fusion(const std::vector<PlanOp>& ops, int n, int mo
     }
     if (!joined) {
       PlanBlock nb;
+      nb.qubits.reserve(3);
+      nb.ops.reserve(8);
       nb.qubits.assign(op.q, op.q + op.j);
       if (mode > 0) std::sort(nb.qubits.begin(), nb.qubits.end());
       nb.ops.push_back(i);
