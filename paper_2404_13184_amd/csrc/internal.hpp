@@ -98,10 +98,12 @@ struct RealPassGeom {
   uint64_t goff[12];                    // address offset of tile element S(2^(b + 1)): bit b of a slot index
   uint32_t op_off[kRealPassMax];        // element offset of superoperator j's operand
   uint16_t sbit[kRealPassMax][13];      // LDS byte offset of index bit b of superoperator j: b < 9 group
-                                        // bits, then its four local index bits (ascending)
+                                        // bits (four of the lanes, three of the waves, two of the column
+                                        // blocks), then its four local index bits (ascending)
   uint8_t emb[kRealPassMax];            // 0: a 16 x 16 operand; else a one-qubit 4 x 4 operand on the local
                                         // bits emb & 3 and (emb >> 2) & 3, the identity on the others (bit 4 set)
   int32_t m;
+  uint32_t sync;                        // bit j: superoperator j + 1 reads what other waves wrote
 };
 
 // Runs of superoperators of any width on small states, one launch per run (run.hip).

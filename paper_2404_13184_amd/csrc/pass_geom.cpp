@@ -301,6 +301,7 @@ RealPassGeom make_real_pass_geom(int n, int m, const int* k, const int* qubits, 
   g.dmask = ((1ull << nb) - 1ull) & ~held;
 
   int tpos[kRealPassMax][4], fpos[kRealPassMax][9];
+  uint32_t tmask[kRealPassMax];
   SwzProblem P{};
   P.W = W;
   P.V = V;
@@ -310,13 +311,10 @@ RealPassGeom make_real_pass_geom(int n, int m, const int* k, const int* qubits, 
     const int bits[4] = {q0, q0 + n, q1, q1 + n};
     uint32_t tm = 0;
     for (int t = 0; t < 4; ++t) tm |= 1u << local_of[real_addr_bit(bits[t], n)];
-    int nt = 0, nf = 0;
-    for (int b = 0; b < V; ++b) {
-      if ((tm >> b) & 1u)
-        tpos[j][nt++] = b;
-      else
-        fpos[j][nf++] = b;
-    }
+    tmask[j] = tm;
+    int nt = 0;
+    for (int b = 0; b < V; ++b)
+      if ((tm >> b) & 1u) tpos[j][nt++] = b;
     if (nt != 4) fail(TANQ_E_STATE, "a real pass superoperator repeats a qubit");
     g.op_off[j] = op_off[j];
     if (k[j] == 1) {
@@ -326,9 +324,32 @@ RealPassGeom make_real_pass_geom(int n, int m, const int* k, const int* qubits, 
         if (tpos[j][t] == local_of[real_addr_bit(q0, n)] || tpos[j][t] == local_of[real_addr_bit(q0 + n, n)]) e[ne++] = t;
       g.emb[j] = (uint8_t)(16 | e[0] | (e[1] << 2));
     }
-    // 32 lanes of 8 bytes: 16 groups (the four lowest free bits) and the lowest target bit
-    for (int t = 0; t < 4; ++t) P.fbits[j][t] = (uint32_t)fpos[j][t];
-    P.t1[j] = P.t2[j] = 1u << tpos[j][0];
+  }
+  // Three bits pick the wave.  Superoperators in a row that leave the same three bits alone share them, so that a
+  // wave reads only what it wrote and they need no barrier between them.  Never bit 0, without which a wave's
+  // lanes would reach half of the banks.
+  for (int j = 0; j < m;) {
+    uint32_t targets = tmask[j] | 1u;
+    int e = j + 1;
+    while (e < m && __builtin_popcount(targets | tmask[e]) <= V - 3) targets |= tmask[e++];
+    uint32_t waves = 0;  // the highest bits, so that the lanes keep the lowest
+    for (int b = V - 1; __builtin_popcount(waves) < 3; --b)
+      if (!((targets >> b) & 1u)) waves |= 1u << b;
+    if (e < m) g.sync |= 1u << (e - 1);
+    for (; j < e; ++j) {
+      int lanes[6], nl = 0, nw = 4;
+      for (int b = 0; b < V; ++b) {
+        if ((waves >> b) & 1u)
+          fpos[j][nw++] = b;
+        else if (!((tmask[j] >> b) & 1u))
+          lanes[nl++] = b;
+      }
+      for (int t = 0; t < 4; ++t) fpos[j][t] = lanes[t];
+      for (int t = 0; t < 2; ++t) fpos[j][7 + t] = lanes[4 + t];
+      // 32 lanes of 8 bytes: 16 groups and the lowest target bit
+      for (int t = 0; t < 4; ++t) P.fbits[j][t] = (uint32_t)fpos[j][t];
+      P.t1[j] = P.t2[j] = 1u << tpos[j][0];
+    }
   }
   // swizzle columns never set bit 0 (the two elements of a 16-byte slot stay together)
   uint8_t best[16] = {0};

@@ -266,19 +266,30 @@ __device__ inline uint64_t pdep64(uint64_t x, uint64_t mask) {
 
 // A run of up to eight one- and two-qubit superoperators on each tile of 2^13 reals (64 KiB) while it
 // is in LDS, as apply_pass_kernel: one workgroup per CU, eight waves that all multiply and each load
-// their share of the next tile into the other buffer, a contiguous range of tiles per workgroup.  A
-// real operand is a third of a 3M operand, so every operand and offset stays in registers for twice
-// the superoperators.  Per tile 128 KiB move (6.5 us at the state's streaming rate) against 0.9 us of
-// products per superoperator, so up to about six superoperators the pass is bound by memory.
+// their share of the next tile into the other buffer.  A real operand is a third of a 3M operand,
+// so every operand and offset stays in registers for twice the superoperators.
+//
+// Three tile bits pick the wave, and superoperators in a row that all leave three bits alone share them
+// (make_real_pass_geom), so a wave reads what it wrote itself and goes on to the next superoperator
+// without a barrier, out of step with the other wave on its SIMD, whose products cover its
+// LDS accesses.  Of seven gaps between eight superoperators about one needs a barrier.  At 14 qubits
+// a pass takes about 150 + 160 m us for m superoperators where memory does not bound it (150 + 190 m
+// with a barrier in every gap; the products alone are 139 m), and not less than 700 to 900 (4.3 GB),
+// so up to four superoperators it is bound by memory.
 __device__ inline void real_pass_tiles(double* __restrict__ w, const double* __restrict__ packed, const RealPassGeom& g,
                                        u32x4* ldsA, u32x4* ldsB) {
   constexpr int NT = kRealPassThreads, ITERS = 8, NBW = 4, MMAX = kRealPassMax;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // Tiles one after the other (first, first + 1, ..) or a grid apart, so that those in flight on the card lie next
+  // to each other.  20 layers of random U3/CX, contiguous -> apart: 12 qubits 2.88 -> 2.76 ms, 13 qubits
+  // 9.92 -> 9.46 ms; from 14 qubits on the two are within 1%, at 16 apart is 2% slower.
+  const bool apart = g.ntiles < (1ull << 15);
   const uint64_t per = (g.ntiles + gridDim.x - 1) / gridDim.x;
-  const uint64_t first = (uint64_t)blockIdx.x * per;
-  const uint64_t end = first + per < g.ntiles ? first + per : g.ntiles;
+  const uint64_t first = apart ? blockIdx.x : (uint64_t)blockIdx.x * per, by = apart ? gridDim.x : 1;
+  const uint64_t end = apart || first + per > g.ntiles ? g.ntiles : first + per;
   if (first >= end) return;  // uniform per workgroup
+  const uint64_t step = pdep64(by, g.dmask);
 
   // slot it * 512 + tid; offsets are linear over GF(2) in the slot index
   uint64_t off_t = 0;
@@ -376,17 +387,22 @@ __device__ inline void real_pass_tiles(double* __restrict__ w, const double* __r
       }
 #pragma unroll
       for (int r = 0; r < 4; ++r) at(NBW - 1, r) = acc[(NBW - 1) & 1][r];
-      raw_barrier();  // the next superoperator (or the store) reads what other waves wrote
+      if ((g.sync >> j) & 1u)
+        raw_barrier();  // the next superoperator reads what other waves wrote
+      else
+        asm volatile("" ::: "memory");  // it reads what this wave wrote; LDS accesses of a wave stay in order
     }
+    raw_barrier();  // the store reads what other waves wrote
 #pragma unroll
     for (int it = 0; it < ITERS; ++it)
       __builtin_nontemporal_store(buf[it * NT + tid], reinterpret_cast<u32x4*>(w + cur + off(it)));
   };
-  for (uint64_t tile = first;; ++tile) {
-    const bool more = tile + 1 < end;
-    // the base of the next tile: an increment under the mask of the bits outside the tile
-    const uint64_t nbase = more ? ((cur | ~g.dmask) + 1ull) & g.dmask : 0;
-    if ((tile - first) & 1)
+  bool odd = false;
+  for (uint64_t tile = first;; tile += by) {
+    const bool more = tile + by < end;
+    // the base of the next tile: a sum under the mask of the bits outside the tile
+    const uint64_t nbase = more ? ((cur | ~g.dmask) + step) & g.dmask : 0;
+    if (odd)
       tile_step(ldsB, ldsA, nbase, more);
     else
       tile_step(ldsA, ldsB, nbase, more);
@@ -394,6 +410,7 @@ __device__ inline void real_pass_tiles(double* __restrict__ w, const double* __r
     vm_wait<ITERS>();  // this wave's loads of the next tile (issued before its stores)
     raw_barrier();     // the next tile is in LDS; this buffer is read out
     cur = nbase;
+    odd = !odd;
   }
 }
 

@@ -163,6 +163,56 @@ def test_long_list_pass_limits(limit):
     assert np.abs(got - want).max() <= LIST_TOL * np.abs(want).max()
 
 
+@pytest.mark.parametrize("mode", [2, 3])
+def test_long_list_whole_and_in_ranges(mode):
+    """The whole list has an order of its own in the real form; ranges keep the list's."""
+    n = 11
+    say("real-form list in ranges, mode=%d" % mode)
+    ops = long_ops(n, 17 + mode) + long_ops(n, 27 + mode)
+    vec = hermitian_vec(n, 9)
+    want, _ = apply_list(n, ops, mode, vec, 8)
+    c = T.Circuit(n, ops)
+    f = c.fuse(mode, "f64")
+    runs = f.launches()
+    cut = sum(runs[:len(runs) // 2])
+    assert len(runs) // 2 >= 12
+    d = T.DM(n, "f64")
+    d.write(vec)
+    d.apply_fused(f, 0, cut)
+    d.apply_fused(f, cut, sum(runs))
+    got = d.read()
+    d.free()
+    f.free()
+    c.free()
+    assert np.abs(got - want).max() <= LIST_TOL * np.abs(want).max()
+
+
+def test_long_list_on_contiguous_tiles():
+    """From 14 qubits on a workgroup's tiles follow one another."""
+    n = 14
+    say("real-form list n=14")
+    ops = W.random_u3_cx(n, 6, 31, 1e-3, 1e-2)
+    idx = np.random.default_rng(1).integers(0, 4 ** n, 5000).astype(np.uint64)
+    old = T.tanq_get_pass_limit()
+    out = []
+    try:
+        c = T.Circuit(n, ops)
+        f = c.fuse(2, "f64")
+        assert len(f.launches()) >= 12
+        for limit in (1, 8):
+            T.tanq_set_pass_limit(limit)
+            d = T.DM(n, "f64")
+            d.apply_fused(f)
+            out.append((d.probs()[0], d.gather(idx)))
+            d.free()
+        f.free()
+        c.free()
+    finally:
+        T.tanq_set_pass_limit(old)
+    for want, got in zip(*out):
+        assert np.abs(got - want).max() <= LIST_TOL * np.abs(want).max()
+
+
 @pytest.mark.parametrize("spoil", ["all", "one", "diagonal", "huge", "nan"])
 def test_long_list_on_other_states(spoil):
     """A state that is not Hermitian in a single element, or out of range, is applied in the complex form:
