@@ -130,27 +130,39 @@ def run_precision(T, torch, n, ops, prec, width, steps, warmup):
         raise RuntimeError("a fused block is narrower than the qubits of its operations")
     f0.free()
 
-    def one_step(events=None):
+    def one_step(spans=None):
+        """Reset, fuse, apply the whole list, read the probabilities; spans: receives the events around the list."""
         d.reset()
         f = circ.fuse(width, prec, stream)
-        if events is None:
-            d.apply_fused(f)
-        else:
-            # the launches apply_fused makes (single applies and multi-superoperator passes),
-            # each bracketed by events on the library's stream
-            pos = 0
-            for r in f.launches():
-                ev0 = torch.cuda.Event(enable_timing=True)
-                ev1 = torch.cuda.Event(enable_timing=True)
-                ev0.record(stream)
-                d.apply_fused(f, pos, pos + r)
-                ev1.record(stream)
-                events.append((f.get_k(pos) if r == 1 else "pass", r, ev0, ev1, sum(block_flops[pos:pos + r])))
-                pos += r
+        ev0 = torch.cuda.Event(enable_timing=True)
+        ev1 = torch.cuda.Event(enable_timing=True)
+        ev0.record(stream)
+        d.apply_fused(f)
+        ev1.record(stream)
+        if spans is not None:
+            spans.append((ev0, ev1))
         p, tr = d.probs(renormalize=True)
         info = f.info
         f.free()
         return info, p, tr
+
+    def launches_step(events):
+        """The list one launch at a time (single applies and multi-superoperator passes), each bracketed by
+        events on the library's stream.  FP64 lists this short keep the complex form, where a whole list on
+        a Hermitian state is applied in real form."""
+        d.reset()
+        f = circ.fuse(width, prec, stream)
+        pos = 0
+        for r in f.launches():
+            ev0 = torch.cuda.Event(enable_timing=True)
+            ev1 = torch.cuda.Event(enable_timing=True)
+            ev0.record(stream)
+            d.apply_fused(f, pos, pos + r)
+            ev1.record(stream)
+            events.append((f.get_k(pos) if r == 1 else "pass", r, ev0, ev1, sum(block_flops[pos:pos + r])))
+            pos += r
+        torch.cuda.synchronize()
+        f.free()
 
     # the other fusion width, for context: one whole apply_fused timed end to end
     alt_w = 3 if chosen == 2 else 2
@@ -174,11 +186,13 @@ def run_precision(T, torch, n, ops, prec, width, steps, warmup):
     for w in range(warmup):
         one_step()
         log("%s warmup step %d done" % (prec, w + 1))
+    events, spans = [], []
+    launches_step(events)
+    log("%s launch by launch: %d launches" % (prec, len(events)))
     torch.cuda.synchronize()
-    events = []
     t0 = time.perf_counter()
     for st in range(steps):
-        info, p, tr = one_step(events)
+        info, p, tr = one_step(spans)
         log("%s step %d done (%.1fs)" % (prec, st + 1, time.perf_counter() - t0))
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
@@ -189,6 +203,8 @@ def run_precision(T, torch, n, ops, prec, width, steps, warmup):
         if r >= 2:
             pass_sizes.append(r)
     circ.free()
+    list_s = sum(a.elapsed_time(b) for a, b in spans) * 1e-3 / max(len(spans), 1)
+    log("%s whole list: %.1f ms" % (prec, list_s * 1e3))
     stream_s = time_stream(torch, d, stream)
     log("%s in-place stream over the state: %.3f ms (%.1f GB/s)" % (prec, stream_s * 1e3, d_bytes(d) / stream_s / 1e9))
     mfma_tf = T.tanq_mfma_rate(prec)
@@ -196,7 +212,7 @@ def run_precision(T, torch, n, ops, prec, width, steps, warmup):
     applies = info["count"] * steps
     return {"wall_s": wall, "applies": applies, "info": info, "per_k": per_k, "trace": tr, "probs": p,
             "tuned_ms": tuned_ms[1:], "variants": variants, "alternative": alternative,
-            "pass_sizes": pass_sizes, "alg_flops": alg_flops, "launches": len(events) // max(steps, 1),
+            "pass_sizes": pass_sizes, "alg_flops": alg_flops, "launches": len(events), "list_s": list_s, "list_flops": sum(block_flops),
             "stream_s": stream_s, "mfma_tflops": mfma_tf}, d
 
 
@@ -574,6 +590,7 @@ def main():
         return rl
 
     def dominant(rr, prec):
+        """Roofline of the kernel with the most time among the launches applied one at a time."""
         k = max(rr["per_k"], key=lambda kk: sum(rr["per_k"][kk]))
         secs = sum(rr["per_k"][k]) / len(rr["per_k"][k])
         if k == "pass":
@@ -631,7 +648,7 @@ def main():
                    "count_by_k": r["info"]["count_k"][1:]},
         "gates_per_s": round(len(ops) * a.steps / r["wall_s"], 1),
         "fusion": fusion,
-        "roofline": dominant(r, main_prec),
+        "roofline": dict(dominant(r, main_prec), sample="launches applied one at a time, before the timed steps"),
     }
     for prec, rr in results.items():
         out[prec] = {"applies_per_s": round(rr["applies"] / rr["wall_s"], 3),
@@ -643,7 +660,9 @@ def main():
                      "roofline": dominant(rr, prec), "trace": rr["trace"],
                      "autotuned_ms_per_apply_by_k": [round(x, 3) for x in rr["tuned_ms"]],
                      "variants": rr["variants"], "launches_per_step": rr["launches"],
-                     "passes_per_step": len(rr["pass_sizes"]) // max(a.steps, 1),
+                     "passes_per_step": len(rr["pass_sizes"]),
+                     "list_ms": round(rr["list_s"] * 1e3, 3),
+                     "list_effective_TFLOPs_algorithmic": round(rr["list_flops"] / rr["list_s"] / 1e12, 2),
                      "other_fusion_width": rr["alternative"],
                      "hbm": hbm_summary(prec, rr)}
     if accuracy is not None:
