@@ -339,9 +339,10 @@ tanq_status tanq_probs_readout(tanq_dm d, const double* p01, const double* p10, 
 tanq_status tanq_sample(tanq_dm d, uint64_t shots, uint64_t seed, const double* p01, const double* p10,
                         uint64_t* host_out);
 
-/* tanq_sample without any device allocation, for callers that cannot allocate: tight serving loops, harnesses that forbid hipMalloc.  Same arguments, draws
- * and outcomes as tanq_sample.  The CDF and the outcomes live in buffers of the handle, so n <= 17 and
- * shots <= 2^17 per call; beyond that TANQ_E_ARG.  Synchronises. */
+/* tanq_sample without any device allocation, for callers that cannot allocate: tight serving loops,
+ * harnesses that forbid hipMalloc.  Same arguments, draws and outcomes as tanq_sample.  The CDF and
+ * the outcomes live in buffers of the handle, so n <= 17 and shots <= 2^17 per call; beyond that
+ * TANQ_E_ARG.  Synchronises. */
 tanq_status tanq_sample_noalloc(tanq_dm d, uint64_t shots, uint64_t seed, const double* p01, const double* p10,
                                 uint64_t* host_out);
 

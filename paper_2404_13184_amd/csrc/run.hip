@@ -16,7 +16,7 @@
 // (their loads later hit the L2); the table of blocks is copied from the kernel's arguments into LDS in
 // one go; a block's entry and operand are read from LDS while the one before is multiplied; blocks one after
 // the other on one qubit keep their amplitudes in registers.  The 640 single-operation blocks of the
-// 8-qubit plain circuit: 640 launches, 2.81 ms, one by one; 59 launches, 0.86 ms, in runs (12.2 us each,
+// 8-qubit plain circuit: 640 launches, 2.81 ms, one by one; 59 launches, 0.81 ms, in runs (12.2 us each,
 // 3.4 us of it the start).  A 6-qubit list of 23 two-qubit blocks: 150 -> 55 us.
 #include <cstddef>
 
