@@ -87,8 +87,10 @@ struct ComposeFeed {
 // k = 3, 3M: P[((mt * 16 + ks) * 3 + c) * 64 + lane] = C_c[16 mt + lane % 16][4 ks + lane / 16]
 //   with C_0 = Re S, C_1 = Im S, C_2 = Re S + Im S (summed in FP64, rounded once).
 // k = 1: the FP64 superoperator itself (32 doubles), for both precisions.
+// ld: elements per row of S (k = 3), which holds the columns from c0 on; nc of them, a multiple of four, are packed.
 template <typename T>
-__device__ void pack_block(int k, const double* __restrict__ S, unsigned char* __restrict__ out) {
+__device__ void pack_block(int k, const double* __restrict__ S, unsigned char* __restrict__ out, int ld = 64, int c0 = 0,
+                           int nc = 64) {
   if (k == 1) {
     double* P = reinterpret_cast<double*>(out);
     for (int e = threadIdx.x; e < 32; e += blockDim.x) P[e] = S[e];
@@ -104,12 +106,13 @@ __device__ void pack_block(int k, const double* __restrict__ S, unsigned char* _
     }
   } else {
     T* P = reinterpret_cast<T*>(out);
-    for (int e = threadIdx.x; e < 4 * 16 * 3 * 64; e += blockDim.x) {
+    const int per = nc / 4 * 3;  // fragments per m-tile
+    for (int e = threadIdx.x; e < 4 * per * 64; e += blockDim.x) {
       const int lane = e & 63, rest = e >> 6;
-      const int c = rest % 3, ks = (rest / 3) % 16, mt = rest / 48;
-      const int a = 16 * mt + (lane & 15), b = 4 * ks + (lane >> 4);
-      const double re = S[2 * (a * 64 + b)], im = S[2 * (a * 64 + b) + 1];
-      P[e] = (T)(c == 0 ? re : (c == 1 ? im : re + im));
+      const int mt = rest / per, f = c0 / 4 * 3 + rest % per, c = f % 3, ks = f / 3;
+      const int a = 16 * mt + (lane & 15), b = 4 * ks + (lane >> 4) - c0;
+      const double re = S[2 * (a * ld + b)], im = S[2 * (a * ld + b) + 1];
+      P[(mt * 48 + f) * 64 + lane] = (T)(c == 0 ? re : (c == 1 ? im : re + im));
     }
   }
 }

@@ -126,28 +126,34 @@ __device__ inline void compose_mac(double& yr, double& yi, const f64x2 w, const 
   yi += __builtin_fma(w[0], x[1], w[1] * x[0]);
 }
 
-// One workgroup per block: M <- S_op(embedded) M for each operation, starting from M = I.
+// One workgroup per block (four at three qubits): M <- S_op(embedded) M for each operation, starting from M = I.
 // Column c of the result is vec of the block's action on the basis operator with vec
 // index c, so the final M is S_blk = S_last ... S_first.  M stays in LDS, and what follows it -- the FP64
 // copy and the operand in the apply kernels' layout -- is written from there.
 //
 // One or two qubits (k): every thread computes one element per operation, from one copy of M into another.
-// Three: a thread owns whole groups of a column (the rows that an operation of one or two qubits mixes)
-// and rewrites them in place from registers; a three-qubit operation mixes whole columns, so its results wait
-// in registers for a barrier.  The chain of operations is serial: ComposeFeed keeps it from waiting for
+// Three: columns do not mix, so four workgroups take 16 of a block's 64 each (a circuit has fewer blocks
+// than the card has CUs, and a block's products are four times the chain's other costs); M is rewritten in
+// place from registers, with a barrier between the reads and the writes where an operation's rows are
+// spread over several threads.  The chain of operations is serial: ComposeFeed keeps it from waiting for
 // memory.  A 6-qubit circuit of 10 layers (26 blocks of about 7 operations): 80 us, and 4.5 us more in a
-// launch of its own for the operands, -> 18 us.
+// launch of its own for the operands, -> 18 us.  The three-qubit blocks of a
+// request of 20 to 80 layers on 4 to 12 qubits: 184 us by one workgroup each, 74 us by four.
+constexpr int kComposeParts = 4, kComposeCols = 64 / kComposeParts;
 template <typename T, int KMAX>
 __global__ __launch_bounds__(256) void compose_kernel(const FuseBlockDev* __restrict__ blocks,
                                                       const FuseOpDev* __restrict__ ops,
                                                       const double* __restrict__ sops, double* __restrict__ out,
                                                       unsigned char* __restrict__ packed) {
-  __shared__ f64x2 M[KMAX == 3 ? 64 * 64 : 2 * 16 * 16];
+  __shared__ f64x2 M[KMAX == 3 ? 64 * kComposeCols : 2 * 16 * 16];
   __shared__ typename ComposeFeed<f64x2>::Lds fl;
-  const FuseBlockDev blk = blocks[blockIdx.x];
+  const FuseBlockDev blk = blocks[KMAX == 3 ? blockIdx.x / kComposeParts : blockIdx.x];
+  const int part = KMAX == 3 ? (int)(blockIdx.x % kComposeParts) : 0;
   const int k = blk.k, Dk = 1 << (2 * k), tid = threadIdx.x;
+  if (k < 3 && part > 0) return;  // uniform per workgroup
   const f64x2* sops2 = reinterpret_cast<const f64x2*>(sops);
-  for (int e = tid; e < Dk * Dk; e += 256) M[e] = f64x2{(e / Dk) == (e % Dk) ? 1.0 : 0.0, 0.0};
+  const int nc = k == 3 ? kComposeCols : Dk, c0 = part * kComposeCols;  // columns of this workgroup
+  for (int e = tid; e < Dk * nc; e += 256) M[e] = f64x2{(e / nc) == c0 + (e % nc) ? 1.0 : 0.0, 0.0};
   ComposeFeed<f64x2> feed(fl, ops + blk.op_begin, sops2, blk.op_count);
   feed.start();
   int cur = 0;  // k <= 2: which copy of M is current
@@ -191,55 +197,58 @@ __global__ __launch_bounds__(256) void compose_kernel(const FuseBlockDev* __rest
       }
       cur ^= 1;
     } else if constexpr (KMAX == 3) {
-      const int c = tid % 64, slot = tid / 64;
+      constexpr int NC = kComposeCols;
+      const int c = tid % NC, slot = tid / NC;  // 16 slots
       const uint32_t fm = 63u & ~tmask;
       if (j == 1) {
-        for (int g = slot; g < 16; g += 4) {
-          const int base = (int)pdep32((uint32_t)g, fm);
-          f64x2 x[4];
+        const int base = (int)pdep32((uint32_t)slot, fm);
+        f64x2 x[4];
 #pragma unroll
-          for (int b = 0; b < 4; ++b) x[b] = M[(base | dep(b)) * 64 + c];
+        for (int b = 0; b < 4; ++b) x[b] = M[(base | dep(b)) * NC + c];
 #pragma unroll
-          for (int a = 0; a < 4; ++a) {
-            double yr = 0.0, yi = 0.0;
+        for (int a = 0; a < 4; ++a) {
+          double yr = 0.0, yi = 0.0;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) compose_mac(yr, yi, S[a * 4 + b], x[b]);
-            M[(base | dep(a)) * 64 + c] = f64x2{yr, yi};
-          }
+          for (int b = 0; b < 4; ++b) compose_mac(yr, yi, S[a * 4 + b], x[b]);
+          M[(base | dep(a)) * NC + c] = f64x2{yr, yi};
         }
       } else if (j == 2) {
-        const int base = (int)pdep32((uint32_t)slot, fm);
-        f64x2 x[16];
+        // four rows of one of the four groups; a wave's rows of S are the same for all of its lanes
+        const int base = (int)pdep32((uint32_t)(slot & 3), fm), a0 = __builtin_amdgcn_readfirstlane(slot >> 2) * 4;
+        f64x2 x[16], y[4];
 #pragma unroll
-        for (int b = 0; b < 16; ++b) x[b] = M[(base | dep(b)) * 64 + c];
-#pragma unroll 4
-        for (int a = 0; a < 16; ++a) {
+        for (int b = 0; b < 16; ++b) x[b] = M[(base | dep(b)) * NC + c];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
           double yr = 0.0, yi = 0.0;
 #pragma unroll
-          for (int b = 0; b < 16; ++b) compose_mac(yr, yi, S[a * 16 + b], x[b]);
-          M[(base | dep(a)) * 64 + c] = f64x2{yr, yi};
-        }
-      } else {
-        const f64x2* Sg = sops2 + op.sop_off;
-        f64x2 y[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int a = slot * 16 + i;  // local index; the row of M is dep(a)
-          double yr = 0.0, yi = 0.0;
-          for (int b = 0; b < 64; ++b) compose_mac(yr, yi, Sg[a * 64 + b], M[dep(b) * 64 + c]);
+          for (int b = 0; b < 16; ++b) compose_mac(yr, yi, S[(a0 + i) * 16 + b], x[b]);
           y[i] = f64x2{yr, yi};
         }
-        lds_barrier();  // every read of M is done before it is overwritten
+        raw_barrier();  // every read of M is done before it is overwritten
 #pragma unroll
-        for (int i = 0; i < 16; ++i) M[dep(slot * 16 + i) * 64 + c] = y[i];
+        for (int i = 0; i < 4; ++i) M[(base | dep(a0 + i)) * NC + c] = y[i];
+      } else {
+        const f64x2* Sg = sops2 + op.sop_off;
+        f64x2 y[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int a = slot * 4 + i;  // local index; the row of M is dep(a)
+          double yr = 0.0, yi = 0.0;
+          for (int b = 0; b < 64; ++b) compose_mac(yr, yi, Sg[a * 64 + b], M[dep(b) * NC + c]);
+          y[i] = f64x2{yr, yi};
+        }
+        raw_barrier();  // every read of M is done before it is overwritten
+#pragma unroll
+        for (int i = 0; i < 4; ++i) M[dep(slot * 4 + i) * NC + c] = y[i];
       }
     }
     feed.next(oi);
   }
   const f64x2* R = M + cur * Dk * Dk;
   f64x2* O = reinterpret_cast<f64x2*>(out) + blk.out_off;
-  for (int e = tid; e < Dk * Dk; e += 256) O[e] = R[e];
-  pack_block<T>(k, reinterpret_cast<const double*>(R), packed + blk.pack_off);
+  for (int e = tid; e < Dk * nc; e += 256) O[(e / nc) * Dk + c0 + e % nc] = R[e];
+  pack_block<T>(k, reinterpret_cast<const double*>(R), packed + blk.pack_off, nc, c0, nc);
 }
 
 // ------------------------------------------------------------------------------------
@@ -463,7 +472,7 @@ static void compose_typed(const FuseBlockDev* blocks, int nblocks, int max_k, co
     hipLaunchKernelGGL((compose_kernel<T, 2>), dim3(nblocks), dim3(256), 0, s, blocks, ops, sops, out,
                        (unsigned char*)packed);
   else
-    hipLaunchKernelGGL((compose_kernel<T, 3>), dim3(nblocks), dim3(256), 0, s, blocks, ops, sops, out,
+    hipLaunchKernelGGL((compose_kernel<T, 3>), dim3(nblocks * kComposeParts), dim3(256), 0, s, blocks, ops, sops, out,
                        (unsigned char*)packed);
   TANQ_HIP(hipGetLastError());
 }
