@@ -273,12 +273,12 @@ tanq_status tanq_autotune_dense(tanq_dm d, int reps, double* ms_per_apply);
  * launch (not with limit 1); the results are bit for bit those of the blocks one by one, and
  * tanq_fused_launches counts them as single applies.
  *
- * Long FP64 lists (11 to 16 qubits, at least 12 launches as tanq_fused_launches counts them, passes
- * not switched off) on an exactly Hermitian rho are applied in real form: the 4^n Pauli expectations, on
- * which every superoperator is a real matrix, formed in place before the first superoperator and
- * turned back after the last.  The device checks rho and chooses; the call stays asynchronous and the
- * results agree with the blocks applied one by one to rounding (exactly Hermitian).  Any other rho
- * takes the launches that tanq_fused_launches lists. */
+ * Long FP64 lists (11 to 16 qubits; at least 12 launches as tanq_fused_launches counts them, 8 from
+ * 13 qubits on; passes not switched off) on an exactly Hermitian rho are applied in real form: the 4^n
+ * Pauli expectations, on which every superoperator is a real matrix, formed in place before the
+ * first superoperator and turned back after the last.  The device checks rho and chooses; the call
+ * stays asynchronous and the results agree with the blocks applied one by one to rounding (exactly
+ * Hermitian).  Any other rho takes the launches that tanq_fused_launches lists. */
 tanq_status tanq_set_pass_limit(int max_superops);
 tanq_status tanq_get_pass_limit(int* max_superops);
 /* How tanq_apply_fused groups f's blocks under the current limit: *passes receives the number

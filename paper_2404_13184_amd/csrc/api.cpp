@@ -251,17 +251,19 @@ int count_launches(BlockAt at, int begin, int end, int n, tanq_prec p, int lim) 
 }
 
 // Lists applied in real form where the state is Hermitian (herm.hip): FP64 states of 11 to 16 qubits,
-// lists of at least kHermMinLaunches launches (single applies and passes).  The check and the way in
+// lists of at least 12 launches (single applies and passes), 8 from 13 qubits on.  The check and the way in
 // and out cost about three and a half passes (16 qubits: 115 ms against 32 ms) and a real pass takes
-// less than half of one (15 ms), so the line is at about seven launches; twelve keeps the gain clear of
-// the cost.  Measured, complex -> real: 20 layers of random U3/CX at width 2, 11 qubits 1204 -> 645
+// less than half of one (15 ms), so the line is at about seven launches: lists of 8, complex ->
+// real: 13 qubits 3.93 -> 3.57 ms, 14 qubits 15.1 -> 13.4 ms, 16 qubits 231 -> 217 ms; of 10 at 15
+// qubits 75.8 -> 58.7 ms.  At 11 and 12 qubits 12 keeps the gain clear of what a state that is not
+// Hermitian pays.  Measured, complex -> real: 20 layers of random U3/CX at width 2, 11 qubits 1204 -> 645
 // us, 12 qubits 4.62 -> 2.33 ms, 14 qubits 78.7 -> 40.3 ms; 10 layers at 16 qubits 740 -> 450 ms.  A
 // state that is not Hermitian pays for the check and the launches that do nothing: 7% at 11 qubits,
 // 3% at 12, 1% at 14.  Below 11 qubits those outweigh the gain.  FP32 keeps the complex form: its
 // results would move in the seventh digit.  Passes switched off (limit 1) keep it off too: the blocks
 // are then applied one by one.
 bool herm_list(int launches, int n, tanq_prec p, int lim) {
-  return p == TANQ_F64 && n >= kHermMinN && n <= kHermMaxN && lim >= 2 && launches >= kHermMinLaunches;
+  return p == TANQ_F64 && n >= kHermMinN && n <= kHermMaxN && lim >= 2 && launches >= herm_min_launches(n);
 }
 
 // Length of the run that starts at block i (blocks before `end`) on a small state: the consecutive blocks of

@@ -88,7 +88,7 @@ struct PassGeom {
 // fill the lower half of vec(rho)'s memory and the pair that differs in the top column bit shares
 // the 16 bytes of the lower element of the pair.
 constexpr int kHermMinN = 11, kHermMaxN = 16;
-constexpr int kHermMinLaunches = 12;
+inline int herm_min_launches(int n) { return n < 13 ? 12 : 8; }
 constexpr int kRealPassBits = 13;  // 2^13 reals = 64 KiB
 constexpr int kRealPassMax = 8;    // superoperators whose operands fit in registers
 constexpr int kRealPassThreads = 512;

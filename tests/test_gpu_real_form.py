@@ -163,6 +163,20 @@ def test_long_list_pass_limits(limit):
     assert np.abs(got - want).max() <= LIST_TOL * np.abs(want).max()
 
 
+def test_list_of_eight_launches():
+    """From 13 qubits on, lists of 8 launches are long enough."""
+    n = 13
+    say("real-form list of 8 launches")
+    ops = W.random_u3_cx(n, 4, 3, 1e-3, 1e-2)
+    vec = hermitian_vec(n, 4)
+    want, _ = apply_list(n, ops, 2, vec, 1)
+    got, launches = apply_list(n, ops, 2, vec, 8)
+    assert 8 <= launches < 12
+    assert np.abs(got - want).max() <= LIST_TOL * np.abs(want).max()
+    m = got.reshape(1 << n, 1 << n)
+    assert np.array_equal(m, m.conj().T)
+
+
 @pytest.mark.parametrize("mode", [2, 3])
 def test_long_list_whole_and_in_ranges(mode):
     """The whole list has an order of its own in the real form; ranges keep the list's."""
