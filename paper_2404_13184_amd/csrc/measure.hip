@@ -10,7 +10,7 @@
 // shots from prefix sums within blocks of 4096 outcomes and the blocks' totals.
 // One after the other (probabilities, readout error, 1000 shots, 7 strings, a reduced matrix): 7 qubits
 // 300 -> 93 us, 16 qubits in FP32 (100,000 shots, 48 strings, three qubits kept) 771 ->
-// 323 us (of which the strings, one cache line per element, are 73 and cannot do with less).
+// 330 us (of which the strings, one cache line per element, are about 80, 10 of them the fixed order of the sums).
 #include "tile.hpp"
 
 namespace tanq {
@@ -260,35 +260,90 @@ __global__ __launch_bounds__(256) void draw_kernel(const double* __restrict__ cd
 // ------------------------------------------------------------------------------------
 
 // Tr(P rho) = sum_s phase(s) rho[s][s ^ xmask],  phase(s) = i^{#Y} (-1)^{popcount(s & zmask)}
-// masks[3 i + 0] = xmask (X or Y), masks[3 i + 1] = zmask (Z or Y), masks[3 i + 2] = #Y mod 4.  gridDim.x
-// workgroups per string; out[(string * 2 + part) * gridDim.x + workgroup]
+// masks[3 i + 0] = xmask (X or Y), masks[3 i + 1] = zmask (Z or Y), masks[3 i + 2] = #Y mod 4.
+//
+// An expectation that vanishes by symmetry is the rounding of its sum, so the order of the sum is part of the
+// result and does not depend on how the work is split: nparts (at most 512) part sums (part b takes s = 256 b + t + 256 nparts k,
+// thread by thread, then wave by wave), added one after the other.  A workgroup forms kPauliParts of them, its four
+// groups of 256 threads (one group where there is one part) two each; where it forms all, it adds them and out[2 string + (re, im)] is the
+// result, else out[(2 string + (re, im)) nparts + part].
+constexpr int kPauliParts = 8;
+constexpr int kMaxParts = 512;
 template <typename T>
-__global__ __launch_bounds__(256) void pauli_kernel(const T* __restrict__ rho, int n,
-                                                    const uint64_t* __restrict__ masks, double* __restrict__ out) {
-  __shared__ double sh[4];
+__global__ __launch_bounds__(1024) void pauli_kernel(const T* __restrict__ rho, int n, int nparts,
+                                                     const uint64_t* __restrict__ masks, double* __restrict__ out) {
+  __shared__ double sh[2][kPauliParts][4];
   const int si = blockIdx.y;
   const uint64_t xm = masks[3 * si], zm = masks[3 * si + 1];
   const int ny = (int)masks[3 * si + 2];
   const uint64_t dim = 1ull << n;
   const auto* v2 = reinterpret_cast<const typename Complex<T>::t*>(rho);
-  double ar = 0.0, ai = 0.0;
-  for (uint64_t s = (uint64_t)blockIdx.x * 256 + threadIdx.x; s < dim; s += (uint64_t)gridDim.x * 256) {
-    const auto v = v2[s + ((s ^ xm) << n)];
-    const double sg = (__popcll(s & zm) & 1) ? -1.0 : 1.0;
-    ar += sg * (double)v[0];
-    ai += sg * (double)v[1];
+  const int t = threadIdx.x & 255;
+  const int first = blockIdx.x * kPauliParts, count = nparts - first < kPauliParts ? nparts - first : kPauliParts;
+  double ar[2] = {0.0, 0.0}, ai[2] = {0.0, 0.0};
+  int p[2];  // this thread's parts
+#pragma unroll
+  for (int r = 0; r < 2; ++r) p[r] = (threadIdx.x >> 8) + r * (kPauliParts / 2);
+  for (uint64_t k = 0; k < dim; k += (uint64_t)nparts * 256) {
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+      const uint64_t s = k + (uint64_t)(first + p[r]) * 256 + t;
+      if (p[r] < count && s < dim) {
+        const auto v = v2[s + ((s ^ xm) << n)];
+        const double sg = (__popcll(s & zm) & 1) ? -1.0 : 1.0;
+        ar[r] += sg * (double)v[0];
+        ai[r] += sg * (double)v[1];
+      }
+    }
   }
-  // multiply by i^{#Y}
-  double pr = ar, pi = ai;
-  if (ny == 1) { pr = -ai; pi = ar; }
-  else if (ny == 2) { pr = -ar; pi = -ai; }
-  else if (ny == 3) { pr = ai; pi = -ar; }
-  const double tr = all_sum(pr, sh);
-  const double ti = all_sum(pi, sh);
-  if (threadIdx.x == 0) {
-    out[((size_t)si * 2 + 0) * gridDim.x + blockIdx.x] = tr;
-    out[((size_t)si * 2 + 1) * gridDim.x + blockIdx.x] = ti;
+#pragma unroll
+  for (int r = 0; r < 2; ++r) {
+    // multiply by i^{#Y}
+    double pr = ar[r], pi = ai[r];
+    if (ny == 1) { pr = -ai[r]; pi = ar[r]; }
+    else if (ny == 2) { pr = -ar[r]; pi = -ai[r]; }
+    else if (ny == 3) { pr = ai[r]; pi = -ar[r]; }
+    for (int o = 32; o > 0; o >>= 1) {
+      pr += __shfl_down(pr, o, 64);
+      pi += __shfl_down(pi, o, 64);
+    }
+    if (p[r] < count && (t & 63) == 0) {
+      sh[0][p[r]][t >> 6] = pr;
+      sh[1][p[r]][t >> 6] = pi;
+    }
   }
+  __syncthreads();
+  auto part = [&](int c, int p) {
+    double x = 0.0;
+    for (int w = 0; w < 4; ++w) x += sh[c][p][w];
+    return x;
+  };
+  if (gridDim.x == 1) {
+    if (threadIdx.x < 2) {
+      double x = 0.0;
+      for (int p = 0; p < count; ++p) x += part(threadIdx.x, p);
+      out[2 * (size_t)si + threadIdx.x] = x;
+    }
+  } else if ((int)threadIdx.x < 2 * count) {
+    const int c = threadIdx.x & 1, p = threadIdx.x >> 1;
+    out[((size_t)si * 2 + c) * nparts + first + p] = part(c, p);
+  }
+}
+
+// out[i] = the sum of partials[i * count ..] one after the other, one wave each
+__global__ __launch_bounds__(64) void sum_in_order_kernel(const double* __restrict__ partials, int count,
+                                                          double* __restrict__ out) {
+  const double* p = partials + (size_t)blockIdx.x * count;
+  double v[kMaxParts / 64], t = 0.0;
+#pragma unroll
+  for (int u = 0; u < kMaxParts / 64; ++u) v[u] = u * 64 + (int)threadIdx.x < count ? p[u * 64 + threadIdx.x] : 0.0;
+#pragma unroll
+  for (int u = 0; u < kMaxParts / 64; ++u) {
+    if (u * 64 >= count) break;
+    const int m = count - u * 64 < 64 ? count - u * 64 : 64;
+    for (int i = 0; i < m; ++i) t += lane_value(v[u], i);
+  }
+  if (threadIdx.x == 0) out[blockIdx.x] = t;
 }
 
 struct Kept {
@@ -413,21 +468,21 @@ void launch_sample(const void* rho, int n, tanq_prec p, const double* p01, const
 
 void launch_pauli(const void* rho, int n, tanq_prec p, int count, const uint64_t* masks, double* partials, double* out,
                   hipStream_t s) {
-  // workgroups per string: at least 2048 elements each, enough for about 2048 in all, within the scratch
+  // 256 elements a part, at most 512 parts, all within the scratch
   const uint64_t dim = 1ull << n;
-  int nb = (int)(dim / 2048 < 1 ? 1 : dim / 2048);
-  const int most = count < 64 ? 2048 / count : 32;
-  if (nb > most) nb = most;
-  if (nb > kPartials / (2 * count)) nb = kPartials / (2 * count);
-  if (nb < 1) nb = 1;
-  double* to = nb == 1 ? out : partials;
+  int nparts = dim < 256 * kMaxParts ? (int)((dim + 255) / 256) : kMaxParts;
+  const int most = kPartials / (2 * count);
+  if (nparts > most) nparts = most < 1 ? 1 : most;
+  const int groups = (nparts + kPauliParts - 1) / kPauliParts;
+  const unsigned nt = nparts == 1 ? 256 : 1024;
+  double* to = groups == 1 ? out : partials;
   if (p == TANQ_F64)
-    hipLaunchKernelGGL(pauli_kernel<double>, dim3(nb, count), dim3(256), 0, s, (const double*)rho, n, masks, to);
+    hipLaunchKernelGGL(pauli_kernel<double>, dim3(groups, count), dim3(nt), 0, s, (const double*)rho, n, nparts, masks, to);
   else
-    hipLaunchKernelGGL(pauli_kernel<float>, dim3(nb, count), dim3(256), 0, s, (const float*)rho, n, masks, to);
+    hipLaunchKernelGGL(pauli_kernel<float>, dim3(groups, count), dim3(nt), 0, s, (const float*)rho, n, nparts, masks, to);
   TANQ_HIP(hipGetLastError());
-  if (nb > 1) {
-    hipLaunchKernelGGL(sum_partials_kernel, dim3(2 * count), dim3(64), 0, s, partials, nb, out);
+  if (groups > 1) {
+    hipLaunchKernelGGL(sum_in_order_kernel, dim3(2 * count), dim3(64), 0, s, partials, nparts, out);
     TANQ_HIP(hipGetLastError());
   }
 }

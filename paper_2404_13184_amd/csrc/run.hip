@@ -51,16 +51,6 @@ __device__ inline void uniform_all(RunOp& o) {
   for (int i = 0; i < (int)(sizeof(RunOp) / 4); ++i) w[i] = uniform(w[i]);
   __builtin_memcpy(&o, w, sizeof(o));
 }
-// lane l's value, uniform
-__device__ inline double lane_value(double v, int l) {
-  const uint64_t u = __builtin_bit_cast(uint64_t, v);
-  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l),
-                 hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
-  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ inline float lane_value(float v, int l) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
-}
 // offset of the geometry among the kernel's arguments (after two pointers)
 constexpr int kRunArgAt = 16;
 

@@ -66,6 +66,17 @@ __device__ inline uint32_t pext32(uint32_t x, uint32_t mask) {
   return r;
 }
 
+// Value of lane l (uniform)
+__device__ inline double lane_value(double v, int l) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)u, l),
+                 hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(u >> 32), l);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ inline float lane_value(float v, int l) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), l));
+}
+
 // LDS swizzle: element e of a tile lives at LDS element e ^ X(e), where X copies up to four
 // group-index bits lying above the 256-byte bank window into target-bit positions inside it
 // (masks xsrc, xdst from make_apply_geom).  The 16 groups of an MFMA column block then fall on
