@@ -275,10 +275,14 @@ tanq_status tanq_autotune_dense(tanq_dm d, int reps, double* ms_per_apply);
  *
  * Long FP64 lists (11 to 16 qubits; at least 12 launches as tanq_fused_launches counts them, 8 from
  * 13 qubits on; passes not switched off) on an exactly Hermitian rho are applied in real form: the 4^n
- * Pauli expectations, on which every superoperator is a real matrix, formed in place before the
- * first superoperator and turned back after the last.  The device checks rho and chooses; the call
- * stays asynchronous and the results agree with the blocks applied one by one to rounding (exactly
- * Hermitian).  Any other rho takes the launches that tanq_fused_launches lists. */
+ * real coefficients of rho over the products of |0><0|, |1><1|, X and Y, on which every superoperator is a
+ * real matrix, formed in place before the first superoperator and turned back after the last.  The
+ * device checks rho and chooses; the call stays asynchronous and the results agree with the blocks applied
+ * one by one to rounding (exactly Hermitian).  Populations keep their relative accuracy, however rare, and exact
+ * zeros stay exact; an element between states that differ in some qubits is known to the rounding of the
+ * largest element between states that differ in the same qubits.  Values that vanish by symmetry are rounding in
+ * either form, and not the same.  Any other rho takes the launches that tanq_fused_launches lists, and so
+ * does a list applied over ranges shorter than the above: that is how a caller keeps vec(rho). */
 tanq_status tanq_set_pass_limit(int max_superops);
 tanq_status tanq_get_pass_limit(int* max_superops);
 /* How tanq_apply_fused groups f's blocks under the current limit: *passes receives the number

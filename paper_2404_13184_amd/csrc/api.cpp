@@ -119,11 +119,10 @@ struct tanq_fused_s {
   double* raw = nullptr;
   unsigned char* packed = nullptr;
   // real operands for long lists on Hermitian FP64 states (herm.hip), if it is long enough for
-  // them; block b's at rpacked + rpack_off[b], the defect table after the last
+  // them; block b's at rpacked + rpack_off[b]
   double* rpacked = nullptr;
   std::vector<size_t> rpack_off;
   std::vector<int> rorder;  // the whole list in the real form's order
-  double* defects = nullptr;
   // pass geometries already built, by (first block, length)
   std::mutex pass_mu;
   std::map<std::pair<int, int>, tanq::PassGeom> passes;
@@ -854,7 +853,7 @@ tanq_status tanq_fuse(tanq_circuit c, int max_width, tanq_prec p, void* hip_stre
       // hipMalloc and hipFree pair costs about 10 us, and fusing a 6-qubit circuit of 180
       // operations took 105 us with six pairs and three uploads.
       const size_t raw_b = align256(L.raw_elems * 2 * sizeof(double));
-      const size_t real_b = rb.empty() ? 0 : align256((real_elems + (size_t)nblk + 1) * sizeof(double));
+      const size_t real_b = rb.empty() ? 0 : align256(real_elems * sizeof(double));
       const size_t keep_b = raw_b + align256(L.pack_bytes) + real_b;
       const size_t ops_b = align256(L.ops.size() * sizeof(FuseOpDev));
       const size_t blk_b = align256(L.blocks.size() * sizeof(FuseBlockDev));
@@ -885,8 +884,7 @@ tanq_status tanq_fuse(tanq_circuit c, int max_width, tanq_prec p, void* hip_stre
                          (const double*)(tmp + ops_b + blk_b + rblk_b), (double*)(tmp + up_b), f->raw, f->packed, p, s);
         if (!rb.empty()) {
           f->rpacked = (double*)(f->packed + align256(L.pack_bytes));
-          f->defects = f->rpacked + real_elems;
-          launch_pack_herm((const RealPackDev*)(tmp + ops_b + blk_b), nblk, f->raw, f->rpacked, f->defects, s);
+          launch_pack_herm((const RealPackDev*)(tmp + ops_b + blk_b), nblk, f->raw, f->rpacked, s);
         }
         TANQ_HIP(hipStreamSynchronize(s));  // `up` is read by the copy
       } catch (...) {
@@ -1070,7 +1068,7 @@ tanq_status tanq_apply_fused_range(tanq_dm d, tanq_fused f, int begin, int end) 
       i += m;
     }
     for (; rg; next_real()) launch_pass_either(d->ptr, nullptr, nullptr, rg, rpacked, flag, d->stream);
-    if (real) launch_herm_out(d->ptr, d->n, f->defects + begin, f->defects + end, flag, d->stream);
+    if (real) launch_herm_out(d->ptr, d->n, flag, d->stream);
   });
 }
 

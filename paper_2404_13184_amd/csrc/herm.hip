@@ -1,4 +1,4 @@
-// Long fused lists on Hermitian FP64 states, in real (Pauli) form (real.hpp): vec(rho) is checked,
+// Long fused lists on Hermitian FP64 states, in real form (real.hpp): vec(rho) is checked,
 // transformed in place to 4^n reals in the lower half of its memory, multiplied there, and
 // transformed back.  A pass over the state then moves half the bytes and executes a third of the
 // products of the 3M form.
@@ -10,10 +10,11 @@
 //
 // The transform.  X = Re rho + Im rho is a real matrix that determines a Hermitian rho (Re is its
 // symmetric part, Im its antisymmetric one), and the real form is the per-qubit butterfly of X,
-// (x00, x11) and (x10, x01) -> (sum, difference), up to a sign: of the two parts of each expectation
-// the butterflies of Re and Im give, one is zero, and (-i)^y takes the other to
-// Tr(P rho) up to (-1) when y mod 4 is 2 or 3.  The inverse is the same butterfly halved.  Sums of
-// exactly Hermitian input are exactly real, and the way back gives an exactly Hermitian matrix.
+// (x10, x01) -> half of (sum, difference) and x00, x11 as they are, up to a sign: of the two parts of each
+// coefficient the butterflies of Re and Im give, one is zero, and (-i)^y takes the other to the coefficient up
+// to (-1) when y mod 4 is 2 or 3 (y: the number of Y).  The inverse is (sum, difference).  Populations pass
+// through unchanged, sums of exactly Hermitian input are exactly real, and the way back gives an exactly
+// Hermitian matrix.
 // The first step of the way in compacts (two complex elements that differ in the top column bit become
 // one 16-byte pair of reals in the place of the lower one) on the qubits 0-4 and n - 1, which hold
 // that bit and whole 128-byte lines; the others take up to five qubits each.  Way in and out together
@@ -24,7 +25,7 @@ namespace tanq {
 
 namespace {
 
-// Entries beyond this could overflow in sums of 4^16 of them; such a state keeps the complex form.
+// Entries beyond this could overflow where they are added; such a state keeps the complex form.
 constexpr double kHermRange = 1e280;
 
 __device__ inline bool flag_set(const uint32_t* flag) { return __builtin_amdgcn_readfirstlane((int)*flag) != 0; }
@@ -69,20 +70,18 @@ __global__ __launch_bounds__(256) void herm_check_kernel(const f64x2* __restrict
   }
 }
 
-// Butterflies of two qubits on 16 tile elements in registers: x[l], l = bits of (p0, p1, p2, p3) with
-// qubit A on bits 0 (row) and 1 (column), qubit B on bits 2 and 3.
-__device__ inline void butterfly4(double& x00, double& x10, double& x01, double& x11) {
-  const double i = x00 + x11, z = x00 - x11, x = x10 + x01, y = x10 - x01;
-  x00 = i;
-  x11 = z;
-  x10 = x;
-  x01 = y;
+// One qubit's butterfly; INV: on the way back.
+template <bool INV>
+__device__ inline void butterfly2(double& x10, double& x01) {
+  const double x = x10 + x01, y = x10 - x01;
+  x10 = INV ? x : 0.5 * x;
+  x01 = INV ? y : 0.5 * y;
 }
 
 // One or two qubits' butterflies on the tile in LDS: each group of 16 (or 4) elements by one thread.
 // ra, ca, rb, cb: tile bits of the row and column bit of qubit A and B (rb < 0: one qubit).  ph: LDS
 // place of a tile element, linear over GF(2), against bank conflicts.
-template <int V, int NT, typename Ph>
+template <bool INV, int V, int NT, typename Ph>
 __device__ inline void tile_butterflies(double* t, int ra, int ca, int rb, int cb, int tid, Ph ph) {
   const uint32_t pra = ph(1u << ra), pca = ph(1u << ca);
   if (rb >= 0) {
@@ -90,14 +89,14 @@ __device__ inline void tile_butterflies(double* t, int ra, int ca, int rb, int c
     const uint32_t fm = ((1u << V) - 1u) & ~((1u << ra) | (1u << ca) | (1u << rb) | (1u << cb));
     for (int g = tid; g < (1 << (V - 4)); g += NT) {
       const uint32_t base = ph(pdep32((uint32_t)g, fm));
-      double x[16];
+      double x[16];  // l: bits of (row A, column A, row B, column B)
 #pragma unroll
       for (int l = 0; l < 16; ++l)
         x[l] = t[base ^ ((l & 1) ? pra : 0u) ^ ((l & 2) ? pca : 0u) ^ ((l & 4) ? prb : 0u) ^ ((l & 8) ? pcb : 0u)];
 #pragma unroll
-      for (int h = 0; h < 4; ++h) butterfly4(x[4 * h], x[4 * h + 1], x[4 * h + 2], x[4 * h + 3]);
+      for (int h = 0; h < 4; ++h) butterfly2<INV>(x[4 * h + 1], x[4 * h + 2]);
 #pragma unroll
-      for (int h = 0; h < 4; ++h) butterfly4(x[h], x[h + 4], x[h + 8], x[h + 12]);
+      for (int h = 0; h < 4; ++h) butterfly2<INV>(x[h + 4], x[h + 8]);
 #pragma unroll
       for (int l = 0; l < 16; ++l)
         t[base ^ ((l & 1) ? pra : 0u) ^ ((l & 2) ? pca : 0u) ^ ((l & 4) ? prb : 0u) ^ ((l & 8) ? pcb : 0u)] = x[l];
@@ -106,7 +105,7 @@ __device__ inline void tile_butterflies(double* t, int ra, int ca, int rb, int c
     const uint32_t fm = ((1u << V) - 1u) & ~((1u << ra) | (1u << ca));
     for (int g = tid; g < (1 << (V - 2)); g += NT) {
       const uint32_t e = ph(pdep32((uint32_t)g, fm));
-      butterfly4(t[e], t[e ^ pra], t[e ^ pca], t[e ^ pra ^ pca]);
+      butterfly2<INV>(t[e ^ pra], t[e ^ pca]);
     }
   }
 }
@@ -126,13 +125,14 @@ __device__ inline uint64_t edge_base(uint32_t ro, uint32_t co, int n) {
 // tile bits 7-9 go to bank bits 0-2 and 5-6 to 3-4, so that the lanes of the first butterflies (on tile
 // bits 0, 1, 5, 6) fall on distinct banks
 __device__ inline uint32_t edge_place(uint32_t e) { return e ^ ((e >> 7) & 7u) ^ (((e >> 5) & 3u) << 3); }
+template <bool INV>
 __device__ inline void edge_butterflies(double* t, int tid) {
   auto ph = [](uint32_t e) { return edge_place(e); };
-  tile_butterflies<kEdgeV, kEdgeNT>(t, 0, 5, 1, 6, tid, ph);
+  tile_butterflies<INV, kEdgeV, kEdgeNT>(t, 0, 5, 1, 6, tid, ph);
   __syncthreads();
-  tile_butterflies<kEdgeV, kEdgeNT>(t, 2, 7, 3, 8, tid, ph);
+  tile_butterflies<INV, kEdgeV, kEdgeNT>(t, 2, 7, 3, 8, tid, ph);
   __syncthreads();
-  tile_butterflies<kEdgeV, kEdgeNT>(t, 4, 9, 10, 11, tid, ph);
+  tile_butterflies<INV, kEdgeV, kEdgeNT>(t, 4, 9, 10, 11, tid, ph);
   __syncthreads();
 }
 
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kEdgeNT) void herm_in_kernel(f64x2* __restrict__ rh
 #pragma unroll
     for (int u = 0; u < 8; ++u) t[edge_place((uint32_t)(u * kEdgeNT + tid))] = v[u][0] + v[u][1];
     __syncthreads();
-    edge_butterflies(t, tid);
+    edge_butterflies<false>(t, tid);
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const uint32_t e = (uint32_t)(u * kEdgeNT + tid);  // top column bit 0
@@ -163,15 +163,12 @@ __global__ __launch_bounds__(kEdgeNT) void herm_in_kernel(f64x2* __restrict__ rh
 // The last step of the way back: a tile and its mirror image (rows and columns of the outside bits
 // exchanged) together, since rho[r][c] takes X[r][c] and X[c][r].
 __global__ __launch_bounds__(kEdgeNT) void herm_out_kernel(f64x2* __restrict__ rho, int n,
-                                                           const double* __restrict__ from,
-                                                           const double* __restrict__ to, const uint32_t* flag) {
+                                                           const uint32_t* flag) {
   __shared__ double t[2][1 << kEdgeV];
   if (!flag_set(flag)) return;
   const int tid = threadIdx.x;
   const int no = n - 6;
   const uint64_t ntiles = 1ull << (2 * no);
-  // the halves of n butterflies and of X +- X^T, and the operands' common factor
-  const double scale = (1.0 + (to[0] - from[0])) * (0.5 / (double)(1ull << n));
   for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
     const uint32_t ro = (uint32_t)(tile & ((1u << no) - 1u)), co = (uint32_t)(tile >> no);
     if (ro > co) continue;  // done with its mirror image
@@ -189,7 +186,7 @@ __global__ __launch_bounds__(kEdgeNT) void herm_out_kernel(f64x2* __restrict__ r
       }
     }
     __syncthreads();
-    for (int s = 0; s < sides; ++s) edge_butterflies(t[s], tid);
+    for (int s = 0; s < sides; ++s) edge_butterflies<true>(t[s], tid);
     for (int s = 0; s < sides; ++s) {
       const double* a = t[s];
       const double* b = t[sides == 2 ? s ^ 1 : 0];
@@ -199,7 +196,7 @@ __global__ __launch_bounds__(kEdgeNT) void herm_out_kernel(f64x2* __restrict__ r
         // rows and columns exchanged inside the tile
         const uint32_t m = ((e & 31u) << 5) | ((e >> 5) & 31u) | ((e & 1024u) << 1) | ((e & 2048u) >> 1);
         const double x = a[edge_place(e)], y = b[edge_place(m)];
-        __builtin_nontemporal_store(f64x2{(x + y) * scale, (x - y) * scale}, rho + base[s] + edge_off(e, n));
+        __builtin_nontemporal_store(f64x2{0.5 * (x + y), 0.5 * (x - y)}, rho + base[s] + edge_off(e, n));
       }
     }
     __syncthreads();
@@ -211,7 +208,8 @@ __global__ __launch_bounds__(kEdgeNT) void herm_out_kernel(f64x2* __restrict__ r
 // whole 128-byte lines (with tiles of 2^13 the five-qubit steps at 16 qubits ran on half lines: 25 ms
 // each instead of 13).  128 KiB of LDS, one workgroup of 16 waves per CU; the next tile is prefetched into
 // registers.  Bound by memory: one read and one write of the reals.  sign: the factor -1 of
-// the elements with y mod 4 in {2, 3} -- 1: after (the last step in), 2: before (the first step out).
+// the elements with y mod 4 in {2, 3} -- 1: after (the last step in), 2: before (the first step out).  INV: a step
+// of the way back.
 constexpr int kMidBits = 14, kMidNT = 1024;
 struct HermMid {
   uint64_t dmask;     // address bits outside the tile
@@ -221,6 +219,7 @@ struct HermMid {
   int32_t n, nq, sign;
 };
 
+template <bool INV>
 __global__ __launch_bounds__(kMidNT) void herm_mid_kernel(double* __restrict__ w, const HermMid g, const uint32_t* flag) {
   constexpr int V = kMidBits, NT = kMidNT, IT = (1 << V) / 2 / NT;
   __shared__ f64x2 t2[(1 << V) / 2];
@@ -269,7 +268,7 @@ __global__ __launch_bounds__(kMidNT) void herm_mid_kernel(double* __restrict__ w
     }
     for (int q = 0; q < g.nq; q += 2) {
       const bool two = q + 1 < g.nq;
-      tile_butterflies<V, NT>(t, g.rbit[q], g.cbit[q], two ? g.rbit[q + 1] : -1, two ? g.cbit[q + 1] : -1, tid, ph);
+      tile_butterflies<INV, V, NT>(t, g.rbit[q], g.cbit[q], two ? g.rbit[q + 1] : -1, two ? g.cbit[q + 1] : -1, tid, ph);
       lds_barrier();
     }
 #pragma unroll
@@ -319,8 +318,7 @@ __global__ __launch_bounds__(256, 2) void real_apply3_kernel(double* __restrict_
 // ------------------------------------------------------------------------------------
 
 __global__ __launch_bounds__(256) void pack_herm_kernel(const RealPackDev* __restrict__ blocks,
-                                                        const double* __restrict__ raw, double* __restrict__ packed,
-                                                        double* __restrict__ defects) {
+                                                        const double* __restrict__ raw, double* __restrict__ packed) {
   const RealPackDev b = blocks[blockIdx.x];
   const f64x2* S = reinterpret_cast<const f64x2*>(raw + 2 * b.raw_off);
   double* P = packed + b.pack_off;
@@ -330,32 +328,10 @@ __global__ __launch_bounds__(256) void pack_herm_kernel(const RealPackDev* __res
     for (int t = 0; t < 2 * b.k; ++t) r |= (uint32_t)((x >> t) & 1) << b.perm[t];
     return r;
   };
-  double hi, lo;
-  real_entry(S, b.k, 0, 0, &hi, &lo);
-  const double d = real_defect(hi);
-  if (threadIdx.x == 0) defects[blockIdx.x + 1] = d;
   for (int e = threadIdx.x; e < D * D; e += blockDim.x) {
     int row = e / D, col = e % D;
     if (b.k > 1) real_frag_index<double>(e, D / 4, &row, &col);
-    real_entry(S, b.k, local(row), local(col), &hi, &lo);
-    P[e] = real_operand(hi, lo, d, row == col, row + col == 0);
-  }
-}
-
-// prefix sums of the blocks' defects, in place, by one wave
-__global__ void herm_defects_kernel(double* __restrict__ t, int n) {
-  const int lane = threadIdx.x;
-  double run = 0.0;
-  if (lane == 0) t[0] = 0.0;
-  for (int i0 = 0; i0 < n; i0 += 64) {
-    double v = i0 + lane < n ? t[1 + i0 + lane] : 0.0;
-    for (int o = 1; o < 64; o <<= 1) {
-      const double u = __shfl_up(v, o, 64);
-      if (lane >= o) v += u;
-    }
-    v += run;
-    if (i0 + lane < n) t[1 + i0 + lane] = v;
-    run = __shfl(v, 63, 64);
+    P[e] = real_entry(S, b.k, local(row), local(col));
   }
 }
 
@@ -363,12 +339,9 @@ __global__ void herm_defects_kernel(double* __restrict__ t, int n) {
 // host side
 // ------------------------------------------------------------------------------------
 
-void launch_pack_herm(const RealPackDev* blocks, int nblocks, const double* raw, double* packed, double* defects,
-                      hipStream_t s) {
+void launch_pack_herm(const RealPackDev* blocks, int nblocks, const double* raw, double* packed, hipStream_t s) {
   if (nblocks <= 0) return;
-  hipLaunchKernelGGL(pack_herm_kernel, dim3(nblocks), dim3(256), 0, s, blocks, raw, packed, defects);
-  TANQ_HIP(hipGetLastError());
-  hipLaunchKernelGGL(herm_defects_kernel, dim3(1), dim3(64), 0, s, defects, nblocks);
+  hipLaunchKernelGGL(pack_herm_kernel, dim3(nblocks), dim3(256), 0, s, blocks, raw, packed);
   TANQ_HIP(hipGetLastError());
 }
 
@@ -386,6 +359,7 @@ void launch_herm_check(const void* rho, int n, uint32_t* flag, hipStream_t s) {
   TANQ_HIP(hipGetLastError());
 }
 
+template <bool INV>
 static void launch_herm_mid(void* rho, int n, int q0, int nq, int sign, const uint32_t* flag, hipStream_t s) {
   HermMid g{};
   g.n = n;
@@ -406,7 +380,7 @@ static void launch_herm_mid(void* rho, int n, int q0, int nq, int sign, const ui
   }
   g.dmask = ((1ull << (2 * n)) - 1ull) & ~held;
   g.ntiles = 1ull << (2 * n - kMidBits);
-  hipLaunchKernelGGL(herm_mid_kernel, dim3(herm_grid(g.ntiles, 1)), dim3(kMidNT), 0, s, (double*)rho, g, flag);
+  hipLaunchKernelGGL(herm_mid_kernel<INV>, dim3(herm_grid(g.ntiles, 1)), dim3(kMidNT), 0, s, (double*)rho, g, flag);
   TANQ_HIP(hipGetLastError());
 }
 
@@ -419,20 +393,20 @@ void launch_herm_in(void* rho, int n, const uint32_t* flag, hipStream_t s) {
   const int steps = herm_steps(n), total = n - 6;
   for (int i = 0, q = 5; i < steps; ++i) {
     const int nq = total / steps + (i < total % steps ? 1 : 0);
-    launch_herm_mid(rho, n, q, nq, i + 1 == steps ? 1 : 0, flag, s);
+    launch_herm_mid<false>(rho, n, q, nq, i + 1 == steps ? 1 : 0, flag, s);
     q += nq;
   }
 }
 
-void launch_herm_out(void* rho, int n, const double* from, const double* to, const uint32_t* flag, hipStream_t s) {
+void launch_herm_out(void* rho, int n, const uint32_t* flag, hipStream_t s) {
   const int steps = herm_steps(n), total = n - 6;
   for (int i = 0, q = 5; i < steps; ++i) {
     const int nq = total / steps + (i < total % steps ? 1 : 0);
-    launch_herm_mid(rho, n, q, nq, i == 0 ? 2 : 0, flag, s);
+    launch_herm_mid<true>(rho, n, q, nq, i == 0 ? 2 : 0, flag, s);
     q += nq;
   }
   hipLaunchKernelGGL(herm_out_kernel, dim3(herm_grid(1ull << (2 * (n - 6)), 2)), dim3(kEdgeNT), 0, s, (f64x2*)rho, n,
-                     from, to, flag);
+                     flag);
   TANQ_HIP(hipGetLastError());
 }
 

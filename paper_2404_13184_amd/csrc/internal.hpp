@@ -253,15 +253,12 @@ struct RealPackDev {
   int32_t k;
   uint8_t perm[8];   // local bit of the real operand -> local bit of the superoperator
 };
-// defects[b] = the sum of the operands' factor defects (real_operand) over the blocks before b (nblocks + 1 values)
-void launch_pack_herm(const RealPackDev* blocks, int nblocks, const double* raw, double* packed, double* defects,
-                      hipStream_t s);
+void launch_pack_herm(const RealPackDev* blocks, int nblocks, const double* raw, double* packed, hipStream_t s);
 // *flag = 1 if vec(rho) is exactly Hermitian and within range, else 0
 void launch_herm_check(const void* rho, int n, uint32_t* flag, hipStream_t s);
 // vec(rho) -> real form and back in place; nothing where *flag is 0
 void launch_herm_in(void* rho, int n, const uint32_t* flag, hipStream_t s);
-// from, to: entries of the defect table around the blocks that were applied (device)
-void launch_herm_out(void* rho, int n, const double* from, const double* to, const uint32_t* flag, hipStream_t s);
+void launch_herm_out(void* rho, int n, const uint32_t* flag, hipStream_t s);
 void launch_real_apply3(void* rho, int n, const int* qubits, const double* packed, const uint32_t* flag, hipStream_t s);
 
 void launch_init_zero(void* rho, int n, tanq_prec p, hipStream_t s);
@@ -299,8 +296,8 @@ void launch_pack_one(int k, const double* raw, void* packed, tanq_prec p, hipStr
 // A one-qubit superoperator (host, 4 x 4 complex) that travels with the launch.
 void launch_apply_one_qubit(void* rho, int n, tanq_prec p, int qubit, const double* S, hipStream_t s);
 
-// Real form (real.hip).  Superoperators of every operation as real 4^j x 4^j matrices minus the identity (offset
-// sop_off, in doubles), their composition per block in circuit order, packed as the real apply kernels'
+// Real form (real.hip).  Superoperators of every operation as real 4^j x 4^j matrices (offset sop_off, in
+// doubles), their composition per block in circuit order, packed as the real apply kernels'
 // operands; FP64, rounded once.  Every block has k qubits (2 or 3).
 void launch_build_real(const FuseOpDev* ops, int nops, const double* kraus, double* sops, hipStream_t s);
 void launch_compose_real(const FuseBlockDev* blocks, int nblocks, int k, const FuseOpDev* ops, const double* sops,
@@ -309,11 +306,10 @@ void launch_compose_real(const FuseBlockDev* blocks, int nblocks, int k, const F
 void launch_real_init(void* w, int n, tanq_prec p, hipStream_t s);
 // Outputs of a state in real form, n <= kRealOutMaxN: out[0] = the trace, then the 2^n probabilities
 // divided by it if want_probs, then (Re, Im) of count Pauli expectations (masks: x, z, #Y mod 4 per
-// string, as launch_pauli).  masks and out are device-accessible (pinned host memory).  packed: the operands
-// of the nblocks k-qubit blocks that were applied (their common factor is the outputs').
+// string, as launch_pauli).  masks and out are device-accessible (pinned host memory).
 constexpr int kRealOutMaxN = 14;
-void launch_real_outputs(const void* w, int n, tanq_prec p, int want_probs, int count, const uint64_t* masks,
-                         const void* packed, int k, size_t stride_bytes, int nblocks, double* out, hipStream_t s);
+void launch_real_outputs(const void* w, int n, tanq_prec p, int want_probs, int count, const uint64_t* masks, double* out,
+                         hipStream_t s);
 
 // Measurement statistics (measure.hip; FP64).  partials: device scratch of at least reduce_partials() doubles;
 // probs_dev: of 2^n doubles.  Outputs (out, trace, masks) are device-accessible: device memory or

@@ -1,18 +1,10 @@
-// Kernels of the real (Pauli) form (real.hpp): operands, initial state and outputs.
-//
-// The form's basis change per qubit is a butterfly of (rho_00, rho_11) and (rho_10, rho_01), so a
-// superoperator S becomes R[a][b] = Re((-i)^(y_a - y_b) 2^-k sum_{u,v} (-1)^(u.c_a + v.c_b)
-// S[i(a,u)][i(b,v)]), i(a, u) = (u ^ r_a ^ c_a) + 2^k u, where (r, c) are a local index's row and
-// column halves and y = popcount(~r & c).  For S = sum_i conj(K_i) (x) K_i the imaginary part of
-// that expression is zero.  R is kept as E = R - I throughout: its first row, (1, 0, .., 0) but for
-// rounding, would otherwise lose the rounding of the Kraus sets that the complex form carries along
-// (errors of 5e-14 on repeated layers instead of 1e-15).
+// Kernels of the real form (real.hpp): operands, initial state and outputs.
 #include "compose.hpp"
 #include "real.hpp"
 
 namespace tanq {
 
-// One workgroup per operation: S in LDS, then E = R - I.
+// One workgroup per operation: S in LDS, then R.
 __global__ __launch_bounds__(256) void build_real_kernel(const FuseOpDev* __restrict__ ops,
                                                          const double* __restrict__ kraus, double* __restrict__ sops) {
   __shared__ f64x2 S[64 * 64];
@@ -33,18 +25,14 @@ __global__ __launch_bounds__(256) void build_real_kernel(const FuseOpDev* __rest
     S[e] = f64x2{sr, si};
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < dd * dd; e += blockDim.x) {
-    double hi, lo;
-    real_entry(S, j, (uint32_t)(e / dd), (uint32_t)(e % dd), &hi, &lo);
-    sops[op.sop_off + e] = hi;
-  }
+  for (int e = threadIdx.x; e < dd * dd; e += blockDim.x)
+    sops[op.sop_off + e] = real_entry(S, j, (uint32_t)(e / dd), (uint32_t)(e % dd));
 }
 
-// One workgroup per block: M <- (I + E_op)(embedded) M in circuit order from M = I, kept as N = M - I (N <- N +
-// E_op (I + N)), out of place between two LDS buffers (one barrier per operation), then the operand
-// (real_operand) and, after its 4^2k elements, its factor's defect d.  Thread t works on column
-// t % D; the 256 / D threads of a column share its groups and outputs.  The chain over a block's operations
-// is serial: ComposeFeed keeps it from waiting for memory.
+// One workgroup per block: M <- R_op(embedded) M in circuit order from M = I, out of place between two LDS buffers (one
+// barrier per operation), then the operand's fragments.  Thread t works on column t % D; the 256 / D threads of a
+// column share its groups and outputs.  The chain over a block's operations is serial: ComposeFeed keeps it from
+// waiting for memory.
 template <typename T, int K>
 __global__ __launch_bounds__(256) void compose_real_kernel(const FuseBlockDev* __restrict__ blocks,
                                                            const FuseOpDev* __restrict__ ops,
@@ -55,7 +43,7 @@ __global__ __launch_bounds__(256) void compose_real_kernel(const FuseBlockDev* _
   __shared__ typename ComposeFeed<double>::Lds fl;
   const FuseBlockDev blk = blocks[blockIdx.x];
   const int tid = threadIdx.x, c = tid % D, slot = tid / D;
-  for (int e = tid; e < D * D; e += 256) M[0][e] = 0.0;
+  for (int e = tid; e < D * D; e += 256) M[0][e] = e / D == e % D ? 1.0 : 0.0;
   ComposeFeed<double> feed(fl, ops + blk.op_begin, sops, blk.op_count);
   feed.start();
   int cur = 0;
@@ -82,27 +70,26 @@ __global__ __launch_bounds__(256) void compose_real_kernel(const FuseBlockDev* _
       return r;
     };
     const uint32_t fm = (uint32_t)(D - 1) & ~tmask;
-    auto full = [&](uint32_t row) { return X[row * D + c] + ((int)row == c ? 1.0 : 0.0); };  // (I + N)[row][c]
     if (j == 1) {
       if constexpr (K == 2) {  // one output each: group slot / 4, output slot % 4
         const uint32_t base = pdep32((uint32_t)(slot >> 2), fm);
         const int a = slot & 3;
         double y = 0.0;
 #pragma unroll
-        for (int b = 0; b < 4; ++b) y += S[a * 4 + b] * full(base | dep(b));
-        Y[(base | dep(a)) * D + c] = X[(base | dep(a)) * D + c] + y;
+        for (int b = 0; b < 4; ++b) y += S[a * 4 + b] * X[(base | dep(b)) * D + c];
+        Y[(base | dep(a)) * D + c] = y;
       } else {
         for (int g = slot; g < D / 4; g += SLOTS) {
           const uint32_t base = pdep32((uint32_t)g, fm);
           double x[4];
 #pragma unroll
-          for (int b = 0; b < 4; ++b) x[b] = full(base | dep(b));
+          for (int b = 0; b < 4; ++b) x[b] = X[(base | dep(b)) * D + c];
 #pragma unroll
           for (int a = 0; a < 4; ++a) {
             double y = 0.0;
 #pragma unroll
             for (int b = 0; b < 4; ++b) y += S[a * 4 + b] * x[b];
-            Y[(base | dep(a)) * D + c] = X[(base | dep(a)) * D + c] + y;
+            Y[(base | dep(a)) * D + c] = y;
           }
         }
       }
@@ -110,90 +97,93 @@ __global__ __launch_bounds__(256) void compose_real_kernel(const FuseBlockDev* _
       if constexpr (K == 2) {  // one group; one output each
         double y = 0.0;
 #pragma unroll
-        for (int b = 0; b < 16; ++b) y += S[slot * 16 + b] * full(dep(b));
-        Y[dep(slot) * D + c] = X[dep(slot) * D + c] + y;
+        for (int b = 0; b < 16; ++b) y += S[slot * 16 + b] * X[dep(b) * D + c];
+        Y[dep(slot) * D + c] = y;
       } else {  // one group each, all its outputs
         const uint32_t base = pdep32((uint32_t)slot, fm);
         double x[16];
 #pragma unroll
-        for (int b = 0; b < 16; ++b) x[b] = full(base | dep(b));
+        for (int b = 0; b < 16; ++b) x[b] = X[(base | dep(b)) * D + c];
 #pragma unroll 4
         for (int a = 0; a < 16; ++a) {
           double y = 0.0;
 #pragma unroll
           for (int b = 0; b < 16; ++b) y += S[a * 16 + b] * x[b];
-          Y[(base | dep(a)) * D + c] = X[(base | dep(a)) * D + c] + y;
+          Y[(base | dep(a)) * D + c] = y;
         }
       }
     } else if constexpr (K == 3) {
       const double* Sg = sops + op.sop_off;
       for (int a = slot; a < D; a += SLOTS) {
         double y = 0.0;
-        for (int b = 0; b < D; ++b) y += Sg[a * D + b] * full(dep(b));
-        Y[dep(a) * D + c] = X[dep(a) * D + c] + y;
+        for (int b = 0; b < D; ++b) y += Sg[a * D + b] * X[dep(b) * D + c];
+        Y[dep(a) * D + c] = y;
       }
     }
     feed.next(oi);
     cur ^= 1;
   }
   T* P = reinterpret_cast<T*>(packed + blk.pack_off);
-  const double d = real_defect(M[cur][0]);
   for (int e = tid; e < D * D; e += 256) {
     int row, col;
     real_frag_index<T>(e, D / 4, &row, &col);
-    P[e] = (T)real_operand(M[cur][row * D + col], 0.0, d, row == col, row + col == 0);
+    P[e] = (T)M[cur][row * D + col];
   }
-  if (tid == 0) P[D * D] = (T)d;
 }
 
-// |0..0><0..0| has expectation 1 for every string of I and Z (r' = c') and 0 for the others.
+// |0..0><0..0| is an element of the basis.
 template <typename T>
 __global__ void real_init_kernel(T* __restrict__ w, int n) {
-  const uint64_t nel = 1ull << (2 * n), dim = 1ull << n;
+  const uint64_t nel = 1ull << (2 * n);
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nel; i += (uint64_t)gridDim.x * blockDim.x)
-    w[i] = (i & (dim - 1)) == (i >> n) ? T(1) : T(0);
+    w[i] = i == 0 ? T(1) : T(0);
 }
 
-// One workgroup: p_x = 2^-n sum_z (-1)^(x.z) w[z, z] is a Walsh-Hadamard transform of the diagonal (in
-// LDS, FP64); every other output is one element of w.
-template <typename T, int NMAX>
-__global__ __launch_bounds__(1024) void real_outputs_kernel(const T* __restrict__ w, int n, int want_probs, int count,
-                                                            const uint64_t* __restrict__ masks, const T* __restrict__ defects,
-                                                            int stride, int nblocks, double* __restrict__ out) {
-  __shared__ double p[1 << NMAX];
+// Workgroup 0: the trace and the probabilities, which are coefficients.  Workgroup 1 + i: string i, which is non-zero on
+// the basis elements with X and Y where it has them: Tr(P B) = 2 on those qubits and +-1 (Z) or 1 on the
+// populations of the others.
+template <typename T>
+__global__ __launch_bounds__(1024) void real_outputs_kernel(const T* __restrict__ w, int n, int want_probs,
+                                                            const uint64_t* __restrict__ masks, double* __restrict__ out) {
+  constexpr int PER = 1 << (kRealOutMaxN - 10);  // values of a thread
   __shared__ double part[16];
   const uint32_t dim = 1u << n;
-  // the common factor of the applied operands: the product of 1 + d, d below 1e-9
-  double f = 0.0;
-  for (int i = threadIdx.x; i < nblocks; i += 1024) f += (double)defects[(size_t)i * stride];
-  for (int o = 32; o > 0; o >>= 1) f += __shfl_down(f, o, 64);
-  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = f;
-  __syncthreads();
-  f = 1.0;
-  for (int i = 0; i < 16; ++i) f += part[i];
-  const double tr = (double)w[0] * f;
-  if (threadIdx.x == 0) out[0] = tr;
-  double* res = out + 1;
-  if (want_probs) {
-    for (uint32_t z = threadIdx.x; z < dim; z += 1024) p[z] = (double)w[z + ((uint64_t)z << n)];
-    __syncthreads();
-    for (int t = 0; t < n; ++t) {
-      for (uint32_t i = threadIdx.x; i < dim / 2; i += 1024) {
-        const uint32_t lo = i & ((1u << t) - 1u), x0 = ((i >> t) << (t + 1)) | lo, x1 = x0 | (1u << t);
-        const double a = p[x0], b = p[x1];
-        p[x0] = a + b;
-        p[x1] = a - b;
-      }
-      __syncthreads();
+  const bool string = blockIdx.x > 0;
+  const uint32_t xm = string ? (uint32_t)masks[3 * (blockIdx.x - 1)] : 0u;
+  const uint32_t zm = string ? (uint32_t)masks[3 * (blockIdx.x - 1) + 1] : 0u;
+  const uint32_t free = (dim - 1u) & ~xm, count = dim >> __popc(xm);
+  const uint64_t at = (uint64_t)(xm & ~zm) + ((uint64_t)(xm & zm) << n);
+  double v[PER], acc = 0.0;
+#pragma unroll
+  for (int u = 0; u < PER; ++u) {
+    const uint32_t i = u * 1024 + threadIdx.x;
+    v[u] = 0.0;
+    if (i < count) {
+      const uint32_t x = pdep32(i, free);
+      const double e = (double)w[at + x + ((uint64_t)x << n)];
+      v[u] = (__popc(x & zm) & 1) ? -e : e;
     }
-    const double inv = 1.0 / tr, scale = f / (double)dim;
-    for (uint32_t x = threadIdx.x; x < dim; x += 1024) res[x] = (p[x] * scale) * inv;
-    res += dim;
+    acc += v[u];
   }
-  for (int i = threadIdx.x; i < count; i += 1024) {
-    const uint64_t xm = masks[3 * i], zm = masks[3 * i + 1];
-    res[2 * i] = (double)w[(xm ^ zm) + (zm << n)] * f;
-    res[2 * i + 1] = 0.0;  // rho is Hermitian
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
+  __syncthreads();
+  acc = 0.0;
+  for (int i = 0; i < 16; ++i) acc += part[i];
+  if (string) {
+    double* res = out + 1 + (want_probs ? dim : 0u) + 2 * (blockIdx.x - 1);
+    if (threadIdx.x == 0) {
+      res[0] = acc * (double)(1u << __popc(xm));
+      res[1] = 0.0;  // rho is Hermitian
+    }
+    return;
+  }
+  if (threadIdx.x == 0) out[0] = acc;
+  if (want_probs) {
+    const double inv = 1.0 / acc;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (u * 1024 + threadIdx.x < dim) out[1 + u * 1024 + threadIdx.x] = v[u] * inv;
   }
 }
 
@@ -308,29 +298,16 @@ void launch_real_init(void* w, int n, tanq_prec p, hipStream_t s) {
   TANQ_HIP(hipGetLastError());
 }
 
-template <typename T>
-static void real_outputs_typed(const void* w, int n, int want_probs, int count, const uint64_t* masks,
-                               const T* defects, int stride, int nblocks, double* out, hipStream_t s) {
-  // two LDS sizes: up to 12 qubits (32 KiB) and up to 14 (128 KiB)
-  if (n <= 12)
-    hipLaunchKernelGGL((real_outputs_kernel<T, 12>), dim3(1), dim3(1024), 0, s, (const T*)w, n, want_probs, count,
-                       masks, defects, stride, nblocks, out);
-  else
-    hipLaunchKernelGGL((real_outputs_kernel<T, kRealOutMaxN>), dim3(1), dim3(1024), 0, s, (const T*)w, n, want_probs,
-                       count, masks, defects, stride, nblocks, out);
-  TANQ_HIP(hipGetLastError());
-}
-
-void launch_real_outputs(const void* w, int n, tanq_prec p, int want_probs, int count, const uint64_t* masks,
-                         const void* packed, int k, size_t stride_bytes, int nblocks, double* out, hipStream_t s) {
+void launch_real_outputs(const void* w, int n, tanq_prec p, int want_probs, int count, const uint64_t* masks, double* out,
+                         hipStream_t s) {
   if (n > kRealOutMaxN) fail(TANQ_E_ARG, "outputs of a real-form state: too many qubits");
-  const int d = 1 << (4 * k);  // a block's defect follows its operand
   if (p == TANQ_F64)
-    real_outputs_typed<double>(w, n, want_probs, count, masks, (const double*)packed + d,
-                               (int)(stride_bytes / sizeof(double)), nblocks, out, s);
+    hipLaunchKernelGGL(real_outputs_kernel<double>, dim3(1 + count), dim3(1024), 0, s, (const double*)w, n, want_probs,
+                       masks, out);
   else
-    real_outputs_typed<float>(w, n, want_probs, count, masks, (const float*)packed + d,
-                              (int)(stride_bytes / sizeof(float)), nblocks, out, s);
+    hipLaunchKernelGGL(real_outputs_kernel<float>, dim3(1 + count), dim3(1024), 0, s, (const float*)w, n, want_probs,
+                       masks, out);
+  TANQ_HIP(hipGetLastError());
 }
 
 }  // namespace tanq

@@ -1,14 +1,21 @@
-// Real (Pauli) form of Hermitian states, shared by the serving kernels and the Hermitian passes
-// (gfx950).
+// Real form of Hermitian states, shared by the serving kernels and the Hermitian passes (gfx950).
 //
-// A Hermitian rho of n qubits is 4^n real numbers: w[r' + c' 2^n] = Tr(P rho) for the Pauli string
-// whose character on qubit t is I, X, Y or Z for (r'_t, c'_t) = (0,0), (1,0), (0,1), (1,1).  In
-// terms of vec(rho)
-//   w[r', c'] = (-i)^{y} sum_u (-1)^{u . c'} rho[u ^ r' ^ c'][u],   y = popcount(~r' & c'),
-// which factorises over the qubits, so a map on k qubits acts on the same 2k index bits as in
+// A Hermitian rho of n qubits is 4^n real numbers, its coefficients over the products of the one-qubit
+// matrices |0><0|, |1><1|, X and Y:
+//   rho = sum w[r' + c' 2^n] B,  qubit t of B being |0><0|, X, Y or |1><1| for (r'_t, c'_t) = (0,0),
+//   (1,0), (0,1) or (1,1).
+// The basis factorises over the qubits, so a map on k qubits acts on the same 2k index bits as in
 // vec(rho), and a map that keeps Hermiticity (every Kraus set does) is a real 4^k x 4^k matrix R.
 // Against vec(rho) that is half the bytes and, per superoperator, one real product in place of
 // the three of the 3M form.  Everything stays in the precision of the state.
+//
+// The populations rho[x][x] are coefficients themselves (r' = c' = x), and R takes populations to
+// populations by the superoperator's own entries.  So rare outcomes keep their relative accuracy and
+// outcomes that cannot occur stay exact zeros, as in vec(rho) (the Pauli basis, whose expectations are all
+// of order one, turns both into rounding of the trace), the trace moves by the Kraus sets' own rounding and
+// nothing else, and errors against 64 bits are no larger than the 3M form's.  A coherence of m qubits is a
+// sum of 2^m coefficients, so it is known to the rounding of the largest coherence of the same
+// qubits.
 //
 // Tiles, groups and swizzle follow tile.hpp with real elements: a workgroup owns 2^V elements (the
 // 2k target bits plus the lowest free bits).  Each wave owns 16-group column blocks and holds all
@@ -58,12 +65,10 @@ struct RealIo {
   __device__ inline bool has(int it, int tid) const { return FULL || it * NT + tid < slots; }
 };
 
-// One superoperator in real form on the tile in LDS, in place: y = x + P x, P = R - I up to a common
-// factor (real_operand).  The accumulators start from x, so the identity part is exact and what P rounds is
-// small where R is near the identity.  P fragment (m, s) of lane l is P[row(m, l % 16)][4 s + l / 16];
-// accumulator value r of lane l holds row 16 m + l / 16 + 4 r in both precisions (the FP32 packing permutes
-// the rows within an m-tile), so the elements a lane writes are the ones it read: one set of addresses
-// serves both, and the accumulators' start is in registers.
+// One superoperator in real form on the tile in LDS, in place: y = R x.  R fragment (m, s) of lane l is
+// R[row(m, l % 16)][4 s + l / 16]; accumulator value r of lane l holds row 16 m + l / 16 + 4 r in both
+// precisions (the FP32 packing permutes the rows within an m-tile), so the elements a lane writes are the
+// ones it read: one set of addresses serves both.
 template <typename T, int K, int VMAX, int NT>
 struct OpReal {
   using M = Mfma<T>;
@@ -134,10 +139,7 @@ struct OpReal {
 #pragma unroll
         for (int u = 0; u < STEP; ++u)
 #pragma unroll
-          for (int m = 0; m < MP; ++m) {
-            const int r0 = 4 * (m0 + m);
-            acc[u][m] = acc_t{b[u][r0], b[u][r0 + 1], b[u][r0 + 2], b[u][r0 + 3]};
-          }
+          for (int m = 0; m < MP; ++m) acc[u][m] = acc_t{0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < KS; ++s)
 #pragma unroll
@@ -210,36 +212,32 @@ __device__ inline int ycount(uint32_t a, int k) {
   return __popc(~a & (a >> k) & m);
 }
 
-// E[a][b] = R[a][b] - (a == b) of the real form R of a superoperator S (4^k x 4^k complex), as hi + lo: summed
-// without rounding loss, because R's first row is (1, 0, .., 0) but for the rounding of S, and that defect,
-// far below one unit in the last place of 1, acts on the trace once per superoperator.
-__device__ inline void real_entry(const f64x2* S, int k, uint32_t a, uint32_t b, double* hi, double* lo) {
+// R[a][b] of a superoperator S (4^k x 4^k complex): Re((-i)^(y_a - y_b) 2^-m_a sum_{u,v} +-
+// S[i(a,u)][i(b,v)]), u and v running over the 2^m choices of (row, column) = (1, 0) or (0, 1) on the m qubits where
+// the index is X or Y, a factor -1 for every Y at (0, 1).  For S = sum_i conj(K_i) (x) K_i the imaginary part
+// is zero.  Between populations it is one entry of S; summed without rounding loss and rounded once.
+__device__ inline double real_entry(const f64x2* S, int k, uint32_t a, uint32_t b) {
   const uint32_t m = (1u << k) - 1u;
   const uint32_t ra = a & m, ca = a >> k, rb = b & m, cb = b >> k;
+  const uint32_t xa = ra ^ ca, xb = rb ^ cb, ya = ~ra & ca, yb = ~rb & cb;
   const int d = (ycount(a, k) - ycount(b, k)) & 3;  // Re((-i)^d (x + i y)) = x, y, -x, -y
-  const double scale = 1.0 / (double)(1u << k);
-  double h = a == b ? -1.0 : 0.0, l = 0.0;
-  for (uint32_t u = 0; u <= m; ++u)
-    for (uint32_t v = 0; v <= m; ++v) {
-      const f64x2 x = S[(((u ^ ra ^ ca) + (u << k)) << (2 * k)) + (v ^ rb ^ cb) + (v << k)];
-      const bool neg = ((__popc(u & ca) + __popc(v & cb)) & 1) != (d >> 1);
+  const double scale = 1.0 / (double)(1u << __popc(xa));
+  double h = 0.0, l = 0.0;
+  for (uint32_t u = xa;; u = (u - 1) & xa) {  // the subsets of xa
+    const uint32_t row = ((ra & ca) | u) + (((ra & ca) | (xa & ~u)) << k);
+    for (uint32_t v = xb;; v = (v - 1) & xb) {
+      const f64x2 x = S[(row << (2 * k)) + ((rb & cb) | v) + (((rb & cb) | (xb & ~v)) << k)];
+      const bool neg = ((__popc(ya & ~u) + __popc(yb & ~v)) & 1) != (d >> 1);
       double t = ((d & 1) ? x[1] : x[0]) * scale;
       t = neg ? -t : t;
       const double s = h + t, bb = s - h;  // s + the error term is the exact sum
       l += (h - (s - bb)) + (t - bb);
       h = s;
+      if (v == 0) break;
     }
-  *hi = h + l;
-  *lo = l - (*hi - h);
-}
-
-// A superoperator that keeps the trace up to rounding (|E[0][0]| below this) is applied as (1 + d) (I + P) with
-// d = E[0][0] and P = (E - d (I + E)) / (1 + d), so P[0][0] = 0: the factors are products of 1 + d over the
-// list, far more exact than a first row rounded to doubles, and are applied to the result once.
-constexpr double kRealDefect = 0x1p-30;
-__device__ inline double real_defect(double e00) { return fabs(e00) < kRealDefect ? e00 : 0.0; }
-__device__ inline double real_operand(double hi, double lo, double d, bool diag, bool first) {
-  return first && d != 0.0 ? 0.0 : hi + (lo - d * (hi + (diag ? 1.0 : 0.0)));
+    if (u == 0) break;
+  }
+  return h + l;
 }
 
 // fragment element e of a packed real operand: its row and column (real.hpp, OpReal)
@@ -375,7 +373,7 @@ __device__ inline void real_pass_tiles(double* __restrict__ w, const double* __r
       f64x4 acc[2];
 #pragma unroll
       for (int i = 0; i < NBW; ++i) {
-        f64x4 c = {b[i][0], b[i][1], b[i][2], b[i][3]};  // y = x + P x (OpReal)
+        f64x4 c = {0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < 4; ++s) c = Mfma<double>::mma(a[j][s], b[i][s], c);
         acc[i & 1] = c;

@@ -483,11 +483,7 @@ void tanq_server_s::run_iteration() {
       uint64_t* masks = (uint64_t*)(hres + 1 + nprob + 2 * np);
       if (np) std::memcpy(masks, r->paulis.data(), 3 * np * sizeof(uint64_t));
       if (p == TANQ_F64) {
-        // every block has the server's width, so the operands lie at equal distances
-        const int nblk = (int)r->pack_off.size();
-        const size_t stride = align256(packed_bytes(cfg.width, p));
-        launch_real_outputs(rho, r->n, p, r->want_probs, (int)np, masks, nblk ? arena_base + r->pack_off[0] : nullptr,
-                            cfg.width, stride, nblk, hres, stream);
+        launch_real_outputs(rho, r->n, p, r->want_probs, (int)np, masks, hres, stream);
       } else {
         launch_probs(rho, r->n, p, 1, nullptr, nullptr, probs_dev, partials, r->want_probs ? hres + 1 : nullptr, hres,
                      stream);
