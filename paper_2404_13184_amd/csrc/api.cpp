@@ -255,10 +255,12 @@ int count_launches(BlockAt at, int begin, int end, int n, tanq_prec p, int lim) 
 // less than half of one (15 ms), so the line is at about seven launches: lists of 8, complex ->
 // real: 13 qubits 3.93 -> 3.57 ms, 14 qubits 15.1 -> 13.4 ms, 16 qubits 231 -> 217 ms; of 10 at 15
 // qubits 75.8 -> 58.7 ms.  At 11 and 12 qubits 12 keeps the gain clear of what a state that is not
-// Hermitian pays.  Measured, complex -> real: 20 layers of random U3/CX at width 2, 11 qubits 1204 -> 645
-// us, 12 qubits 4.62 -> 2.33 ms, 14 qubits 78.7 -> 40.3 ms; 10 layers at 16 qubits 740 -> 450 ms.  A
-// state that is not Hermitian pays for the check and the launches that do nothing: 7% at 11 qubits,
-// 3% at 12, 1% at 14.  Below 11 qubits those outweigh the gain.  FP32 keeps the complex form: its
+// Hermitian pays.  Measured, complex -> real: 20 layers of random U3/CX at width 2, 11 qubits 1185 -> 624
+// us, 12 qubits 4.79 -> 2.23 ms, 14 qubits 78.7 -> 40.3 ms; 10 layers at 16 qubits 740 -> 450 ms.  A program that
+// fuses, applies once and reads the probabilities, the geometry of both forms in the call: 8 layers (13
+// launches) at 11 qubits 877 -> 578 us, 8 (14) at 12 qubits 2.49 -> 1.45 ms, 6 (12) at 13 qubits 6.63 ->
+// 4.57 ms.  A state that is not Hermitian pays for the check and the launches that do nothing: 2 to 4% at 11
+// qubits, up to 1.5% at 12, 1% at 13.  Below 11 qubits those outweigh the gain.  FP32 keeps the complex form: its
 // results would move in the seventh digit.  Passes switched off (limit 1) keep it off too: the blocks
 // are then applied one by one.
 bool herm_list(int launches, int n, tanq_prec p, int lim) {

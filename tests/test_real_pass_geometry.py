@@ -1,0 +1,85 @@
+"""Host check of the real-form passes' geometry (pass_geom.cpp), built with the host compiler: the LDS swizzle leaves the
+operand accesses of all but a few of the superoperators free of bank conflicts, and finding it takes microseconds, since the
+first application of every list pays for it (random columns took up to 25 ms a pass)."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2404_13184_amd", "csrc")
+
+DRIVER = r"""
+#include <algorithm>
+#include <chrono>
+#include <cstdio>
+#include <random>
+
+#include "internal.hpp"
+
+using namespace tanq;
+
+// superoperators whose 32 lanes of one access (16 groups, two rows) fall on distinct banks of 8 bytes
+static int conflict_free(const RealPassGeom& g) {
+  int count = 0;
+  for (int j = 0; j < g.m; ++j) {
+    unsigned used = 0;
+    for (int l = 0; l < 32; ++l) {
+      unsigned at = (l & 16) ? g.sbit[j][9] : 0;
+      for (int b = 0; b < 4; ++b)
+        if ((l >> b) & 1) at ^= g.sbit[j][b];
+      used |= 1u << ((at / 8) & 31);
+    }
+    count += used == ~0u;
+  }
+  return count;
+}
+
+int main() {
+  std::mt19937 r(7);
+  long ops = 0, good = 0;
+  double sum = 0, worst = 0;
+  const int passes = 3000;
+  for (int it = 0; it < passes; ++it) {
+    const int n = 11 + r() % 6, m = 1 + r() % 8;
+    std::vector<int> perm(n);
+    for (int i = 0; i < n; ++i) perm[i] = i;
+    std::shuffle(perm.begin(), perm.end(), r);
+    int held = n;
+    for (; held > 2; --held) {
+      uint64_t mask = 0;
+      for (int i = 0; i < held; ++i) mask |= 1ull << perm[i];
+      if (real_pass_fits(mask, n)) break;
+    }
+    int k[8], q[24] = {0};
+    uint32_t off[8] = {0};
+    for (int j = 0; j < m; ++j) {
+      k[j] = r() % 8 ? 2 : 1;
+      const int a = r() % held, b = (a + 1 + r() % (held - 1)) % held;
+      q[3 * j] = std::min(perm[a], perm[b]);
+      q[3 * j + 1] = std::max(perm[a], perm[b]);
+    }
+    double us = 1e9;
+    RealPassGeom g{};
+    for (int rep = 0; rep < 3; ++rep) {
+      const auto t0 = std::chrono::steady_clock::now();
+      g = make_real_pass_geom(n, m, k, q, off);
+      us = std::min(us, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count());
+    }
+    sum += us;
+    worst = std::max(worst, us);
+    good += conflict_free(g);
+    ops += m;
+  }
+  std::printf("%ld %ld %f %f\n", good, ops, sum / passes, worst);
+}
+"""
+
+
+def test_swizzles_are_found_in_microseconds(tmp_path):
+    src, exe = tmp_path / "driver.cpp", tmp_path / "driver"
+    src.write_text(DRIVER)
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-w", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + CSRC,
+                           str(src), os.path.join(CSRC, "pass_geom.cpp"), "-o", str(exe)])
+    good, ops, mean, worst = (float(v) for v in subprocess.check_output([str(exe)]).split())
+    assert good >= 0.999 * ops
+    # 3 us and 22 us on an idle core: ten times that leaves room for a busy one
+    assert mean < 30 and worst < 500
