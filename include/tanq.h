@@ -274,7 +274,8 @@ tanq_status tanq_autotune_dense(tanq_dm d, int reps, double* ms_per_apply);
  * tanq_fused_launches counts them as single applies.
  *
  * Long FP64 lists (11 to 16 qubits; at least 12 launches as tanq_fused_launches counts them, 8 from
- * 13 qubits on; passes not switched off) on an exactly Hermitian rho are applied in real form: the 4^n
+ * 13 qubits on; passes not switched off; no measurement, reset or post-selection, i.e. no operation that
+ * clears elements of rho) on an exactly Hermitian rho are applied in real form: the 4^n
  * real coefficients of rho over the products of |0><0|, |1><1|, X and Y, on which every superoperator is a
  * real matrix, formed in place before the first superoperator and turned back after the last.  The
  * device checks rho and chooses; the call stays asynchronous and the results agree with the blocks applied
@@ -398,7 +399,8 @@ tanq_status tanq_dm_compare(tanq_dm a, tanq_dm b, double* out3);
  * captured once in a hipGraph and replayed); requests arriving meanwhile join at the next
  * iteration.  A request's arithmetic does not depend on the other requests in the batch, so
  * its results are the same alone and in the mix.  All blocks are widened to the server's
- * fusion width (2 or 3).  Errors on the scheduler thread fail the affected requests with
+ * fusion width (2 or 3).  FP64 requests are held in real form from |0..0><0..0| on (see
+ * tanq_set_pass_limit for what that means for small values); FP32 requests as vec(rho).  Errors on the scheduler thread fail the affected requests with
  * TANQ_E_HIP and the server stops accepting work.
  * ------------------------------------------------------------------------------------- */
 
