@@ -392,7 +392,8 @@ tanq_status tanq_dm_compare(tanq_dm a, tanq_dm b, double* out3);
  * Serving: continuous batching of many small noisy circuits.
  *
  * Requests are admitted in arrival order while a slot is free and their device footprint
- * (vec(rho) plus packed superoperators plus fusion temporaries, known at submit) fits in the
+ * (the state, 4^n doubles in FP64 and vec(rho) in FP32, plus packed superoperators plus fusion
+ * temporaries, known at submit) fits in the
  * budget.  Each admitted request's state stays resident on the device until its results are
  * read back.  A scheduler thread applies, per batched launch, the next fused superoperator of
  * every resident request at once (steps_per_launch such launches per iteration, optionally
@@ -400,8 +401,8 @@ tanq_status tanq_dm_compare(tanq_dm a, tanq_dm b, double* out3);
  * iteration.  A request's arithmetic does not depend on the other requests in the batch, so
  * its results are the same alone and in the mix.  All blocks are widened to the server's
  * fusion width (2 or 3).  FP64 requests are held in real form from |0..0><0..0| on (see
- * tanq_set_pass_limit for what that means for small values); FP32 requests as vec(rho).  Errors on the scheduler thread fail the affected requests with
- * TANQ_E_HIP and the server stops accepting work.
+ * tanq_set_pass_limit for what that means for small values), FP32 requests as vec(rho).  Errors on
+ * the scheduler thread fail the affected requests with TANQ_E_HIP and the server stops accepting work.
  * ------------------------------------------------------------------------------------- */
 
 typedef struct tanq_server_s* tanq_server;

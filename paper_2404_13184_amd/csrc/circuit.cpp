@@ -22,7 +22,8 @@ void widen_plan(std::vector<PlanBlock>& plan, int n, int w) {
   }
 }
 
-FuseLayout make_fuse_layout(const std::vector<HostOp>& ops, const std::vector<PlanBlock>& plan, tanq_prec p) {
+FuseLayout make_fuse_layout(const std::vector<HostOp>& ops, const std::vector<PlanBlock>& plan, tanq_prec p,
+                            bool real) {
   FuseLayout L;
   // identical Kraus sets (same pool, offset and size, e.g. a noise channel repeated through a
   // circuit) are uploaded once; their superoperators are still built per operation.  Open addressing:
@@ -49,7 +50,7 @@ FuseLayout make_fuse_layout(const std::vector<HostOp>& ops, const std::vector<Pl
     bh.raw_off = L.raw_elems;
     bh.pack_off = L.pack_bytes;
     L.raw_elems += (size_t)1 << (4 * k);
-    L.pack_bytes += align256(packed_bytes(k, p));
+    L.pack_bytes += align256(real ? real_pack_elems(k) * sizeof(double) : packed_bytes(k, p));
     for (int oi : pb.ops) {
       const HostOp& ho = ops[oi];
       FuseOpDev od{};

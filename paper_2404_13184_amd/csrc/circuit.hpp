@@ -50,14 +50,16 @@ struct FuseLayout {
   std::vector<FuseBlockDev> blocks;
   std::vector<double> kraus;  // interleaved complex
   std::vector<FusedBlockHost> host;
-  size_t sop_elems = 0;   // complex elements of all operations' superoperators
+  size_t sop_elems = 0;   // elements (complex, or real in real form) of all operations' superoperators
   size_t raw_elems = 0;   // complex elements of all blocks' FP64 superoperators
   size_t pack_bytes = 0;  // packed operands
   int max_k = 1;
   int count_k[4] = {0, 0, 0, 0};
 };
 
-FuseLayout make_fuse_layout(const std::vector<HostOp>& ops, const std::vector<PlanBlock>& plan, tanq_prec p);
+// real: operands of the real form, real.hpp.
+FuseLayout make_fuse_layout(const std::vector<HostOp>& ops, const std::vector<PlanBlock>& plan, tanq_prec p,
+                            bool real = false);
 
 // Superoperator construction, FP64 composition and packing on stream s; the tables
 // (d_ops, d_blk, d_kraus) must already hold the layout's contents.

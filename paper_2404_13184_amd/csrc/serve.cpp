@@ -129,14 +129,26 @@ constexpr int kServeMaxN = 14;
 constexpr uint64_t kChunksPerItem = 64;
 constexpr uint64_t kMinChunkTiles = 4;    // smallest chunk (guided sizes shrink towards it)
 
-static size_t state_bytes(int n, tanq_prec p) { return ((size_t)1 << (2 * n)) * elem_size(p); }
+// FP64 requests are held in real form (real.hpp), FP32 ones as vec(rho).
+static bool real_form(tanq_prec p) { return p == TANQ_F64; }
+static size_t state_bytes(int n, tanq_prec p) {
+  return ((size_t)1 << (2 * n)) * (real_form(p) ? sizeof(double) : elem_size(p));
+}
+// superoperators of a request's operations, and the FP64 compositions beside its packed operands (which the
+// real form writes as operands at once)
+static size_t sop_bytes(tanq_prec p, const FuseLayout& L) {
+  return align256(L.sop_elems * (real_form(p) ? 1 : 2) * sizeof(double));
+}
+static size_t raw_bytes(tanq_prec p, const FuseLayout& L) {
+  return real_form(p) ? 0 : align256(L.raw_elems * 2 * sizeof(double));
+}
 
-// Device bytes a request holds while its fusion runs: rho and the packed operands (kept to the
+// Device bytes a request holds while its fusion runs: its state and the packed operands (kept to the
 // end) plus the fusion tables, superoperators and FP64 compositions (released after fusion).
 static size_t request_footprint(int n, tanq_prec p, const FuseLayout& L) {
   return align256(state_bytes(n, p)) + L.pack_bytes + align256(L.ops.size() * sizeof(FuseOpDev)) +
          align256(L.blocks.size() * sizeof(FuseBlockDev)) + align256(L.kraus.size() * sizeof(double)) +
-         align256(L.sop_elems * 2 * sizeof(double)) + align256(L.raw_elems * 2 * sizeof(double)) + 7 * 256;
+         sop_bytes(p, L) + raw_bytes(p, L) + 7 * 256;
 }
 
 }  // namespace tanq
@@ -261,8 +273,7 @@ void tanq_server_s::admit_one(ServeRequest* r) {
   const size_t ops_b = align256(L.ops.size() * sizeof(FuseOpDev));
   const size_t blk_b = align256(L.blocks.size() * sizeof(FuseBlockDev));
   const size_t kr_b = align256(L.kraus.size() * sizeof(double));
-  const size_t sop_b = align256(L.sop_elems * 2 * sizeof(double));
-  const size_t raw_b = align256(L.raw_elems * 2 * sizeof(double));
+  const size_t sop_b = sop_bytes(p, L), raw_b = raw_bytes(p, L);
   const size_t tmp_size = ops_b + blk_b + kr_b + sop_b + raw_b;
   size_t keep_off = 0, tmp_off = 0, stage_off = 0;
   if (!arena.alloc(r->keep_size, &keep_off)) fail(TANQ_E_OOM, "arena exhausted at admission");
@@ -291,7 +302,7 @@ void tanq_server_s::admit_one(ServeRequest* r) {
   const FuseBlockDev* d_blk = (const FuseBlockDev*)(tmp + ops_b);
   const double* d_kraus = (const double*)(tmp + ops_b + blk_b);
   double* d_sops = (double*)(tmp + ops_b + blk_b + kr_b);
-  if (p == TANQ_F64) {
+  if (real_form(p)) {
     launch_build_real(d_ops, (int)L.ops.size(), d_kraus, d_sops, adm_stream);
     launch_compose_real(d_blk, (int)L.blocks.size(), w, d_ops, d_sops, arena_base + keep_off + rho_b, p, adm_stream);
   } else {
@@ -301,7 +312,7 @@ void tanq_server_s::admit_one(ServeRequest* r) {
   // every later user of this region is ordered after the fusion kernels: other admissions run
   // on the same stream, and only admissions allocate from the arena
   arena.release(tmp_off, tmp_size);
-  if (p == TANQ_F64)
+  if (real_form(p))
     launch_real_init(arena_base + r->rho_off, r->n, p, adm_stream);
   else
     launch_init_zero(arena_base + r->rho_off, r->n, p, adm_stream);
@@ -316,7 +327,7 @@ void tanq_server_s::admit_one(ServeRequest* r) {
   const int vb = batch_tile_bits(p);
   for (size_t i = 0; i < L.host.size(); ++i) {
     r->pack_off[i] = keep_off + rho_b + L.host[i].pack_off;
-    if (p == TANQ_F64) {
+    if (real_form(p)) {
       // rows, then columns: ascending, as the composed operand's local index
       int tbits[6];
       for (int t = 0; t < w; ++t) {
@@ -419,7 +430,7 @@ void tanq_server_s::run_iteration() {
     uint64_t remaining = 0;
     for (uint32_t i = 0; i < ni; ++i) {
       order[i] = i;
-      ntiles[i] = cfg.prec == TANQ_F64 ? items[i].geom.rg.ntiles : items[i].geom.g.ntiles;
+      ntiles[i] = real_form((tanq_prec)cfg.prec) ? items[i].geom.rg.ntiles : items[i].geom.g.ntiles;
       remaining += ntiles[i];
     }
     std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return ntiles[a] > ntiles[b]; });
@@ -482,7 +493,7 @@ void tanq_server_s::run_iteration() {
       const size_t np = r->paulis.size(), nprob = r->want_probs ? (size_t)1 << r->n : 0;
       uint64_t* masks = (uint64_t*)(hres + 1 + nprob + 2 * np);
       if (np) std::memcpy(masks, r->paulis.data(), 3 * np * sizeof(uint64_t));
-      if (p == TANQ_F64) {
+      if (real_form(p)) {
         launch_real_outputs(rho, r->n, p, r->want_probs, (int)np, masks, hres, stream);
       } else {
         launch_probs(rho, r->n, p, 1, nullptr, nullptr, probs_dev, partials, r->want_probs ? hres + 1 : nullptr, hres,
@@ -804,7 +815,7 @@ tanq_status tanq_server_submit(tanq_server s, tanq_circuit c, const tanq_outputs
     const tanq_prec p = (tanq_prec)s->cfg.prec;
     std::vector<PlanBlock> plan = plan_fusion(plan_ops(r->ops), r->n, s->cfg.width);
     widen_plan(plan, r->n, s->cfg.width);
-    r->layout = make_fuse_layout(r->ops, plan, p);
+    r->layout = make_fuse_layout(r->ops, plan, p, real_form(p));
     r->footprint = request_footprint(r->n, p, r->layout);
     std::lock_guard<std::mutex> lk(s->mu);
     if (s->failed) fail(TANQ_E_STATE, "server failed: " + s->fail_msg);
