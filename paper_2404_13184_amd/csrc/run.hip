@@ -18,6 +18,8 @@
 // the other on one qubit keep their amplitudes in registers.  The 640 single-operation blocks of the
 // 8-qubit plain circuit: 640 launches, 2.81 ms, one by one; 59 launches, 0.81 ms, in runs (12.2 us each,
 // 3.4 us of it the start).  A 6-qubit list of 23 two-qubit blocks: 150 -> 55 us.
+// Touching the three-qubit operands: a 6-qubit FP32 list with 22 of them, operands out of the L2: 266 us where the
+// last third of each was left out, 227 us (213 and 216 us where they are in the L2).
 #include <cstddef>
 
 #include "real.hpp"
@@ -66,6 +68,7 @@ __global__ __launch_bounds__(kRunThreads) void apply_run_kernel(T* __restrict__ 
   constexpr int V = RunShape<T>::V, NT = kRunThreads, NW = NT / 64;
   constexpr int EPS = 16 / (2 * (int)sizeof(T)), SLOTS = (1 << V) / EPS, ITERS = SLOTS / NT;
   constexpr int OPE = 1024;  // elements of a two-qubit operand
+  constexpr int LINES3 = packed_elems(3) * (int)sizeof(T) / 128;  // cache lines of a three-qubit one
   __shared__ u32x4 tile4[SLOTS];
   __shared__ RunOp tab[kRunMax];
   __shared__ T opl1[kRunMax][32];
@@ -107,7 +110,8 @@ __global__ __launch_bounds__(kRunThreads) void apply_run_kernel(T* __restrict__ 
     if (j >= g.m3) break;
     const unsigned char* P = packed + (size_t)g.off3[j] * 256;
 #pragma unroll
-    for (int u = 0; u < 4 * 16 * 3 * 64 * (int)sizeof(T) / 128 / NT; ++u) {
+    for (int u = 0; u < (LINES3 + NT - 1) / NT; ++u) {
+      if (u * NT + tid >= LINES3) break;
       const uint32_t x = *reinterpret_cast<const uint32_t*>(P + (u * NT + tid) * 128);
       asm volatile("" ::"v"(x));
     }
