@@ -219,12 +219,12 @@ __global__ __launch_bounds__(NT, (BatchMinBlocks<T, K>::value)) void batch_apply
 // at width 3 147 -> 66.7 ms, 4-11 qubits at width 2 95 -> 49 ms.  FP32 keeps vec(rho), although the
 // real form serves it 1.9 times faster (82 -> 43 ms) with a fifth of the error: its results are
 // defined by their rounding in single precision, which would change in the seventh digit.
-template <typename T, int K, int VMAX, int NT>
+template <int K, int VMAX, int NT>
 __global__ __launch_bounds__(NT, 2) void batch_real_kernel(const BatchItem* __restrict__ items,
                                                          const BatchChunk* __restrict__ chunks,
                                                          uint32_t* __restrict__ count) {
-  using IO = RealIo<T, VMAX, NT>;
-  using Op = OpReal<T, K, VMAX, NT>;
+  using IO = RealIo<VMAX, NT>;
+  using Op = OpReal<K, VMAX, NT>;
   static_assert(sizeof(RealGeom) % 4 == 0, "geometry copied as dwords");
 
   __shared__ u32x4 lds[2][IO::SLOTS];
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(NT, 2) void batch_real_kernel(const BatchItem* __re
   IO io;
   Op op;
   BatchRuns runs;
-  T* rho = nullptr;
+  double* rho = nullptr;
   for (;;) {
     // dynamic assignment: each workgroup claims the next chunk (count[1], zeroed by the copy of
     // the work list that precedes every launch), so the launch ends when its last chunks do
@@ -257,8 +257,8 @@ __global__ __launch_bounds__(NT, 2) void batch_real_kernel(const BatchItem* __re
       uint32_t* dst = reinterpret_cast<uint32_t*>(&sg);
       for (int i = tid; i < (int)(sizeof(RealGeom) / 4); i += NT) dst[i] = src[i];
       lds_barrier();
-      rho = reinterpret_cast<T*>(items[ch.item].rho);
-      const T* frag = reinterpret_cast<const T*>(items[ch.item].frag);
+      rho = reinterpret_cast<double*>(items[ch.item].rho);
+      const double* frag = reinterpret_cast<const double*>(items[ch.item].frag);
       io.init(sg, tid);
       op.load(frag, lane);
       op.prepare(sg, lane, wave);
@@ -269,9 +269,9 @@ __global__ __launch_bounds__(NT, 2) void batch_real_kernel(const BatchItem* __re
     if (ch.tile_begin >= ch.tile_end) continue;
     auto base = [&](uint32_t t) { return (uint32_t)runs.base(t); };
     if (full)
-      real_tiles<true, T>(rho, io, op, base, lds, ch.tile_begin, ch.tile_end, tid);
+      real_tiles<true>(rho, io, op, base, lds, ch.tile_begin, ch.tile_end, tid);
     else
-      real_tiles<false, T>(rho, io, op, base, lds, ch.tile_begin, ch.tile_end, tid);
+      real_tiles<false>(rho, io, op, base, lds, ch.tile_begin, ch.tile_end, tid);
   }
 }
 
@@ -288,7 +288,7 @@ struct BatchShape<float> { static constexpr int V = 11, NT = 256; };
 template <typename T, int K>
 static constexpr auto batch_kernel() {
   if constexpr (sizeof(T) == 8)
-    return batch_real_kernel<T, K, BatchShape<T>::V, BatchShape<T>::NT>;
+    return batch_real_kernel<K, BatchShape<T>::V, BatchShape<T>::NT>;
   else
     return batch_apply_kernel<T, K, BatchShape<T>::V, BatchShape<T>::NT>;
 }

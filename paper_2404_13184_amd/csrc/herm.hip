@@ -295,8 +295,8 @@ __global__ __launch_bounds__(kMidNT) void herm_mid_kernel(double* __restrict__ w
 __global__ __launch_bounds__(256, 2) void real_apply3_kernel(double* __restrict__ w, const double* __restrict__ frag,
                                                              const RealGeom g, const uint32_t* flag) {
   constexpr int V = 12, NT = 256;
-  using IO = RealIo<double, V, NT>;
-  using Op = OpReal<double, 3, V, NT>;
+  using IO = RealIo<V, NT>;
+  using Op = OpReal<3, V, NT>;
   __shared__ u32x4 lds[2][IO::SLOTS];
   if (!flag_set(flag)) return;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -330,7 +330,7 @@ __global__ __launch_bounds__(256) void pack_herm_kernel(const RealPackDev* __res
   };
   for (int e = threadIdx.x; e < D * D; e += blockDim.x) {
     int row = e / D, col = e % D;
-    if (b.k > 1) real_frag_index<double>(e, D / 4, &row, &col);
+    if (b.k > 1) real_frag_index(e, D / 4, &row, &col);
     P[e] = real_entry(S, b.k, local(row), local(col));
   }
 }
@@ -416,7 +416,7 @@ void launch_real_apply3(void* rho, int n, const int* qubits, const double* packe
     tbits[t] = qubits[t] + 1;
     tbits[3 + t] = qubits[t] == n - 1 ? 0 : qubits[t] + n + 1;
   }
-  const RealGeom g = make_real_geom(2 * n, 3, tbits, 12, TANQ_F64);
+  const RealGeom g = make_real_geom(2 * n, 3, tbits, 12);
   hipLaunchKernelGGL(real_apply3_kernel, dim3(herm_grid(g.ntiles, 2)), dim3(256), 0, s, (double*)rho, packed, g, flag);
   TANQ_HIP(hipGetLastError());
 }

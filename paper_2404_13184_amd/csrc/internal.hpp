@@ -203,7 +203,7 @@ constexpr int packed_elems(int k) { return k == 1 ? 32 : (k == 2 ? 32 * 32 : 4 *
 ApplyGeom make_apply_geom(int n, int k, const int* qubits, int vbits, tanq_prec p);
 // Geometry of one k-qubit superoperator on a state in real form: tbits = its 2k target bits in the
 // state's element address (any order), nb = 2n.
-RealGeom make_real_geom(int nb, int k, const int* tbits, int vbits, tanq_prec p);
+RealGeom make_real_geom(int nb, int k, const int* tbits, int vbits);
 
 // Apply-kernel variants per (k, precision), k in {2, 3}: count, shape, process-wide choice.
 int variant_count(int k, tanq_prec p);
@@ -301,15 +301,14 @@ void launch_apply_one_qubit(void* rho, int n, tanq_prec p, int qubit, const doub
 // operands; FP64, rounded once.  Every block has k qubits (2 or 3).
 void launch_build_real(const FuseOpDev* ops, int nops, const double* kraus, double* sops, hipStream_t s);
 void launch_compose_real(const FuseBlockDev* blocks, int nblocks, int k, const FuseOpDev* ops, const double* sops,
-                         void* packed, tanq_prec p, hipStream_t s);
+                         void* packed, hipStream_t s);
 // w = the real form of |0..0><0..0|
-void launch_real_init(void* w, int n, tanq_prec p, hipStream_t s);
+void launch_real_init(void* w, int n, hipStream_t s);
 // Outputs of a state in real form, n <= kRealOutMaxN: out[0] = the trace, then the 2^n probabilities
 // divided by it if want_probs, then (Re, Im) of count Pauli expectations (masks: x, z, #Y mod 4 per
 // string, as launch_pauli).  masks and out are device-accessible (pinned host memory).
 constexpr int kRealOutMaxN = 14;
-void launch_real_outputs(const void* w, int n, tanq_prec p, int want_probs, int count, const uint64_t* masks, double* out,
-                         hipStream_t s);
+void launch_real_outputs(const void* w, int n, int want_probs, int count, const uint64_t* masks, double* out, hipStream_t s);
 
 // Measurement statistics (measure.hip; FP64).  partials: device scratch of at least reduce_partials() doubles;
 // probs_dev: of 2^n doubles.  Outputs (out, trace, masks) are device-accessible: device memory or

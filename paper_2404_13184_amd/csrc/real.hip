@@ -33,7 +33,7 @@ __global__ __launch_bounds__(256) void build_real_kernel(const FuseOpDev* __rest
 // barrier per operation), then the operand's fragments.  Thread t works on column t % D; the 256 / D threads of a
 // column share its groups and outputs.  The chain over a block's operations is serial: ComposeFeed keeps it from
 // waiting for memory.
-template <typename T, int K>
+template <int K>
 __global__ __launch_bounds__(256) void compose_real_kernel(const FuseBlockDev* __restrict__ blocks,
                                                            const FuseOpDev* __restrict__ ops,
                                                            const double* __restrict__ sops,
@@ -123,27 +123,25 @@ __global__ __launch_bounds__(256) void compose_real_kernel(const FuseBlockDev* _
     feed.next(oi);
     cur ^= 1;
   }
-  T* P = reinterpret_cast<T*>(packed + blk.pack_off);
+  double* P = reinterpret_cast<double*>(packed + blk.pack_off);
   for (int e = tid; e < D * D; e += 256) {
     int row, col;
-    real_frag_index<T>(e, D / 4, &row, &col);
-    P[e] = (T)M[cur][row * D + col];
+    real_frag_index(e, D / 4, &row, &col);
+    P[e] = M[cur][row * D + col];
   }
 }
 
 // |0..0><0..0| is an element of the basis.
-template <typename T>
-__global__ void real_init_kernel(T* __restrict__ w, int n) {
+__global__ void real_init_kernel(double* __restrict__ w, int n) {
   const uint64_t nel = 1ull << (2 * n);
   for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nel; i += (uint64_t)gridDim.x * blockDim.x)
-    w[i] = i == 0 ? T(1) : T(0);
+    w[i] = i == 0 ? 1.0 : 0.0;
 }
 
 // Workgroup 0: the trace and the probabilities, which are coefficients.  Workgroup 1 + i: string i, which is non-zero on
 // the basis elements with X and Y where it has them: Tr(P B) = 2 on those qubits and +-1 (Z) or 1 on the
 // populations of the others.
-template <typename T>
-__global__ __launch_bounds__(1024) void real_outputs_kernel(const T* __restrict__ w, int n, int want_probs,
+__global__ __launch_bounds__(1024) void real_outputs_kernel(const double* __restrict__ w, int n, int want_probs,
                                                             const uint64_t* __restrict__ masks, double* __restrict__ out) {
   constexpr int PER = 1 << (kRealOutMaxN - 10);  // values of a thread
   __shared__ double part[16];
@@ -160,7 +158,7 @@ __global__ __launch_bounds__(1024) void real_outputs_kernel(const T* __restrict_
     v[u] = 0.0;
     if (i < count) {
       const uint32_t x = pdep32(i, free);
-      const double e = (double)w[at + x + ((uint64_t)x << n)];
+      const double e = w[at + x + ((uint64_t)x << n)];
       v[u] = (__popc(x & zm) & 1) ? -e : e;
     }
     acc += v[u];
@@ -191,7 +189,7 @@ __global__ __launch_bounds__(1024) void real_outputs_kernel(const T* __restrict_
 // host side
 // ------------------------------------------------------------------------------------
 
-RealGeom make_real_geom(int nb, int k, const int* tbits, int vbits, tanq_prec p) {
+RealGeom make_real_geom(int nb, int k, const int* tbits, int vbits) {
   RealGeom g{};
   const int V = vbits < nb ? vbits : nb;
   uint64_t tmask = 0;
@@ -216,11 +214,10 @@ RealGeom make_real_geom(int nb, int k, const int* tbits, int vbits, tanq_prec p)
   g.G = 1 << (V - 2 * k);
   g.free_mask = ((1u << V) - 1u) & ~tlocal;
   // LDS swizzle.  The bits that differ between the lanes of one access are the four lowest free bits
-  // (16 groups) and the lowest target bits (rows l / 16: two of them over 64 lanes of 4 bytes, one
-  // over 32 lanes of 8 bytes).  Those above the 256-byte window are XORed into the window bits that
-  // none of them covers.  Bits inside a 16-byte slot are never destinations: such a bit is free
-  // (then it is among the lowest four) or a target (then it is among the lowest).
-  const int w = p == TANQ_F64 ? 5 : 6, lo = p == TANQ_F64 ? 1 : 2;
+  // (16 groups) and the lowest target bit (rows l / 16, over 32 lanes).  Those above the 256-byte window are
+  // XORed into the window bits that none of them covers.  The bit inside a 16-byte slot is never a
+  // destination: it is free (then among the lowest four) or a target (then the lowest).
+  constexpr int w = 5, lo = 1;
   uint32_t lanes = 0;
   int nf = 0;
   for (int b = 0; b < V && nf < 4; ++b)
@@ -228,7 +225,7 @@ RealGeom make_real_geom(int nb, int k, const int* tbits, int vbits, tanq_prec p)
       lanes |= 1u << b;
       ++nf;
     }
-  for (int t = 0; t < w - 4; ++t) lanes |= 1u << g.tpos[t];
+  lanes |= 1u << g.tpos[0];
   int np = 0;
   for (int p2 = 0; p2 < kRealSwzPairs; ++p2) g.xsrc[p2] = 31;
   for (int b = w, d = lo; b < V; ++b) {
@@ -264,49 +261,29 @@ void launch_build_real(const FuseOpDev* ops, int nops, const double* kraus, doub
   TANQ_HIP(hipGetLastError());
 }
 
-template <typename T>
-static void compose_real_typed(const FuseBlockDev* blocks, int nblocks, int k, const FuseOpDev* ops,
-                               const double* sops, void* packed, hipStream_t s) {
+void launch_compose_real(const FuseBlockDev* blocks, int nblocks, int k, const FuseOpDev* ops, const double* sops,
+                         void* packed, hipStream_t s) {
+  if (nblocks <= 0) return;
   if (k == 2)
-    hipLaunchKernelGGL((compose_real_kernel<T, 2>), dim3(nblocks), dim3(256), 0, s, blocks, ops, sops,
-                       (unsigned char*)packed);
+    hipLaunchKernelGGL(compose_real_kernel<2>, dim3(nblocks), dim3(256), 0, s, blocks, ops, sops, (unsigned char*)packed);
   else if (k == 3)
-    hipLaunchKernelGGL((compose_real_kernel<T, 3>), dim3(nblocks), dim3(256), 0, s, blocks, ops, sops,
-                       (unsigned char*)packed);
+    hipLaunchKernelGGL(compose_real_kernel<3>, dim3(nblocks), dim3(256), 0, s, blocks, ops, sops, (unsigned char*)packed);
   else
     fail(TANQ_E_ARG, "real blocks have two or three qubits");
   TANQ_HIP(hipGetLastError());
 }
 
-void launch_compose_real(const FuseBlockDev* blocks, int nblocks, int k, const FuseOpDev* ops, const double* sops,
-                         void* packed, tanq_prec p, hipStream_t s) {
-  if (nblocks <= 0) return;
-  if (p == TANQ_F64)
-    compose_real_typed<double>(blocks, nblocks, k, ops, sops, packed, s);
-  else
-    compose_real_typed<float>(blocks, nblocks, k, ops, sops, packed, s);
-}
-
-void launch_real_init(void* w, int n, tanq_prec p, hipStream_t s) {
+void launch_real_init(void* w, int n, hipStream_t s) {
   uint64_t blocks = ((1ull << (2 * n)) + 1023) / 1024;
   const uint64_t cap = (uint64_t)device_cu_count() * 16;
   if (blocks > cap) blocks = cap;
-  if (p == TANQ_F64)
-    hipLaunchKernelGGL(real_init_kernel<double>, dim3((unsigned)blocks), dim3(256), 0, s, (double*)w, n);
-  else
-    hipLaunchKernelGGL(real_init_kernel<float>, dim3((unsigned)blocks), dim3(256), 0, s, (float*)w, n);
+  hipLaunchKernelGGL(real_init_kernel, dim3((unsigned)blocks), dim3(256), 0, s, (double*)w, n);
   TANQ_HIP(hipGetLastError());
 }
 
-void launch_real_outputs(const void* w, int n, tanq_prec p, int want_probs, int count, const uint64_t* masks, double* out,
-                         hipStream_t s) {
+void launch_real_outputs(const void* w, int n, int want_probs, int count, const uint64_t* masks, double* out, hipStream_t s) {
   if (n > kRealOutMaxN) fail(TANQ_E_ARG, "outputs of a real-form state: too many qubits");
-  if (p == TANQ_F64)
-    hipLaunchKernelGGL(real_outputs_kernel<double>, dim3(1 + count), dim3(1024), 0, s, (const double*)w, n, want_probs,
-                       masks, out);
-  else
-    hipLaunchKernelGGL(real_outputs_kernel<float>, dim3(1 + count), dim3(1024), 0, s, (const float*)w, n, want_probs,
-                       masks, out);
+  hipLaunchKernelGGL(real_outputs_kernel, dim3(1 + count), dim3(1024), 0, s, (const double*)w, n, want_probs, masks, out);
   TANQ_HIP(hipGetLastError());
 }
 

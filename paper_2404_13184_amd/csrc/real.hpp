@@ -7,7 +7,7 @@
 // The basis factorises over the qubits, so a map on k qubits acts on the same 2k index bits as in
 // vec(rho), and a map that keeps Hermiticity (every Kraus set does) is a real 4^k x 4^k matrix R.
 // Against vec(rho) that is half the bytes and, per superoperator, one real product in place of
-// the three of the 3M form.  Everything stays in the precision of the state.
+// the three of the 3M form.
 //
 // The populations rho[x][x] are coefficients themselves (r' = c' = x), and R takes populations to
 // populations by the superoperator's own entries.  So rare outcomes keep their relative accuracy and
@@ -41,9 +41,9 @@ __device__ inline uint32_t real_swz(uint32_t e, const RealGeom& g) {
 
 // 16-byte slots a thread moves: global element offset and swizzled LDS slot, the same for every
 // tile of one geometry.  has<true>: full tiles, no per-slot guard.
-template <typename T, int VMAX, int NT>
+template <int VMAX, int NT>
 struct RealIo {
-  static constexpr int EPS = 16 / (int)sizeof(T);  // elements per slot
+  static constexpr int EPS = 2;  // elements per slot
   static constexpr int SLOTS = (1 << VMAX) / EPS;
   static constexpr int ITERS = (SLOTS + NT - 1) / NT;
   uint32_t off[ITERS];  // elements (states of up to 2^32 elements)
@@ -66,12 +66,11 @@ struct RealIo {
 };
 
 // One superoperator in real form on the tile in LDS, in place: y = R x.  R fragment (m, s) of lane l is
-// R[row(m, l % 16)][4 s + l / 16]; accumulator value r of lane l holds row 16 m + l / 16 + 4 r in both
-// precisions (the FP32 packing permutes the rows within an m-tile), so the elements a lane writes are the
-// ones it read: one set of addresses serves both.
-template <typename T, int K, int VMAX, int NT>
+// R[row(m, l % 16)][4 s + l / 16]; accumulator value r of lane l holds row 16 m + l / 16 + 4 r, so the elements a
+// lane writes are the ones it read: one set of addresses serves both.
+template <int K, int VMAX, int NT>
 struct OpReal {
-  using M = Mfma<T>;
+  using M = Mfma<double>;
   using acc_t = typename M::acc_t;
   static constexpr int D = 1 << (2 * K), MT = D / 16, KS = D / 4;
   static constexpr int NW = NT / 64;
@@ -81,13 +80,13 @@ struct OpReal {
   // column blocks multiplied together: k = 2 has one accumulation chain per block, so pairs keep
   // the matrix unit from waiting for the previous product of the chain
   static constexpr int STEP = (K == 2 && NBW % 2 == 0) ? 2 : 1;
-  T a[MT][KS];
+  double a[MT][KS];
   uint32_t lb[NBW];  // S(group part ^ row part l / 16) of this lane in each of its column blocks
   bool act[NBW];
   uint32_t tb[2 * K - 2];  // S(tile offset of local index bit b + 2), uniform
   int nblk;
 
-  __device__ inline void load(const T* __restrict__ frag_in, int lane) {
+  __device__ inline void load(const double* __restrict__ frag_in, int lane) {
     const auto* frag = global_ptr(frag_in);
 #pragma unroll
     for (int m = 0; m < MT; ++m)
@@ -121,12 +120,12 @@ struct OpReal {
   }
 
   template <bool FULL>
-  __device__ inline void compute(T* lds) const {
+  __device__ inline void compute(double* lds) const {
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
 #pragma unroll
     for (int i0 = 0; i0 < NBW; i0 += STEP) {
       if (!FULL && wave + i0 * NW >= nblk) break;  // uniform per wave
-      T b[STEP][KS];
+      double b[STEP][KS];
 #pragma unroll
       for (int u = 0; u < STEP; ++u)
 #pragma unroll
@@ -163,8 +162,8 @@ struct OpReal {
 // current one is multiplied in one of two LDS buffers.  A wave multiplies its own groups in place,
 // so a tile takes two barriers: one between the multiplication and the store phase (which also
 // fills the other buffer with the next tile), one after it.
-template <bool FULL, typename T, typename IO, typename Op, typename Base>
-__device__ inline void real_tiles(T* __restrict__ rho, const IO& io, const Op& op, const Base& base, u32x4 (&lds)[2][IO::SLOTS], uint32_t t0, uint32_t t1, int tid) {
+template <bool FULL, typename IO, typename Op, typename Base>
+__device__ inline void real_tiles(double* __restrict__ rho, const IO& io, const Op& op, const Base& base, u32x4 (&lds)[2][IO::SLOTS], uint32_t t0, uint32_t t1, int tid) {
   uint32_t cur = base(t0);
   u32x4 buf[IO::ITERS];
 #pragma unroll
@@ -185,7 +184,7 @@ __device__ inline void real_tiles(T* __restrict__ rho, const IO& io, const Op& o
         if (io.template has<FULL>(it, tid))
           buf[it] = *global_ptr(reinterpret_cast<const u32x4*>(rho + (nbase + io.off[it])));
     }
-    op.template compute<FULL>(reinterpret_cast<T*>(lds[b]));
+    op.template compute<FULL>(reinterpret_cast<double*>(lds[b]));
     lds_barrier();  // results complete
 #pragma unroll
     for (int it = 0; it < IO::ITERS; ++it)
@@ -241,10 +240,9 @@ __device__ inline double real_entry(const f64x2* S, int k, uint32_t a, uint32_t 
 }
 
 // fragment element e of a packed real operand: its row and column (real.hpp, OpReal)
-template <typename T>
 __device__ inline void real_frag_index(int e, int KS, int* row, int* col) {
   const int lane = e & 63, rest = e >> 6, s = rest % KS, m = rest / KS, i = lane & 15;
-  *row = 16 * m + (Mfma<T>::kRowsStrided ? i : (i >> 2) + 4 * (i & 3));
+  *row = 16 * m + i;
   *col = 4 * s + (lane >> 4);
 }
 

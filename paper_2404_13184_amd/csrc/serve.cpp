@@ -304,7 +304,7 @@ void tanq_server_s::admit_one(ServeRequest* r) {
   double* d_sops = (double*)(tmp + ops_b + blk_b + kr_b);
   if (real_form(p)) {
     launch_build_real(d_ops, (int)L.ops.size(), d_kraus, d_sops, adm_stream);
-    launch_compose_real(d_blk, (int)L.blocks.size(), w, d_ops, d_sops, arena_base + keep_off + rho_b, p, adm_stream);
+    launch_compose_real(d_blk, (int)L.blocks.size(), w, d_ops, d_sops, arena_base + keep_off + rho_b, adm_stream);
   } else {
     run_fuse_kernels(L, d_ops, d_blk, d_kraus, d_sops, (double*)(tmp + ops_b + blk_b + kr_b + sop_b),
                      arena_base + keep_off + rho_b, p, adm_stream);
@@ -313,7 +313,7 @@ void tanq_server_s::admit_one(ServeRequest* r) {
   // on the same stream, and only admissions allocate from the arena
   arena.release(tmp_off, tmp_size);
   if (real_form(p))
-    launch_real_init(arena_base + r->rho_off, r->n, p, adm_stream);
+    launch_real_init(arena_base + r->rho_off, r->n, adm_stream);
   else
     launch_init_zero(arena_base + r->rho_off, r->n, p, adm_stream);
   // the batched launches (on the other stream) take the request only once this has completed,
@@ -334,7 +334,7 @@ void tanq_server_s::admit_one(ServeRequest* r) {
         tbits[t] = L.host[i].qubits[t];
         tbits[w + t] = L.host[i].qubits[t] + r->n;
       }
-      r->geom[i].rg = make_real_geom(2 * r->n, w, tbits, vb, p);
+      r->geom[i].rg = make_real_geom(2 * r->n, w, tbits, vb);
     } else
       r->geom[i].g = make_apply_geom(r->n, w, L.host[i].qubits, vb, p);
   }
@@ -494,7 +494,7 @@ void tanq_server_s::run_iteration() {
       uint64_t* masks = (uint64_t*)(hres + 1 + nprob + 2 * np);
       if (np) std::memcpy(masks, r->paulis.data(), 3 * np * sizeof(uint64_t));
       if (real_form(p)) {
-        launch_real_outputs(rho, r->n, p, r->want_probs, (int)np, masks, hres, stream);
+        launch_real_outputs(rho, r->n, r->want_probs, (int)np, masks, hres, stream);
       } else {
         launch_probs(rho, r->n, p, 1, nullptr, nullptr, probs_dev, partials, r->want_probs ? hres + 1 : nullptr, hres,
                      stream);
