@@ -889,6 +889,8 @@ tanq_status tanq_fuse(tanq_circuit c, int max_width, tanq_prec p, void* hip_stre
       constexpr size_t kShareMax = (size_t)16 << 20;
       unsigned char* tmp = nullptr;
       unsigned char* own_tmp = nullptr;
+      // outlives the stream's work on every way out: the copy reads it
+      std::unique_ptr<unsigned char[]> up(new unsigned char[up_b]);
       try {
         TANQ_HIP(hipMalloc((void**)&f->mem, keep_b + (tmp_b <= kShareMax ? tmp_b : 0)));
         if (tmp_b <= kShareMax) {
@@ -899,7 +901,6 @@ tanq_status tanq_fuse(tanq_circuit c, int max_width, tanq_prec p, void* hip_stre
         }
         f->raw = (double*)f->mem;
         f->packed = f->mem + raw_b;
-        std::unique_ptr<unsigned char[]> up(new unsigned char[up_b]);
         std::memcpy(up.get(), L.ops.data(), L.ops.size() * sizeof(FuseOpDev));
         std::memcpy(up.get() + ops_b, L.blocks.data(), L.blocks.size() * sizeof(FuseBlockDev));
         if (!rb.empty()) std::memcpy(up.get() + ops_b + blk_b, rb.data(), rb.size() * sizeof(RealPackDev));
