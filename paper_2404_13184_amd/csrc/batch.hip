@@ -216,7 +216,7 @@ __global__ __launch_bounds__(NT, (BatchMinBlocks<T, K>::value)) void batch_apply
 // FP64 states are kept in real form (real.hpp): half the bytes of vec(rho) and one real product per
 // superoperator in place of the complex form's three or four.  Bound by the state traffic at 11
 // and 12 qubits, by launches below.  Bursts of 40 requests, complex form -> real form: 4-12 qubits
-// at width 3 147 -> 66.7 ms, 4-11 qubits at width 2 95 -> 49 ms.  FP32 keeps vec(rho), although the
+// at width 3 147 -> 75 ms, 4-11 qubits at width 2 99 -> 50 ms.  FP32 keeps vec(rho), although the
 // real form serves it 1.9 times faster (82 -> 43 ms) with a fifth of the error: its results are
 // defined by their rounding in single precision, which would change in the seventh digit.
 template <int K, int VMAX, int NT>
