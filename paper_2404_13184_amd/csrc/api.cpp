@@ -267,26 +267,45 @@ bool herm_list(int launches, int n, tanq_prec p, int lim) {
   return p == TANQ_F64 && n >= kHermMinN && n <= kHermMaxN && lim >= 2 && launches >= herm_min_launches(n);
 }
 
-// Whether an operation sets elements of rho to zero whatever rho is: a measurement, a reset, a post-selection.  Element
-// (r, c) of its result is a sum of products of row r and the conjugate of row c of each Kraus matrix.
+// Whether an operation (m Kraus matrices on j qubits) sets an element of rho to zero whatever rho is, as a
+// measurement, a reset and a post-selection do: a row of sum_i conj(K_i) (x) K_i is exactly zero.  The search of row
+// (a, c) starts at its diagonal, where nearly every operation has an entry: m products a row.
 //
 // Lists with such an operation keep vec(rho).  What is left after it may be a rare branch, whose coherences the
 // real form knows only to the rounding of larger ones between the same qubits, and circuits of this kind have
 // expectations that vanish by symmetry, which stay those of the blocks one by one, bit for bit.  (8 layers of
 // teleportation on 11 qubits, 25 launches, would take 0.60 ms in real form and take 1.15 ms.)
-bool clears_elements(const HostOp& op) {
-  const int d = 1 << op.j;
-  uint64_t kept = 0;  // pairs of rows that some Kraus matrix has both of
-  for (int i = 0; i < op.m; ++i) {
-    const double* K = op.K() + (size_t)i * d * d * 2;
-    uint32_t rows = 0;
-    for (int r = 0; r < d; ++r)
-      if (std::any_of(K + (size_t)r * d * 2, K + (size_t)(r + 1) * d * 2, [](double v) { return v != 0.0; })) rows |= 1u << r;
-    if (rows == (1u << d) - 1u) return false;
-    for (int r = 0; r < d; ++r)
-      if ((rows >> r) & 1u) kept |= (uint64_t)rows << (r * d);
+bool clears_elements(const double* K, int j, int m) {
+  const int d = 1 << j;
+  auto zero = [&](int a, int b, int c, int e) {  // sum_i K_i[a][b] conj(K_i[c][e])
+    double re = 0.0, im = 0.0;
+    for (int i = 0; i < m; ++i) {
+      const double* x = K + 2 * ((size_t)i * d * d + a * d + b);
+      const double* y = K + 2 * ((size_t)i * d * d + c * d + e);
+      re += x[0] * y[0] + x[1] * y[1];
+      im += x[1] * y[0] - x[0] * y[1];
+    }
+    return re == 0.0 && im == 0.0;
+  };
+  for (int a = 0; a < d; ++a)
+    for (int c = 0; c < d; ++c) {
+      int t = 0;
+      while (t < d * d && zero(a, a ^ (t & (d - 1)), c, c ^ (t >> j))) ++t;
+      if (t == d * d) return true;
+    }
+  return false;
+}
+
+// The operations of a layout; a Kraus set that several share is looked at once (each new one follows the last in the
+// pool).
+bool clears_elements(const FuseLayout& L) {
+  int64_t next = 0;
+  for (const FuseOpDev& op : L.ops) {
+    if (op.kraus_off != next) continue;
+    if (clears_elements(L.kraus.data() + 2 * op.kraus_off, op.j, op.m)) return true;
+    next += (int64_t)op.m << (2 * op.j);
   }
-  return kept != (d == 8 ? ~0ull : (1ull << (d * d)) - 1ull);
+  return false;
 }
 
 // Length of the run that starts at block i (blocks before `end`) on a small state: the consecutive blocks of
@@ -851,8 +870,7 @@ tanq_status tanq_fuse(tanq_circuit c, int max_width, tanq_prec p, void* hip_stre
       const int nblk = (int)f->blocks.size();
       std::vector<RealPackDev> rb;
       size_t real_elems = 0;
-      if (herm_list(count_launches(at, 0, nblk, n, p, pass_limit()), n, p, pass_limit()) &&
-          std::none_of(c->ops.begin(), c->ops.end(), clears_elements)) {
+      if (herm_list(count_launches(at, 0, nblk, n, p, pass_limit()), n, p, pass_limit()) && !clears_elements(L)) {
         rb.resize(nblk);
         for (int i = 0; i < nblk; ++i) {
           const FusedBlockHost& b = f->blocks[i];

@@ -51,6 +51,8 @@ def test_teleportation_keeps_its_bits(n, width):
 CLEARING = {
     "dephase": (W.dephase(), 1),
     "reset": (W.reset(), 1),
+    # the dephasing of a measurement as a mixture of I and Z
+    "mixture": ([np.sqrt(0.5) * W.I2, np.sqrt(0.5) * W.PZ], 1),
     "agree": (W.agree_projector(), 2),
     "three": ([np.diag([1.0] * 7 + [0.0]), np.diag([0.0] * 7 + [1.0])], 3),
 }
