@@ -1,6 +1,6 @@
 """Host check of the real-form passes' geometry (pass_geom.cpp), built with the host compiler: the LDS swizzle leaves the
 operand accesses of all but a few of the superoperators free of bank conflicts, and finding it takes microseconds, since the
-first application of every list pays for it (random columns took up to 25 ms a pass)."""
+first application of every list pays for it (random columns took up to 12 ms a pass)."""
 import os
 import subprocess
 
